@@ -21,12 +21,17 @@
 
 namespace pc {
 
-hipError_t launch_convert(const double *ra, const double *dec, int64_t n, double4 *a64, float4 *a32,
-                          int *err, hipStream_t st);
-hipError_t launch_zero(unsigned long long *p, int64_t n, hipStream_t st);
+// preparation steps that do not depend on the tile size (pc_prep.hip)
+hipError_t launch_zero(void *p, size_t bytes, hipStream_t st);
+int64_t convert_blocks(int64_t n);
+int64_t order_blocks(int64_t n);
+uint32_t order_buckets(int64_t n, int per_point);
+size_t scan_sums_words(int64_t m);
+hipError_t launch_convert(const SrcDesc *srcs, int n_srcs, int64_t blocks, hipStream_t st);
+hipError_t launch_order(const ViewDesc *views, int n_views, int64_t blocks, uint32_t *hist, int64_t buckets,
+                        uint32_t *sums, hipStream_t st);
 hipError_t launch_add_copies(unsigned long long *dst, const unsigned long long *src, int64_t n, int32_t n_copies,
                              hipStream_t st);
-size_t sort_scratch_words(int64_t n);
 
 // the per-tile-size steps (pc_kernels.hip, pc_prep.hip; one instance per size)
 #define PC_TILE_STEPS                                                                                              \
@@ -36,8 +41,7 @@ size_t sort_scratch_words(int64_t n);
                             uint64_t total_items, uint32_t lut_lds_off, uint32_t stage_lds_off,                    \
                             unsigned long long *queue, unsigned long long *rechecked, int chunk,                   \
                             uint32_t lds_bytes, int grid, uint64_t flush_cap, hipStream_t st);                     \
-    hipError_t launch_sort(const double4 *src, int64_t base, int64_t n, uint32_t *scratch, double4 *a64s,          \
-                           float4 *a32s, float4 *g32s, double4 *bounds, hipStream_t st);                           \
+    hipError_t launch_bounds(const ViewDesc *views, int n_views, int64_t tiles, hipStream_t st);                   \
     hipError_t launch_prune(const SegDesc *segs, int32_t n_segs, const TableDesc *tabs, int64_t total_rows,        \
                             uint64_t *survivors, uint64_t *sub, unsigned long long *meta, int32_t mfma_ok,         \
                             int32_t split_ok, hipStream_t st);                                                     \
@@ -54,14 +58,14 @@ struct TileOps {
     int subs;
     bool matrix_cores;
     decltype(&t256::launch_count) launch_count;
-    decltype(&t256::launch_sort) launch_sort;
+    decltype(&t256::launch_bounds) launch_bounds;
     decltype(&t256::launch_prune) launch_prune;
     decltype(&t256::count_occupancy) count_occupancy;
     decltype(&t256::set_max_lds) set_max_lds;
 };
-static const TileOps kTile256 = {256, 4, true, t256::launch_count, t256::launch_sort, t256::launch_prune,
+static const TileOps kTile256 = {256, 4, true, t256::launch_count, t256::launch_bounds, t256::launch_prune,
                                  t256::count_occupancy, t256::set_max_lds};
-static const TileOps kTile128 = {128, 2, false, t128::launch_count, t128::launch_sort, t128::launch_prune,
+static const TileOps kTile128 = {128, 2, false, t128::launch_count, t128::launch_bounds, t128::launch_prune,
                                  t128::count_occupancy, t128::set_max_lds};
 // the tile size resident catalogues are ordered and bounded for
 static const TileOps &kResidentTile = kTile256;
@@ -447,7 +451,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         const pc_catalog *c = nullptr;
         std::shared_ptr<Resident> res;
         int64_t n = 0;
-        size_t o_a64 = 0, o_ra = 0, o_dec = 0;
+        size_t o_a64 = 0, o_ra = 0, o_dec = 0, o_ext = 0;
     };
     std::vector<Source> srcs;
     std::map<std::tuple<const double *, const double *, int64_t>, int> src_of_ptr;
@@ -494,11 +498,15 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         int src = -1;
         int64_t b = 0, e = 0;
         bool resident_full = false;
-        size_t o_a64s = 0, o_a32s = 0, o_g32s = 0, o_bounds = 0;
+        size_t o_a64s = 0, o_a32s = 0, o_g32s = 0, o_bounds = 0, o_keys = 0;
+        int64_t hist0 = 0;
+        uint32_t buckets = 0;
     };
     std::vector<View> views;
     std::map<std::tuple<int, int64_t, int64_t>, int> view_of;
-    int64_t max_sort_n = 0;
+    // which ordered forms the launch's kernels read: plain binary32 (vector
+    // paths), tile-centred Gram form (pruned mixed launches)
+    const bool need_a32 = !fp64, need_g32 = prune && !fp64;
     auto add_view = [&](int src, int64_t b, int64_t e) -> int {
         auto key = std::make_tuple(src, b, e);
         auto it = view_of.find(key);
@@ -515,10 +523,9 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         } else if (n > 0) {
             v.o_a64s = ar.take(sizeof(double4) * static_cast<size_t>(n));
             // binary32 copies padded: the kernel reads a step of j-points ahead
-            v.o_a32s = ar.take(sizeof(float4) * static_cast<size_t>(n + kJPad));
-            v.o_g32s = ar.take(sizeof(float4) * static_cast<size_t>(n + kJPad));
+            if (need_a32) v.o_a32s = ar.take(sizeof(float4) * static_cast<size_t>(n + kJPad));
+            if (need_g32) v.o_g32s = ar.take(sizeof(float4) * static_cast<size_t>(n + kJPad));
             v.o_bounds = ar.take(sizeof(double4) * static_cast<size_t>(n_tiles(n, tile) * (1 + T.subs)));
-            max_sort_n = std::max(max_sort_n, n);
         }
         const int id = static_cast<int>(views.size());
         view_of.emplace(key, id);
@@ -612,11 +619,12 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     }
     const size_t o_err = o_res + sizeof(unsigned long long) * res_words;
     const size_t o_meta = o_res;
-    // the prune pass's copies of every job's counters (zeroed with the results)
+    // the prune pass's copies of every job's counters, the sources' extents
+    // and the ordering counters follow the results: zeroed by one launch
     const size_t count_words = res_words - kMetaWords;
     const size_t o_pcopies = ar.take(sizeof(unsigned long long) * kPruneStripes * count_words);
-    const size_t zero_words = (o_pcopies - o_res) / sizeof(unsigned long long) + kPruneStripes * count_words;
-    const size_t o_scratch = ar.take(sizeof(uint32_t) * (max_sort_n > 0 ? sort_scratch_words(max_sort_n) : 1));
+    for (Source &sc : srcs)
+        if (!sc.res) sc.o_ext = ar.take(sizeof(uint32_t) * kExtWords);
 
     // ---- segments
     std::vector<SegDesc> segs;
@@ -661,13 +669,35 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     if (items_overflow || items > kItemMask)
         return fail(PC_ERR_INVALID, "too many tile pairs in one call (more than " + std::to_string(kItemMask) +
                                         "); split the catalogues into row ranges");
-    const size_t o_segs = ar.take(sizeof(SegDesc) * std::max<size_t>(segs.size(), 1));
-    const size_t o_tabs = ar.take(sizeof(TableDesc) * tabs.size());
-    const size_t o_surv = ar.take(sizeof(uint64_t) * std::max<uint64_t>(prune ? items : 1, 1));
     // split survivors: the prune pass looks at the j-tile's sub-blocks too
     // (mixed mode); their descriptions sit beside the survivors
     const bool split = PC_SPLIT && prune && !fp64;
-    const size_t o_sub = ar.take(sizeof(uint64_t) * std::max<uint64_t>(split ? items : 1, 1));
+    // the ordering's counters and keys are done with when the prune pass
+    // writes the survivors: one region holds the one, then the other
+    int64_t hist_words = 0;
+    size_t order_bytes = 0;
+    for (View &v : views) {
+        if (v.resident_full || v.e <= v.b) continue;
+        v.hist0 = hist_words;
+        v.buckets = order_buckets(v.e - v.b, prune ? 4 : 2);
+        hist_words += v.buckets;
+    }
+    order_bytes = sizeof(uint32_t) * static_cast<size_t>(hist_words);
+    for (View &v : views) {
+        if (v.resident_full || v.e <= v.b) continue;
+        v.o_keys = order_bytes;  // from the region's start
+        order_bytes += sizeof(uint32_t) * static_cast<size_t>((v.e - v.b + 63) & ~int64_t(63));
+    }
+    const size_t surv_bytes = sizeof(uint64_t) * std::max<uint64_t>(prune ? items : 1, 1);
+    const size_t o_region =
+        ar.take(std::max(order_bytes, surv_bytes + (split ? sizeof(uint64_t) * std::max<uint64_t>(items, 1) : 0)));
+    const size_t o_surv = o_region, o_sub = o_region + surv_bytes;
+    const size_t zero_bytes = (o_region - o_res + sizeof(uint32_t) * static_cast<size_t>(hist_words) + 15) & ~size_t(15);
+    const size_t o_sums = ar.take(sizeof(uint32_t) * std::max<size_t>(scan_sums_words(hist_words), 4));
+    // descriptors, sent with one copy: sources | views | segments | tables
+    const size_t b_srcs = sizeof(SrcDesc) * srcs.size(), b_views = sizeof(ViewDesc) * views.size(),
+                 b_segs = sizeof(SegDesc) * segs.size(), b_tabs = sizeof(TableDesc) * tabs.size();
+    const size_t o_desc = ar.take(b_srcs + b_views + b_segs + b_tabs);
     std::vector<size_t> o_blob(blobs.size());
     for (size_t k = 0; k < blobs.size(); ++k) o_blob[k] = ar.take(blobs[k].bytes.size());
     if (plan_only) {
@@ -697,33 +727,42 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         W = static_cast<unsigned char *>(ws.mem);
     }
 
-    // ---- convert the sources (validity flags read back at the end)
-    PC_HIP(launch_zero(reinterpret_cast<unsigned long long *>(W + o_res), static_cast<int64_t>(zero_words), st),
-           "zero results");
+    // ---- the sources to convert (validity flags read back at the end) and
+    // the views to order
     std::vector<const double4 *> src_a64(srcs.size(), nullptr);
+    std::vector<const uint32_t *> src_ext(srcs.size(), nullptr);
+    std::vector<SrcDesc> sds;
+    int64_t conv_blocks = 0;
     for (size_t k = 0; k < srcs.size(); ++k) {
         if (srcs[k].res) {
             src_a64[k] = srcs[k].res->a64;
+            src_ext[k] = srcs[k].res->ext;
             continue;
         }
         const pc_catalog *c = srcs[k].c;
         src_a64[k] = reinterpret_cast<const double4 *>(W + srcs[k].o_a64);
+        src_ext[k] = reinterpret_cast<const uint32_t *>(W + srcs[k].o_ext);
         if (c->n <= 0) continue;
-        const double *ra = c->ra_deg, *dec = c->dec_deg;
+        SrcDesc d;
+        d.ra = c->ra_deg;
+        d.dec = c->dec_deg;
         if (!c->on_device) {
             double *dra = reinterpret_cast<double *>(W + srcs[k].o_ra);
             double *ddec = reinterpret_cast<double *>(W + srcs[k].o_dec);
-            PC_HIP(hipMemcpyAsync(dra, ra, sizeof(double) * c->n, hipMemcpyHostToDevice, st), "H2D ra");
-            PC_HIP(hipMemcpyAsync(ddec, dec, sizeof(double) * c->n, hipMemcpyHostToDevice, st), "H2D dec");
-            ra = dra;
-            dec = ddec;
+            PC_HIP(hipMemcpyAsync(dra, c->ra_deg, sizeof(double) * c->n, hipMemcpyHostToDevice, st), "H2D ra");
+            PC_HIP(hipMemcpyAsync(ddec, c->dec_deg, sizeof(double) * c->n, hipMemcpyHostToDevice, st), "H2D dec");
+            d.ra = dra;
+            d.dec = ddec;
         }
-        PC_HIP(launch_convert(ra, dec, c->n, reinterpret_cast<double4 *>(W + srcs[k].o_a64), nullptr,
-                              reinterpret_cast<int *>(W + o_err) + k, st),
-               "convert");
+        d.a64 = reinterpret_cast<double4 *>(W + srcs[k].o_a64);
+        d.a32 = nullptr;
+        d.err = reinterpret_cast<int *>(W + o_err) + k;
+        d.ext = reinterpret_cast<uint32_t *>(W + srcs[k].o_ext);
+        d.n = c->n;
+        d.blk0 = conv_blocks;
+        conv_blocks += convert_blocks(c->n);
+        sds.push_back(d);
     }
-
-    // ---- spatially ordered views and their tile bounds
     struct ViewPtrs {
         const double4 *a64s = nullptr;
         const float4 *a32s = nullptr;
@@ -732,6 +771,9 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         const double4 *sub_bounds = nullptr;  // T.subs per tile, after the tiles' own
     };
     std::vector<ViewPtrs> vp(views.size());
+    std::vector<ViewDesc> vds;
+    int64_t ord_blocks = 0, all_tiles = 0;
+    uint32_t points = 0;
     for (size_t v = 0; v < views.size(); ++v) {
         const View &vw = views[v];
         if (vw.resident_full) {
@@ -745,18 +787,31 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         }
         const int64_t n = vw.e - vw.b;
         if (n <= 0) continue;
-        double4 *a64s = reinterpret_cast<double4 *>(W + vw.o_a64s);
-        float4 *a32s = reinterpret_cast<float4 *>(W + vw.o_a32s);
-        float4 *g32s = reinterpret_cast<float4 *>(W + vw.o_g32s);
-        double4 *bnd = reinterpret_cast<double4 *>(W + vw.o_bounds);
-        PC_HIP(T.launch_sort(src_a64[vw.src], vw.b, n, reinterpret_cast<uint32_t *>(W + o_scratch), a64s, a32s, g32s,
-                           bnd, st),
-               "sort");
-        vp[v].a64s = a64s;
-        vp[v].a32s = a32s;
-        vp[v].g32s = g32s;
-        vp[v].bounds = bnd;
-        vp[v].sub_bounds = bnd + n_tiles(n, tile);
+        ViewDesc d;
+        d.src = src_a64[vw.src] + vw.b;
+        d.ext = src_ext[vw.src];
+        d.keys = reinterpret_cast<uint32_t *>(W + o_region + vw.o_keys);
+        d.hist = reinterpret_cast<uint32_t *>(W + o_region) + vw.hist0;
+        d.a64s = reinterpret_cast<double4 *>(W + vw.o_a64s);
+        d.a32s = need_a32 ? reinterpret_cast<float4 *>(W + vw.o_a32s) : nullptr;
+        d.g32s = need_g32 ? reinterpret_cast<float4 *>(W + vw.o_g32s) : nullptr;
+        d.bounds = reinterpret_cast<double4 *>(W + vw.o_bounds);
+        d.n = n;
+        d.hist0 = vw.hist0;
+        d.blk0 = ord_blocks;
+        d.tile0 = all_tiles;
+        d.tiles = n_tiles(n, tile);
+        d.buckets = vw.buckets;
+        d.points0 = points;
+        ord_blocks += order_blocks(n);
+        all_tiles += d.tiles;
+        points += static_cast<uint32_t>(n);
+        vds.push_back(d);
+        vp[v].a64s = d.a64s;
+        vp[v].a32s = d.a32s;
+        vp[v].g32s = d.g32s;
+        vp[v].bounds = d.bounds;
+        vp[v].sub_bounds = d.bounds + d.tiles;
     }
 
     // ---- descriptors
@@ -824,16 +879,29 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         return fail(PC_ERR_INVALID, "edge set needs " + std::to_string(lds_bytes) +
                                         " bytes of LDS per wave; the device allows " +
                                         std::to_string(di->lds_per_block));
-    if (!segs.empty())
-        PC_HIP(hipMemcpyAsync(W + o_segs, segs.data(), sizeof(SegDesc) * segs.size(), hipMemcpyHostToDevice, st),
-               "H2D segments");
-    PC_HIP(hipMemcpyAsync(W + o_tabs, tds.data(), sizeof(TableDesc) * tds.size(), hipMemcpyHostToDevice, st),
-           "H2D tables");
+    // ---- send the descriptors; zero, convert, order, bound
+    std::vector<unsigned char> desc(b_srcs + b_views + b_segs + b_tabs);
+    auto put = [&](size_t at, const void *p, size_t bytes) {
+        if (bytes) memcpy(desc.data() + at, p, bytes);
+    };
+    put(0, sds.data(), sizeof(SrcDesc) * sds.size());
+    put(b_srcs, vds.data(), sizeof(ViewDesc) * vds.size());
+    put(b_srcs + b_views, segs.data(), b_segs);
+    put(b_srcs + b_views + b_segs, tds.data(), b_tabs);
+    PC_HIP(hipMemcpyAsync(W + o_desc, desc.data(), desc.size(), hipMemcpyHostToDevice, st), "H2D descriptors");
+    const SrcDesc *d_srcs = reinterpret_cast<const SrcDesc *>(W + o_desc);
+    const ViewDesc *d_views = reinterpret_cast<const ViewDesc *>(W + o_desc + b_srcs);
+    PC_HIP(launch_zero(W + o_res, zero_bytes, st), "zero results");
+    PC_HIP(launch_convert(d_srcs, static_cast<int>(sds.size()), conv_blocks, st), "convert");
+    PC_HIP(launch_order(d_views, static_cast<int>(vds.size()), ord_blocks, reinterpret_cast<uint32_t *>(W + o_region),
+                        hist_words, reinterpret_cast<uint32_t *>(W + o_sums), st),
+           "order");
+    PC_HIP(T.launch_bounds(d_views, static_cast<int>(vds.size()), all_tiles, st), "bounds");
     unsigned long long *meta = reinterpret_cast<unsigned long long *>(W + o_meta);
 
     // ---- whole-tile-pair binning, then the counting kernel over the rest
-    const SegDesc *d_segs = reinterpret_cast<const SegDesc *>(W + o_segs);
-    const TableDesc *d_tabs = reinterpret_cast<const TableDesc *>(W + o_tabs);
+    const SegDesc *d_segs = reinterpret_cast<const SegDesc *>(W + o_desc + b_srcs + b_views);
+    const TableDesc *d_tabs = reinterpret_cast<const TableDesc *>(W + o_desc + b_srcs + b_views + b_segs);
     uint64_t *surv = reinterpret_cast<uint64_t *>(W + o_surv);
     uint64_t *sub_words = reinterpret_cast<uint64_t *>(W + o_sub);
     int grid = 0;
@@ -943,14 +1011,24 @@ int upload_catalog(const pc_catalog *c, hipStream_t st, uint64_t *handle) {
     const size_t og32s = ar.take(sizeof(float4) * (n + kJPad));
     const size_t ob = ar.take(sizeof(double4) * static_cast<size_t>(n_tiles(static_cast<int64_t>(n), kResidentTile.tile) *
                                                                      (1 + kResidentTile.subs)));
-    const size_t oerr = ar.take(sizeof(int));
-    const size_t osc = ar.take(sizeof(uint32_t) * sort_scratch_words(static_cast<int64_t>(n)));
+    const size_t oerr = ar.take(sizeof(int) * 4 + sizeof(uint32_t) * kExtWords);  // flag, then the extent
+    const size_t odesc = ar.take(sizeof(SrcDesc) + sizeof(ViewDesc));
+    // ordering scratch, given back when the upload is done
+    Arena tmp;
+    const uint32_t buckets = order_buckets(static_cast<int64_t>(n), 4);
+    const size_t ohist = tmp.take(sizeof(uint32_t) * buckets);
+    const size_t okeys = tmp.take(sizeof(uint32_t) * n);
+    const size_t osums = tmp.take(sizeof(uint32_t) * std::max<size_t>(scan_sums_words(buckets), 4));
     size_t ora = 0, odec = 0;
     if (!c->on_device) {
-        ora = ar.take(sizeof(double) * n);
-        odec = ar.take(sizeof(double) * n);
+        ora = tmp.take(sizeof(double) * n);
+        odec = tmp.take(sizeof(double) * n);
     }
     PC_HIP(injected_alloc_failure() ? hipErrorOutOfMemory : hipMalloc(&r->d_mem, ar.size), "hipMalloc(catalogue)");
+    Workspace ws;
+    ws.st = st;
+    PC_HIP(hipMallocAsync(&ws.mem, tmp.size, st), "hipMallocAsync(catalogue scratch)");
+    unsigned char *S = static_cast<unsigned char *>(ws.mem);
     unsigned char *W = static_cast<unsigned char *>(r->d_mem);
     r->a64 = reinterpret_cast<double4 *>(W + o64);
     r->a32 = reinterpret_cast<float4 *>(W + o32);
@@ -958,19 +1036,46 @@ int upload_catalog(const pc_catalog *c, hipStream_t st, uint64_t *handle) {
     r->a32s = reinterpret_cast<float4 *>(W + o32s);
     r->g32s = reinterpret_cast<float4 *>(W + og32s);
     r->bounds = reinterpret_cast<double4 *>(W + ob);
-    PC_HIP(hipMemsetAsync(W + oerr, 0, sizeof(int), st), "hipMemsetAsync");
+    r->ext = reinterpret_cast<uint32_t *>(W + oerr) + 4;
+    PC_HIP(launch_zero(W + oerr, sizeof(int) * 4 + sizeof(uint32_t) * kExtWords, st), "zero");
     if (c->n > 0) {
-        const double *ra = c->ra_deg, *dec = c->dec_deg;
+        struct {
+            SrcDesc s;
+            ViewDesc v;
+        } d = {};
+        d.s.ra = c->ra_deg;
+        d.s.dec = c->dec_deg;
         if (!c->on_device) {
-            PC_HIP(hipMemcpyAsync(W + ora, ra, sizeof(double) * c->n, hipMemcpyHostToDevice, st), "H2D ra");
-            PC_HIP(hipMemcpyAsync(W + odec, dec, sizeof(double) * c->n, hipMemcpyHostToDevice, st), "H2D dec");
-            ra = reinterpret_cast<const double *>(W + ora);
-            dec = reinterpret_cast<const double *>(W + odec);
+            PC_HIP(hipMemcpyAsync(S + ora, c->ra_deg, sizeof(double) * c->n, hipMemcpyHostToDevice, st), "H2D ra");
+            PC_HIP(hipMemcpyAsync(S + odec, c->dec_deg, sizeof(double) * c->n, hipMemcpyHostToDevice, st), "H2D dec");
+            d.s.ra = reinterpret_cast<const double *>(S + ora);
+            d.s.dec = reinterpret_cast<const double *>(S + odec);
         }
-        PC_HIP(launch_convert(ra, dec, c->n, r->a64, r->a32, reinterpret_cast<int *>(W + oerr), st), "convert");
-        PC_HIP(kResidentTile.launch_sort(r->a64, 0, c->n, reinterpret_cast<uint32_t *>(W + osc), r->a64s, r->a32s, r->g32s,
-                           r->bounds, st),
-               "sort");
+        d.s.a64 = r->a64;
+        d.s.a32 = r->a32;
+        d.s.err = reinterpret_cast<int *>(W + oerr);
+        d.s.ext = r->ext;
+        d.s.n = c->n;
+        d.v.src = r->a64;
+        d.v.ext = r->ext;
+        d.v.keys = reinterpret_cast<uint32_t *>(S + okeys);
+        d.v.hist = reinterpret_cast<uint32_t *>(S + ohist);
+        d.v.a64s = r->a64s;
+        d.v.a32s = r->a32s;
+        d.v.g32s = r->g32s;
+        d.v.bounds = r->bounds;
+        d.v.n = c->n;
+        d.v.tiles = n_tiles(c->n, kResidentTile.tile);
+        d.v.buckets = buckets;
+        PC_HIP(hipMemcpyAsync(W + odesc, &d, sizeof(d), hipMemcpyHostToDevice, st), "H2D descriptors");
+        const SrcDesc *ds = reinterpret_cast<const SrcDesc *>(W + odesc);
+        const ViewDesc *dv = reinterpret_cast<const ViewDesc *>(W + odesc + sizeof(SrcDesc));
+        PC_HIP(launch_zero(S + ohist, sizeof(uint32_t) * buckets, st), "zero");
+        PC_HIP(launch_convert(ds, 1, convert_blocks(c->n), st), "convert");
+        PC_HIP(launch_order(dv, 1, order_blocks(c->n), reinterpret_cast<uint32_t *>(S + ohist), buckets,
+                            reinterpret_cast<uint32_t *>(S + osums), st),
+               "order");
+        PC_HIP(kResidentTile.launch_bounds(dv, 1, d.v.tiles, st), "bounds");
     }
     int flag = 0;
     PC_HIP(hipMemcpyAsync(&flag, W + oerr, sizeof(int), hipMemcpyDeviceToHost, st), "D2H flag");

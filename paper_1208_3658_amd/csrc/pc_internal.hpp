@@ -175,6 +175,32 @@ struct SegDesc {
     int64_t pstride;
 };
 
+// A catalogue to convert (n > 0): RA/Dec arrays on the device to unit vectors.
+struct SrcDesc {
+    const double *ra, *dec;
+    double4 *a64;
+    float4 *a32;            // binary32 copy, or null
+    int *err;               // validity flag
+    uint32_t *ext;          // kExtWords zeroed words: the extent on each cube face (see k_convert)
+    int64_t n;
+    int64_t blk0;           // first block of the conversion launch
+};
+constexpr int kExtWords = 24;
+
+// An index range of a source to order spatially (n > 0).
+struct ViewDesc {
+    const double4 *src;     // first point of the range
+    const uint32_t *ext;    // extent of its source
+    uint32_t *keys;         // n words
+    uint32_t *hist;         // `buckets` zeroed counters, hist0 words into the launch's counters
+    double4 *a64s;          // ordered copies: binary64,
+    float4 *a32s, *g32s;    // binary32 (or null), Gram form centred on the tile (or null)
+    double4 *bounds;        // of its tiles, then of their sub-blocks
+    int64_t n, hist0, blk0, tile0, tiles;  // blk0, tile0: first block of the ordering, of the bounds launch
+    uint32_t buckets;
+    uint32_t points0;       // points of the views before
+};
+
 // Host-side form of an edge set.
 struct HostTable {
     // histogram columns and row size of each kernel's layout (the cell tables

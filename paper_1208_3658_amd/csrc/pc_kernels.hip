@@ -20,66 +20,8 @@
 //     64-bit global counters when the job changes and at the end; the
 //     few-edge paths count in registers and touch LDS once per item.
 #include "pc_internal.hpp"
-#include "pc_math.h"
 
 namespace pc {
-
-#if PC_R == 4
-// ------------------- tile-independent part (compiled once, 256-point build)
-
-// -------------------------------------------------------------- conversion
-
-// RA/Dec (degrees, binary64) -> unit vectors: binary64 (x, y, z, 0) and its
-// round-to-nearest binary32 copy.  Invalid inputs (non-finite, |Dec| > 90) set
-// *err and produce the vector of (0, 0).
-__global__ void __launch_bounds__(256) k_convert(const double *__restrict__ ra,
-                                                 const double *__restrict__ dec, int64_t n,
-                                                 double4 *__restrict__ a64,
-                                                 float4 *__restrict__ a32,
-                                                 int *__restrict__ err) {
-#pragma clang fp contract(off)
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    double r = ra[i], d = dec[i];
-    const bool ok = isfinite(r) && isfinite(d) && d >= -90.0 && d <= 90.0;
-    if (!ok) {
-        atomicOr(err, 1);
-        r = 0.0;
-        d = 0.0;
-    }
-    double sa, ca, sd, cd;
-    sincosd(r, &sa, &ca);
-    sincosd(d, &sd, &cd);
-    const double x = cd * ca;
-    const double y = cd * sa;
-    const double z = sd;
-    a64[i] = make_double4(x, y, z, 0.0);
-    if (a32) a32[i] = make_float4(static_cast<float>(x), static_cast<float>(y), static_cast<float>(z), 0.0f);
-}
-
-__global__ void __launch_bounds__(256) k_zero_u64(unsigned long long *p, int64_t n) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0ull;
-}
-
-// ---------------------------------------------------------------- launchers
-
-hipError_t launch_convert(const double *ra, const double *dec, int64_t n, double4 *a64, float4 *a32,
-                          int *err, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    const int64_t blocks = (n + 255) / 256;
-    k_convert<<<dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, st>>>(ra, dec, n, a64, a32, err);
-    return hipGetLastError();
-}
-
-hipError_t launch_zero(unsigned long long *p, int64_t n, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    const int64_t blocks = (n + 255) / 256;
-    k_zero_u64<<<dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, st>>>(p, n);
-    return hipGetLastError();
-}
-
-#endif  // tile-independent part
 
 // ------------------------------------------------ per tile size
 

@@ -68,6 +68,7 @@ struct Resident {
     float4 *a32s = nullptr;
     float4 *g32s = nullptr;     // ordered copy in Gram form, centred on its tile
     double4 *bounds = nullptr;  // tile bounds of the ordered copy
+    uint32_t *ext = nullptr;    // extent on each cube face (kExtWords)
     int64_t n = 0;
     int device = 0;
     ~Resident();
