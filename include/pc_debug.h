@@ -83,9 +83,11 @@ int pc_debug_set_compact_table(int32_t mode);
 
 /*
  * pc_debug_set_tile -- tile = 128 or 256: the calling thread's later counting
- * launches (except pc_autotune's own candidates) cut the pair matrix into
+ * launches (except pc_autotune's own candidates) run the vector kernel on
  * tiles of that many points whatever the tuner chose; 0 restores the default
- * (256, or the tuned size with PC_TUNED).  Counts do not depend on it.
+ * (the block kernel on pairs of 512-point tiles where it serves the launch --
+ * PC_MIXED with neither PC_NO_PRUNE nor PC_MATRIX_CORES -- the vector kernel on
+ * 256-point tiles elsewhere, or the tuned size with PC_TUNED).  Counts do not depend on it.
  * PC_ERR_INVALID for other values.
  */
 int pc_debug_set_tile(int32_t tile);
@@ -103,8 +105,9 @@ int pc_debug_fail_allocations(int32_t n);
 /*
  * pc_debug_last_launch -- facts about the calling thread's last counting
  * launch: kernel time in ms from the HIP events (-1 if timing was off),
- * number of tile-pair work items, grid size (single-wave workgroups) and LDS
- * bytes per workgroup.  Any pointer may be NULL.
+ * number of tile-pair work items (512-point tiles in the block kernel, else the
+ * launch's tile size), grid size (workgroups of one wave; of four in the block
+ * kernel) and dynamic LDS bytes per workgroup.  Any pointer may be NULL.
  */
 int pc_debug_last_launch(double *kernel_ms, uint64_t *items, int32_t *grid, uint32_t *lds_bytes);
 
@@ -118,7 +121,11 @@ int pc_debug_last_launch(double *kernel_ms, uint64_t *items, int32_t *grid, uint
  * those items).  few_items counts the work units (items, or open sub-blocks
  * of split items) with at most 3 edges inside their chord interval (binned by
  * comparing with those edges alone), gram_items those whose vector-path
- * chords are formed in tile-centred Gram form.  Any pointer may be NULL.
+ * chords are formed in tile-centred Gram form.  The block kernel (the mixed
+ * mode's pruned launches) looks at every left item in 32 x 32 blocks, all from
+ * tile-centred coordinates: there split_items and gram_items count the items
+ * with blocks left, few_items those of them with a block of at most 3 edges, and
+ * mfma_items stays 0 (it counts PC_MATRIX_CORES items).  Any pointer may be NULL.
  */
 int pc_debug_last_pruning(uint64_t *survivors, uint64_t *pairs_computed, uint64_t *pairs_total,
                           uint64_t *mfma_items, uint64_t *few_items, uint64_t *gram_items,
@@ -131,7 +138,8 @@ int pc_debug_last_pruning(uint64_t *survivors, uint64_t *pairs_computed, uint64_
  *                   binned by comparing with the m edges inside their tile
  *                   pair's (or sub-block's) chord interval; [0] the pairs
  *                   binned through the cell table (every computed pair of the
- *                   binary64 kernel and of launches with PC_NO_PRUNE).
+ *                   binary64 kernel and of launches with PC_NO_PRUNE) or, in the
+ *                   block kernel, in blocks of more than 3 edges.
  *   gram_pairs      of the few-edge pairs, those whose chords the vector path
  *                   forms in tile-centred Gram form (NULL allowed).
  *   mfma_pairs      pairs whose chords came from the matrix cores (NULL allowed).

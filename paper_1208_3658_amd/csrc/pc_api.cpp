@@ -44,10 +44,21 @@ hipError_t launch_add_copies(unsigned long long *dst, const unsigned long long *
     hipError_t launch_bounds(const ViewDesc *views, int n_views, int64_t tiles, hipStream_t st);                   \
     hipError_t launch_prune(const SegDesc *segs, int32_t n_segs, const TableDesc *tabs, int64_t total_rows,        \
                             uint64_t *survivors, uint64_t *sub, unsigned long long *meta, int32_t mfma_ok,         \
-                            int32_t split_ok, hipStream_t st);                                                     \
+                            int32_t split_ok, bool blocks, hipStream_t st);                                        \
     hipError_t count_occupancy(bool fp64, bool mc, bool compact, uint32_t lds_bytes, int *blocks_per_cu);          \
     hipError_t set_max_lds(uint32_t bytes);
 namespace t256 { PC_TILE_STEPS }
+// the block kernel (pc_blocks.hip)
+namespace blk {
+hipError_t launch_bounds(const ViewDesc *views, int n_views, int64_t tiles, hipStream_t st);
+void lds_layout(int32_t max_edges, int32_t max_cells, int32_t cols, int32_t *cols_out, int32_t *cells_out,
+                uint32_t *lds_bytes);
+hipError_t occupancy(uint32_t lds_bytes, int *per_cu);
+hipError_t launch_count(const SegDesc *segs, const TableDesc *tabs, const uint64_t *items, const uint64_t *tiles,
+                        const unsigned long long *n_items, unsigned long long *queue, unsigned long long *rechecked,
+                        unsigned long long *stats, int32_t max_edges, int32_t max_cells, int32_t cols, uint32_t lds_bytes,
+                        int chunk, uint64_t flush_cap, int grid, hipStream_t st);
+}
 namespace t128 { PC_TILE_STEPS }
 #undef PC_TILE_STEPS
 
@@ -67,7 +78,11 @@ static const TileOps kTile256 = {256, 4, true, t256::launch_count, t256::launch_
                                  t256::count_occupancy, t256::set_max_lds};
 static const TileOps kTile128 = {128, 2, false, t128::launch_count, t128::launch_bounds, t128::launch_prune,
                                  t128::count_occupancy, t128::set_max_lds};
-// the tile size resident catalogues are ordered and bounded for
+// the block kernel's preparation (its launch has its own arguments)
+static const TileOps kTileBlocks = {kBlockTile, 0, false, nullptr, blk::launch_bounds, t256::launch_prune,
+                                    nullptr, nullptr};
+// resident catalogues are ordered, and bounded for 256-point tiles and the
+// block kernel's
 static const TileOps &kResidentTile = kTile256;
 
 #ifndef PC_SPLIT
@@ -186,8 +201,10 @@ void table_blob(const HostTable &h, TableBlob *out) {
     const size_t b_lc = sizeof(LutEntryC) * h.lut32.compact.size();
     out->o_lut64 = (out->o_lutc + b_lc + 255) & ~size_t(255);
     const size_t b_l64 = sizeof(LutEntry64) * h.lut64.size();
+    out->o_lutb = (out->o_lut64 + b_l64 + 255) & ~size_t(255);
+    const size_t b_lb = sizeof(LutEntryB) * h.lutb.size();
     std::vector<unsigned char> &blob = out->bytes;
-    blob.assign(out->o_lut64 + b_l64 + 256, 0);
+    blob.assign(out->o_lutb + b_lb + 256, 0);
     memcpy(blob.data(), h.e64.data(), b_e);
     for (size_t k = 0; k < h.e64.size(); ++k) {
         const float bb[4] = {h.lo[k], h.hi[k], h.lo_g[k], h.hi_g[k]};
@@ -200,6 +217,7 @@ void table_blob(const HostTable &h, TableBlob *out) {
     if (b_l32) memcpy(blob.data() + out->o_lut32, h.lut32.entries.data(), b_l32);
     if (b_lc) memcpy(blob.data() + out->o_lutc, h.lut32.compact.data(), b_lc);
     if (b_l64) memcpy(blob.data() + out->o_lut64, h.lut64.data(), b_l64);
+    if (b_lb) memcpy(blob.data() + out->o_lutb, h.lutb.data(), b_lb);
 }
 
 void table_place(DevTable *t, const TableBlob &b, unsigned char *base) {
@@ -211,6 +229,7 @@ void table_place(DevTable *t, const TableBlob &b, unsigned char *base) {
     t->d_lut32 = base + b.o_lut32;
     t->d_lutc = t->host.lut32.compact.empty() ? nullptr : base + b.o_lutc;
     t->d_lut64 = base + b.o_lut64;
+    t->d_lutb = base + b.o_lutb;
 }
 
 int get_table(const double *theta, int32_t n_edges, std::shared_ptr<DevTable> *out, int cols) {
@@ -290,6 +309,10 @@ TableDesc table_desc(const DevTable &t, bool fp64) {
         d.band_g = t.d_band_g;
         d.fband = t.d_fband;
         d.fband_g = t.d_fband_g;
+        d.lutb = t.d_lutb;
+        d.b_shift = h.b_shift;
+        d.b_key0 = h.b_key0;
+        d.b_cells = static_cast<int32_t>(h.lutb.size());
     }
     return d;
 }
@@ -406,13 +429,20 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     } else {
         lt.matrix_cores = (mode_flags & PC_MATRIX_CORES) != 0;
     }
-    if (!tune && t_force_tile) lt.tile = t_force_tile;
+    if (!tune && t_force_tile) {
+        lt.tile = t_force_tile;
+        lt.vector = true;
+    }
     if (lt.chunk < 1 || lt.chunk > 64) return fail(PC_ERR_INVALID, "work chunk must be in [1, 64]");
     // the matrix-core path needs the prune pass's marks; binary32 only
     if (lt.tile != 0 && lt.tile != 128 && lt.tile != 256) return fail(PC_ERR_INVALID, "tile must be 128 or 256 points");
-    const TileOps &T = lt.tile == 128 ? kTile128 : kTile256;
+    const bool mc = lt.matrix_cores && prune && !fp64 && lt.tile != 128;
+    // the block kernel runs the mixed mode's pruned launches.  The vector
+    // kernels stay for 128-point tiles, for visiting every pair, for
+    // PC_MATRIX_CORES and for binary64.
+    const bool blocks = prune && !fp64 && !mc && lt.tile != 128 && !lt.vector;
+    const TileOps &T = blocks ? kTileBlocks : lt.tile == 128 ? kTile128 : kTile256;
     const int tile = T.tile;
-    const bool mc = lt.matrix_cores && prune && !fp64 && T.matrix_cores;
     // host-side validation first, so bad arguments are reported as such
     for (const BatchJob &j : jobs) {
         if (j.auto_flag != 0 && j.auto_flag != 1) return fail(PC_ERR_INVALID, "auto_flag must be 0 or 1");
@@ -498,7 +528,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         int src = -1;
         int64_t b = 0, e = 0;
         bool resident_full = false;
-        size_t o_a64s = 0, o_a32s = 0, o_g32s = 0, o_bounds = 0, o_keys = 0;
+        size_t o_a64s = 0, o_a32s = 0, o_g32s = 0, o_bounds = 0, o_groups = 0, o_keys = 0;
         int64_t hist0 = 0;
         uint32_t buckets = 0;
     };
@@ -506,7 +536,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     std::map<std::tuple<int, int64_t, int64_t>, int> view_of;
     // which ordered forms the launch's kernels read: plain binary32 (vector
     // paths), tile-centred Gram form (pruned mixed launches)
-    const bool need_a32 = !fp64, need_g32 = prune && !fp64;
+    const bool need_a32 = !fp64 && !blocks, need_g32 = prune && !fp64;
     auto add_view = [&](int src, int64_t b, int64_t e) -> int {
         auto key = std::make_tuple(src, b, e);
         auto it = view_of.find(key);
@@ -518,7 +548,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         const int64_t n = e - b;
         // a resident catalogue's own ordered copy and bounds serve a view of
         // all of it when the launch uses the tile size they were built for
-        if (srcs[src].res && b == 0 && e == srcs[src].n && &T == &kResidentTile) {
+        if (srcs[src].res && b == 0 && e == srcs[src].n && (&T == &kResidentTile || blocks)) {
             v.resident_full = true;
         } else if (n > 0) {
             v.o_a64s = ar.take(sizeof(double4) * static_cast<size_t>(n));
@@ -526,6 +556,8 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
             if (need_a32) v.o_a32s = ar.take(sizeof(float4) * static_cast<size_t>(n + kJPad));
             if (need_g32) v.o_g32s = ar.take(sizeof(float4) * static_cast<size_t>(n + kJPad));
             v.o_bounds = ar.take(sizeof(double4) * static_cast<size_t>(n_tiles(n, tile) * (1 + T.subs)));
+            if (blocks) v.o_keys = ar.take(sizeof(uint32_t) * static_cast<size_t>(n));
+            if (blocks) v.o_groups = ar.take(sizeof(float4) * static_cast<size_t>(n_tiles(n, tile) * kGroups));
         }
         const int id = static_cast<int>(views.size());
         view_of.emplace(key, id);
@@ -629,6 +661,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     // ---- segments
     std::vector<SegDesc> segs;
     uint64_t items = 0;
+    uint64_t limit_items = 0;
     bool items_overflow = false;  // more tile pairs than an item number holds
     int64_t prune_rows = 0;
     auto view_n = [&](int v) { return views[v].e - views[v].b; };
@@ -649,7 +682,13 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
             const unsigned __int128 n_items =
                 tri ? static_cast<unsigned __int128>(sd.tiles_i) * static_cast<unsigned __int128>(sd.tiles_i + 1) / 2
                     : static_cast<unsigned __int128>(sd.tiles_i) * static_cast<unsigned __int128>(sd.tiles_j);
-            if (n_items > kItemMask || items + static_cast<uint64_t>(n_items) > kItemMask) items_overflow = true;
+            // the limit counts pairs of 256-point tiles, whatever the tile size
+            const int64_t li = blocks ? n_tiles(ni, 256) : sd.tiles_i, lj = blocks ? n_tiles(nj, 256) : sd.tiles_j;
+            const unsigned __int128 l_items =
+                tri ? static_cast<unsigned __int128>(li) * static_cast<unsigned __int128>(li + 1) / 2
+                    : static_cast<unsigned __int128>(li) * static_cast<unsigned __int128>(lj);
+            if (l_items > kItemMask || limit_items + static_cast<uint64_t>(l_items) > kItemMask) items_overflow = true;
+            limit_items = std::min<uint64_t>(limit_items + static_cast<uint64_t>(std::min<unsigned __int128>(l_items, kItemMask)), kItemMask + 1);
             sd.n_items = static_cast<uint64_t>(std::min<unsigned __int128>(n_items, kItemMask));
             sd.item0 = items;
             items = std::min<uint64_t>(items + sd.n_items, kItemMask + 1);
@@ -671,9 +710,11 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
                                         "); split the catalogues into row ranges");
     // split survivors: the prune pass looks at the j-tile's sub-blocks too
     // (mixed mode); their descriptions sit beside the survivors
+    // (block kernel: the survivors' tiles do)
     const bool split = PC_SPLIT && prune && !fp64;
-    // the ordering's counters and keys are done with when the prune pass
-    // writes the survivors: one region holds the one, then the other
+    // the ordering's counters (and keys, where the ordered copies take more
+    // room) are done with when the prune pass writes the survivors: one region
+    // holds the one, then the other
     int64_t hist_words = 0;
     size_t order_bytes = 0;
     for (View &v : views) {
@@ -684,13 +725,15 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     }
     order_bytes = sizeof(uint32_t) * static_cast<size_t>(hist_words);
     for (View &v : views) {
-        if (v.resident_full || v.e <= v.b) continue;
+        if (v.resident_full || v.e <= v.b || blocks) continue;
         v.o_keys = order_bytes;  // from the region's start
         order_bytes += sizeof(uint32_t) * static_cast<size_t>((v.e - v.b + 63) & ~int64_t(63));
     }
-    const size_t surv_bytes = sizeof(uint64_t) * std::max<uint64_t>(prune ? items : 1, 1);
+    // (16 bytes per pair of 256-point tiles also where the block kernel's larger
+    // tiles leave a quarter of them)
+    const size_t surv_bytes = sizeof(uint64_t) * std::max<uint64_t>(prune ? std::max(items, limit_items) : 1, 1);
     const size_t o_region =
-        ar.take(std::max(order_bytes, surv_bytes + (split ? sizeof(uint64_t) * std::max<uint64_t>(items, 1) : 0)));
+        ar.take(std::max(order_bytes, surv_bytes + (split ? sizeof(uint64_t) * std::max<uint64_t>(std::max(items, limit_items), 1) : 0)));
     const size_t o_surv = o_region, o_sub = o_region + surv_bytes;
     const size_t zero_bytes = (o_region - o_res + sizeof(uint32_t) * static_cast<size_t>(hist_words) + 15) & ~size_t(15);
     const size_t o_sums = ar.take(sizeof(uint32_t) * std::max<size_t>(scan_sums_words(hist_words), 4));
@@ -755,7 +798,6 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
             d.dec = ddec;
         }
         d.a64 = reinterpret_cast<double4 *>(W + srcs[k].o_a64);
-        d.a32 = nullptr;
         d.err = reinterpret_cast<int *>(W + o_err) + k;
         d.ext = reinterpret_cast<uint32_t *>(W + srcs[k].o_ext);
         d.n = c->n;
@@ -769,6 +811,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         const float4 *g32s = nullptr;
         const double4 *bounds = nullptr;
         const double4 *sub_bounds = nullptr;  // T.subs per tile, after the tiles' own
+        const float4 *groups = nullptr;       // kGroups per tile (block kernel)
     };
     std::vector<ViewPtrs> vp(views.size());
     std::vector<ViewDesc> vds;
@@ -780,9 +823,10 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
             const Resident &r = *srcs[vw.src].res;
             vp[v].a64s = r.a64s;
             vp[v].a32s = r.a32s;
-            vp[v].g32s = r.g32s;
-            vp[v].bounds = r.bounds;
-            vp[v].sub_bounds = r.bounds + n_tiles(r.n, tile);
+            vp[v].g32s = blocks ? r.g512 : r.g32s;
+            vp[v].bounds = blocks ? r.b512 : r.bounds;
+            vp[v].sub_bounds = r.bounds + n_tiles(r.n, kResidentTile.tile);
+            vp[v].groups = r.groups;
             continue;
         }
         const int64_t n = vw.e - vw.b;
@@ -790,12 +834,13 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         ViewDesc d;
         d.src = src_a64[vw.src] + vw.b;
         d.ext = src_ext[vw.src];
-        d.keys = reinterpret_cast<uint32_t *>(W + o_region + vw.o_keys);
+        d.keys = reinterpret_cast<uint32_t *>(W + (blocks ? 0 : o_region) + vw.o_keys);
         d.hist = reinterpret_cast<uint32_t *>(W + o_region) + vw.hist0;
         d.a64s = reinterpret_cast<double4 *>(W + vw.o_a64s);
         d.a32s = need_a32 ? reinterpret_cast<float4 *>(W + vw.o_a32s) : nullptr;
         d.g32s = need_g32 ? reinterpret_cast<float4 *>(W + vw.o_g32s) : nullptr;
         d.bounds = reinterpret_cast<double4 *>(W + vw.o_bounds);
+        d.groups = blocks ? reinterpret_cast<float4 *>(W + vw.o_groups) : nullptr;
         d.n = n;
         d.hist0 = vw.hist0;
         d.blk0 = ord_blocks;
@@ -812,6 +857,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         vp[v].g32s = d.g32s;
         vp[v].bounds = d.bounds;
         vp[v].sub_bounds = d.bounds + d.tiles;
+        vp[v].groups = d.groups;
     }
 
     // ---- descriptors
@@ -825,7 +871,10 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         sd.j32 = vp[vj].a32s;
         sd.j64 = vp[vj].a64s;
         sd.jb = vp[vj].bounds;
+        sd.ig = vp[vi].g32s;
         sd.jg = vp[vj].g32s;
+        sd.ib32 = vp[vi].groups;
+        sd.jb32 = vp[vj].groups;
         sd.jb_sub = vp[vj].sub_bounds;
         sd.counts = reinterpret_cast<unsigned long long *>(W + plan[static_cast<size_t>(sd.job)].o_counts);
         sd.pcounts = reinterpret_cast<unsigned long long *>(W + o_pcopies + plan[static_cast<size_t>(sd.job)].o_counts -
@@ -833,7 +882,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         sd.pstride = static_cast<int64_t>(count_words);
     }
     std::vector<TableDesc> tds;
-    bool compact_ok = !fp64 && !mc;
+    bool compact_ok = !fp64 && !mc && !blocks;
     for (auto &t : tabs) {
         tds.push_back(table_desc(*t, fp64));
         compact_ok = compact_ok && t->d_lutc != nullptr;
@@ -875,7 +924,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
             lds_bytes = lds_c;
         }
     }
-    if (lds_bytes > di->lds_per_block)
+    if (!blocks && lds_bytes > di->lds_per_block)
         return fail(PC_ERR_INVALID, "edge set needs " + std::to_string(lds_bytes) +
                                         " bytes of LDS per wave; the device allows " +
                                         std::to_string(di->lds_per_block));
@@ -908,7 +957,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     if (items > 0) {
         if (prune) {
             PC_HIP(T.launch_prune(d_segs, static_cast<int32_t>(segs.size()), d_tabs, prune_rows, surv,
-                                split ? sub_words : nullptr, meta, mc ? 1 : 0, split ? 1 : 0, st),
+                                split ? sub_words : nullptr, meta, mc ? 1 : 0, split ? 1 : 0, blocks, st),
                    "prune");
             PC_HIP(launch_add_copies(reinterpret_cast<unsigned long long *>(W + o_res) + kMetaWords,
                                      reinterpret_cast<const unsigned long long *>(W + o_pcopies),
@@ -916,10 +965,21 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
                    "add prune counts");
         }
         int per_cu = 0;
-        PC_HIP(T.count_occupancy(fp64, mc, compact, lds_bytes, &per_cu), "occupancy");
+        int32_t max_edges = 0, max_cells = 0, bcols = 0;
+        if (blocks) {
+            for (auto &t : tabs) {
+                max_edges = std::max(max_edges, static_cast<int32_t>(t->host.e64.size()));
+                max_cells = std::max(max_cells, static_cast<int32_t>(t->host.lutb.size()));
+            }
+            blk::lds_layout(max_edges, max_cells, lt.cols ? std::min(lt.cols, 16) : 16, &bcols, &max_cells, &lds_bytes);
+            PC_HIP(blk::occupancy(lds_bytes, &per_cu), "occupancy");
+        } else {
+            PC_HIP(T.count_occupancy(fp64, mc, compact, lds_bytes, &per_cu), "occupancy");
+        }
         per_cu = std::max(per_cu, 1);
         int64_t g = static_cast<int64_t>(di->cus) * per_cu;
-        g = std::min<int64_t>(g, static_cast<int64_t>(items));
+        // (the block kernel cuts few survivors into up to sixteen units)
+        g = std::min<int64_t>(g, static_cast<int64_t>(std::min<uint64_t>(items, 1u << 20)) * (blocks ? 16 : 1));
         if (g >= 8) g -= g % 8;
         grid = static_cast<int>(std::max<int64_t>(g, 1));
         const bool timed = t_timing && !ext;  // events are not created in the caller's-workspace mode
@@ -930,7 +990,13 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
             }
             PC_HIP(hipEventRecord(t_ev0, st), "hipEventRecord");
         }
-        PC_HIP(T.launch_count(fp64, mc, compact, d_segs, static_cast<int32_t>(segs.size()), d_tabs, prune ? surv : nullptr,
+        if (blocks)
+            PC_HIP(blk::launch_count(d_segs, d_tabs, surv, sub_words, meta, meta + kQueueBase, meta + 7,
+                                     meta + kPruneStatBase, max_edges, max_cells, bcols, lds_bytes, lt.chunk, t_flush_cap,
+                                     grid, st),
+                   "block kernel");
+        else
+            PC_HIP(T.launch_count(fp64, mc, compact, d_segs, static_cast<int32_t>(segs.size()), d_tabs, prune ? surv : nullptr,
                             prune ? meta : nullptr, split ? sub_words : nullptr, items, lut_off, stage_off, meta + kQueueBase,
                             meta + 7, lt.chunk, lds_bytes, grid, t_flush_cap, st),
                "count kernel");
@@ -1005,61 +1071,56 @@ int upload_catalog(const pc_catalog *c, hipStream_t st, uint64_t *handle) {
     const size_t n = static_cast<size_t>(std::max<int64_t>(c->n, 1));
     Arena ar;
     const size_t o64 = ar.take(sizeof(double4) * n);
-    const size_t o32 = ar.take(sizeof(float4) * n);
     const size_t o64s = ar.take(sizeof(double4) * n);
     const size_t o32s = ar.take(sizeof(float4) * (n + kJPad));  // padded as in run_batch
     const size_t og32s = ar.take(sizeof(float4) * (n + kJPad));
+    const int64_t t512 = n_tiles(static_cast<int64_t>(n), kBlockTile);
+    const size_t og512 = ar.take(std::max(sizeof(float4) * n, sizeof(uint32_t) * order_buckets(static_cast<int64_t>(n), 4)));
+    const size_t ob512 = ar.take(sizeof(double4) * static_cast<size_t>(t512));
+    const size_t og = ar.take(sizeof(float4) * static_cast<size_t>(t512 * kGroups));
     const size_t ob = ar.take(sizeof(double4) * static_cast<size_t>(n_tiles(static_cast<int64_t>(n), kResidentTile.tile) *
                                                                      (1 + kResidentTile.subs)));
     const size_t oerr = ar.take(sizeof(int) * 4 + sizeof(uint32_t) * kExtWords);  // flag, then the extent
-    const size_t odesc = ar.take(sizeof(SrcDesc) + sizeof(ViewDesc));
-    // ordering scratch, given back when the upload is done
-    Arena tmp;
+    const size_t odesc = ar.take(sizeof(SrcDesc) + 2 * sizeof(ViewDesc));
+    // scratch of the conversion and the ordering lies in copies that are
+    // written after it is done with: counters and keys in the two Gram forms,
+    // the caller's host arrays in the ordered binary32 copy
     const uint32_t buckets = order_buckets(static_cast<int64_t>(n), 4);
-    const size_t ohist = tmp.take(sizeof(uint32_t) * buckets);
-    const size_t okeys = tmp.take(sizeof(uint32_t) * n);
-    const size_t osums = tmp.take(sizeof(uint32_t) * std::max<size_t>(scan_sums_words(buckets), 4));
-    size_t ora = 0, odec = 0;
-    if (!c->on_device) {
-        ora = tmp.take(sizeof(double) * n);
-        odec = tmp.take(sizeof(double) * n);
-    }
+    const size_t ohist = og512, okeys = og32s, ora = o32s, odec = o32s + sizeof(double) * n;
+    const size_t osums = ar.take(sizeof(uint32_t) * std::max<size_t>(scan_sums_words(buckets), 4));
     PC_HIP(injected_alloc_failure() ? hipErrorOutOfMemory : hipMalloc(&r->d_mem, ar.size), "hipMalloc(catalogue)");
-    Workspace ws;
-    ws.st = st;
-    PC_HIP(hipMallocAsync(&ws.mem, tmp.size, st), "hipMallocAsync(catalogue scratch)");
-    unsigned char *S = static_cast<unsigned char *>(ws.mem);
     unsigned char *W = static_cast<unsigned char *>(r->d_mem);
     r->a64 = reinterpret_cast<double4 *>(W + o64);
-    r->a32 = reinterpret_cast<float4 *>(W + o32);
     r->a64s = reinterpret_cast<double4 *>(W + o64s);
     r->a32s = reinterpret_cast<float4 *>(W + o32s);
     r->g32s = reinterpret_cast<float4 *>(W + og32s);
     r->bounds = reinterpret_cast<double4 *>(W + ob);
+    r->g512 = reinterpret_cast<float4 *>(W + og512);
+    r->b512 = reinterpret_cast<double4 *>(W + ob512);
+    r->groups = reinterpret_cast<float4 *>(W + og);
     r->ext = reinterpret_cast<uint32_t *>(W + oerr) + 4;
     PC_HIP(launch_zero(W + oerr, sizeof(int) * 4 + sizeof(uint32_t) * kExtWords, st), "zero");
     if (c->n > 0) {
         struct {
             SrcDesc s;
-            ViewDesc v;
+            ViewDesc v, v512;  // v512: the bounds of the block kernel's tiles
         } d = {};
         d.s.ra = c->ra_deg;
         d.s.dec = c->dec_deg;
         if (!c->on_device) {
-            PC_HIP(hipMemcpyAsync(S + ora, c->ra_deg, sizeof(double) * c->n, hipMemcpyHostToDevice, st), "H2D ra");
-            PC_HIP(hipMemcpyAsync(S + odec, c->dec_deg, sizeof(double) * c->n, hipMemcpyHostToDevice, st), "H2D dec");
-            d.s.ra = reinterpret_cast<const double *>(S + ora);
-            d.s.dec = reinterpret_cast<const double *>(S + odec);
+            PC_HIP(hipMemcpyAsync(W + ora, c->ra_deg, sizeof(double) * c->n, hipMemcpyHostToDevice, st), "H2D ra");
+            PC_HIP(hipMemcpyAsync(W + odec, c->dec_deg, sizeof(double) * c->n, hipMemcpyHostToDevice, st), "H2D dec");
+            d.s.ra = reinterpret_cast<const double *>(W + ora);
+            d.s.dec = reinterpret_cast<const double *>(W + odec);
         }
         d.s.a64 = r->a64;
-        d.s.a32 = r->a32;
         d.s.err = reinterpret_cast<int *>(W + oerr);
         d.s.ext = r->ext;
         d.s.n = c->n;
         d.v.src = r->a64;
         d.v.ext = r->ext;
-        d.v.keys = reinterpret_cast<uint32_t *>(S + okeys);
-        d.v.hist = reinterpret_cast<uint32_t *>(S + ohist);
+        d.v.keys = reinterpret_cast<uint32_t *>(W + okeys);
+        d.v.hist = reinterpret_cast<uint32_t *>(W + ohist);
         d.v.a64s = r->a64s;
         d.v.a32s = r->a32s;
         d.v.g32s = r->g32s;
@@ -1067,15 +1128,21 @@ int upload_catalog(const pc_catalog *c, hipStream_t st, uint64_t *handle) {
         d.v.n = c->n;
         d.v.tiles = n_tiles(c->n, kResidentTile.tile);
         d.v.buckets = buckets;
+        d.v512 = d.v;
+        d.v512.g32s = r->g512;
+        d.v512.bounds = r->b512;
+        d.v512.groups = r->groups;
+        d.v512.tiles = t512;
         PC_HIP(hipMemcpyAsync(W + odesc, &d, sizeof(d), hipMemcpyHostToDevice, st), "H2D descriptors");
         const SrcDesc *ds = reinterpret_cast<const SrcDesc *>(W + odesc);
         const ViewDesc *dv = reinterpret_cast<const ViewDesc *>(W + odesc + sizeof(SrcDesc));
-        PC_HIP(launch_zero(S + ohist, sizeof(uint32_t) * buckets, st), "zero");
+        PC_HIP(launch_zero(W + ohist, sizeof(uint32_t) * buckets, st), "zero");
         PC_HIP(launch_convert(ds, 1, convert_blocks(c->n), st), "convert");
-        PC_HIP(launch_order(dv, 1, order_blocks(c->n), reinterpret_cast<uint32_t *>(S + ohist), buckets,
-                            reinterpret_cast<uint32_t *>(S + osums), st),
+        PC_HIP(launch_order(dv, 1, order_blocks(c->n), reinterpret_cast<uint32_t *>(W + ohist), buckets,
+                            reinterpret_cast<uint32_t *>(W + osums), st),
                "order");
         PC_HIP(kResidentTile.launch_bounds(dv, 1, d.v.tiles, st), "bounds");
+        PC_HIP(kTileBlocks.launch_bounds(dv + 1, 1, t512, st), "bounds");
     }
     int flag = 0;
     PC_HIP(hipMemcpyAsync(&flag, W + oerr, sizeof(int), hipMemcpyDeviceToHost, st), "D2H flag");
@@ -1225,9 +1292,7 @@ int pc_unit_vectors(const pc_catalog *c, double *xyz64, float *xyz32, void *stre
     const size_t n = static_cast<size_t>(c->n);
     if (n > 0) {
         std::vector<double4> v64(n);
-        std::vector<float4> v32(n);
         PC_HIP(hipMemcpyAsync(v64.data(), r->a64, sizeof(double4) * n, hipMemcpyDeviceToHost, st), "D2H a64");
-        PC_HIP(hipMemcpyAsync(v32.data(), r->a32, sizeof(float4) * n, hipMemcpyDeviceToHost, st), "D2H a32");
         PC_HIP(hipStreamSynchronize(st), "hipStreamSynchronize");
         for (size_t i = 0; i < n; ++i) {
             if (xyz64) {
@@ -1236,9 +1301,9 @@ int pc_unit_vectors(const pc_catalog *c, double *xyz64, float *xyz32, void *stre
                 xyz64[3 * i + 2] = v64[i].z;
             }
             if (xyz32) {
-                xyz32[3 * i + 0] = v32[i].x;
-                xyz32[3 * i + 1] = v32[i].y;
-                xyz32[3 * i + 2] = v32[i].z;
+                xyz32[3 * i + 0] = static_cast<float>(v64[i].x);
+                xyz32[3 * i + 1] = static_cast<float>(v64[i].y);
+                xyz32[3 * i + 2] = static_cast<float>(v64[i].z);
             }
         }
     }

@@ -1,0 +1,948 @@
+// pc_blocks.hip -- the mixed counting kernel of the default launch: pairs of
+// 512-point tiles as 16 x 16 blocks of 32 x 32 points, squared chords from the
+// matrix cores.
+//
+// A survivor of the prune pass is a pair of tiles (I, J) whose chord interval
+// meets some edges.  One workgroup of four waves takes it:
+//   * classification: one lane per block bounds the block's chords from the
+//     bounding spheres of its two 32-point groups; a block inside one bin is
+//     counted whole, the others ("open") get the first edge k0 and the number m
+//     of edges inside their interval;
+//   * the i-tile sits in LDS in the form the matrix instruction reads, shared
+//     by the four waves and kept while the i-tile stays the same; each wave
+//     takes four of the J tile's sixteen columns of blocks, one after the
+//     other, with the column's 32 j-points in registers;
+//   * an open block is four v_mfma_f32_16x16x32_bf16, each giving
+//     d = h - c for 256 pairs (c the squared chord, h the threshold of the
+//     block's first edge); the sign of d is the count, and d within a proven
+//     width of 0 sends the pair to binary64.
+//
+// Chords.  With o_I, o_J the tiles' sphere centres, D = o_I - o_J, and the
+// points centred on their own tile (a' = RN32(a - o_I), b' = RN32(b - o_J)),
+//   c = |D|^2 + s_a + s_b - 2 a'.b',  s_a = |a'|^2 + 2 D.a',
+//                                     s_b = |b'|^2 - 2 D.b'.
+// s_a and s_b are formed in binary32 once per point and tile pair.  Every
+// binary32 operand is split exactly into three bf16 limbs (truncation leaves
+// at most 8 bits at each step), and one K = 32 product holds per coordinate
+// the eight limb products that reach binary32 accuracy (all but the 3rd x 3rd,
+// below 2^-30), and s_a, s_b as limbs against ones; the threshold is the
+// accumulator's starting value.
+//
+// Why the matrix cores, and why 32 x 32.  The vector form of the same chord
+// needs four or five instructions per pair before it is binned; the product
+// takes 16 cycles of a SIMD per 256 pairs, a quarter of that, and leaves the
+// vector unit the binning alone (per two pairs one byte permute that spreads
+// the two sign bits, half an add, one three-operand minimum).  Finer blocks
+// meet fewer edges: of the 1M workload's pairs 14% are visited at 256 x 64
+// points, 10% at 32 x 32, and most of those meet one edge instead of two.  The
+// tiles are 512 points because an item's fixed work (its centre and bounds, a
+// column's operands, a run's bookkeeping) is shared by all its blocks: at 256
+// points it was 70% of the kernel's vector instructions.
+//
+// What bounds it: vector instructions and matrix products, which a SIMD does
+// not overlap (1M workload: 71% + 19% of the SIMDs' cycles, 61 vector
+// instructions per block).  Counting kernel, this one against the vector kernel
+// of 256-point tiles on the same ordering: 24.0 / 42.7 ms on the 1M workload,
+// 130 / 212 ms for 1M x 1M points in 254 bins, 16.5 / 21.0 ms for 64 mocks x
+// 300,000 randoms, 0.12 / 0.29 ms for 10,000 + 10,000 points, 0.028 / 0.134 ms
+// for 1003 points.
+//
+// Error bound (u = 2^-24, v = 2^-53, R = r_I + r_J the tiles' radii, D = |D|).
+// For an edge inside the tile pair's interval |h - D^2| <= R (2D + R) to
+// rounding.  Against the exact chord of the binary64 unit vectors:
+//   * rounding a', b':            <= 2 (D + R) u R + (u R)^2
+//   * D rounded to binary32:      <= 2 u D R
+//   * s_a, s_b (|.|^2, three fused multiply-adds, three roundings in |.|^2):
+//                                 <= 7 u (R^2 + 2 D R)
+//   * the threshold rounded:      <= u R (2D + R)
+//   * the product: at most 12 u M + u M, M = sum of |terms| <= 4 D R + 2.5 R^2,
+//     the second for the dropped limb products.  The hardware does not document
+//     its 33-term sum; over 1.2 10^8 products of such operands its largest
+//     error was 3.9 u M (a binary32 chain: 7.7 u M), a third of what is allowed:
+//                                 <= 13 u (4 D R + 2.5 R^2)
+//   * a higher edge of the block, d_t = RN(d + RN(h_t - h)): <= u (8 D R + 2 R^2)
+// in all below u (80 D R + 45 R^2).  E = u R (88 D + 50 R) + 2^-48 (D + R)^2 +
+// 2^-110 lies 10% above that; its second term covers the binary64 steps and the
+// binary64 chord itself (5 v c), the third underflow.  With h = e + E: d < 0
+// proves the binary64 chord at or above e, d > W = 2E proves it below, and 0 <=
+// d <= W is recomputed in binary64 in the reference's order.  Measured against
+// binary64 over tile pairs of catalogues of 1003 to 1M points: at most 0.05 E;
+// 2.7 u (D + R)^2 at most and 0.05 to 0.17 in the mean square, where the vector
+// kernel's forms have 28 and 0.5 to 2.2 (differences), 2.8 and 0.23 to 0.76
+// (tile-centred Gram).
+//
+// Blocks of five edges and more (near tiles, sparse catalogues) look each chord
+// up in a table instead: c' = RN(RN(h) - d) is within E_t = E + 4 u (D + R)^2 of the
+// chord, its cell holds at most one edge, and a chord within E_t of that edge
+// goes to binary64.  The table needs E_t below an eighth of a cell (see
+// build_lutb); blocks that reach below that (near ones: E grows with the tiles'
+// size, not with the chord) form their chords from differences, (D + a') - b'
+// per coordinate, whose error follows the chord: the difference vector is off
+// by at most u (2D + 2R + sqrt(c)) <= 3 u (D + R), three roundings square it, and
+// the table's edge and the final difference add two: below A sqrt(c) + B with
+// A = 16 u (D + R), B = 64 u^2 (D + R)^2.
+#include <algorithm>
+
+#include "pc_internal.hpp"
+
+namespace pc {
+
+namespace blk {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+constexpr int kT = kBlockTile;              // points per tile
+constexpr int kWaves = 4;                   // waves per workgroup
+constexpr int kThreads = kWave * kWaves;
+constexpr int kG = kGroup;                  // points per block side
+constexpr int kN = kT / kG;                 // blocks per tile side
+constexpr int kPer = kT / kThreads;         // i-points per thread
+static_assert(kN * kN == kThreads, "one lane classifies one block");
+constexpr uint32_t kColMask = (1u << kN) - 1u;
+constexpr float kNever = 1e30f;             // added to d of a pair that counts nowhere
+constexpr uint32_t kDiagBlock = 1u << 31;   // block descriptor: on the diagonal, only i < j counts
+constexpr uint32_t kTableBlock = 1u << 30;  // block descriptor: chords go through the table
+constexpr uint32_t kNearBlock = 1u << 29;   // with kTableBlock: chords from differences
+// Edges from which a whole block goes through the table: one edge costs a block
+// the same half add and minimum per pair, the table one LDS read per pair whatever
+// their number.  Counting kernel with the line at 3 / 5 / 8 / never: 2.05 / 2.04 /
+// 2.47 / 3.17 ms for 300,000 x 400,000 points, 16.9 / 16.5 / 17.6 / 18.8 ms for 64
+// mocks, 24.2 / 24.0 / 24.1 / 24.7 ms on the 1M workload.
+constexpr uint32_t kTableEdges = 5;
+constexpr uint32_t kOnes = 0x3F803F80u;     // two bf16 ones
+
+struct BParams {
+    const SegDesc *segs;
+    const TableDesc *tabs;
+    const uint64_t *items;                  // survivors: seg | K0 << 32 | M << 43
+    const uint64_t *tiles;                  // beside them: t | u << 32
+    const unsigned long long *n_items;
+    unsigned long long *queue;              // 8 zeroed counters kQueueStride words apart
+    unsigned long long *rechecked;
+    unsigned long long *stats;              // the statistics stripes (see k_prune)
+    uint32_t flush_every;                   // items between flushes, so that no 32-bit word can wrap
+    int32_t max_edges, max_cells;           // of the launch's tables: LDS layout (max_cells 0: no table)
+    int32_t cols;                           // lane columns of the histogram (power of two)
+    int32_t chunk;                          // work units taken from the queue at a time, at most
+};
+
+// Loads through the constant address space: wave-uniform addresses, scalar loads.
+template <typename T>
+__device__ __forceinline__ T ld_uniform(const T *p) {
+    static_assert(sizeof(T) % 4 == 0, "size");
+    using CU = const __attribute__((address_space(4))) uint32_t;
+    CU *q = (CU *)(p);
+    T out;
+    uint32_t *o = reinterpret_cast<uint32_t *>(&out);
+#pragma unroll
+    for (int i = 0; i < static_cast<int>(sizeof(T) / 4); ++i) o[i] = q[i];
+    return out;
+}
+
+__device__ __forceinline__ uint32_t uni(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ uint64_t uni64(uint64_t x) {
+    return static_cast<uint64_t>(uni(static_cast<uint32_t>(x))) | (static_cast<uint64_t>(uni(static_cast<uint32_t>(x >> 32))) << 32);
+}
+__device__ __forceinline__ float uni_f(float x) { return __uint_as_float(uni(__float_as_uint(x))); }
+__device__ __forceinline__ float pow2(uint32_t k) { return __uint_as_float((127u + k) << 23); }
+__device__ __forceinline__ uint32_t ballot32(bool b) { return static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(b)); }
+
+// The three bf16 limbs of x, exact, each in the upper half of a word.
+struct Limbs {
+    uint32_t a, b, c;
+};
+__device__ __forceinline__ Limbs split(float x) {
+    Limbs l;
+    l.a = __float_as_uint(x) & 0xFFFF0000u;
+    const float r = x - __uint_as_float(l.a);
+    l.b = __float_as_uint(r) & 0xFFFF0000u;
+    l.c = __float_as_uint(r - __uint_as_float(l.b));
+    return l;
+}
+// upper halves of (lo, hi) as one word
+__device__ __forceinline__ uint32_t pack(uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); }
+
+// A point's eight K slots of one lane group (16 bytes): a coordinate as the i
+// side (1,1,2,2,1,3,2,3) and as the j side (1,2,1,2,3,1,3,2); the last group
+// carries s_a and s_b against ones.
+__device__ __forceinline__ u32x4 slots_i(float x) {
+    const Limbs l = split(x);
+    return u32x4{pack(l.a, l.a), pack(l.b, l.b), pack(l.a, l.c), pack(l.b, l.c)};
+}
+__device__ __forceinline__ u32x4 slots_si(float x) {
+    const Limbs l = split(x);
+    return u32x4{pack(l.a, l.b), pack(l.c, kOnes), kOnes, 0u};
+}
+// the j side of both kinds (last = the lane is of the last group)
+__device__ __forceinline__ u32x4 slots_j(float x, bool last) {
+    const Limbs l = split(x);
+    const uint32_t ab = pack(l.a, l.b);
+    return u32x4{last ? kOnes : ab, last ? pack(kOnes, l.a) : ab, last ? pack(l.b, l.c) : pack(l.c, l.a),
+                 last ? 0u : pack(l.c, l.b)};
+}
+
+__device__ __forceinline__ f32x4 product(u32x4 a, u32x4 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
+                                                   0, 0);
+}
+
+// Two values of d against one edge: the permute turns their sign bits into two
+// bytes (0xFF when negative), the lower two of the word for the run's first
+// edge (kSelLo) or the upper two for the next (kSelHi), and subtracting it
+// counts them: with n_k the count in byte k, the word is n_0 + 2^8 (n_1 - n_0) +
+// 2^16 (n_2 - n_1) + 2^24 (n_3 - n_2).  A byte takes 255, a block adds at most 8
+// to one: kRunBlocks blocks in a run.  mn keeps the smallest d (as
+// unsigned bits: negative ones are large).
+constexpr uint32_t kSelLo = 0x0C0C0B09u, kSelHi = 0x0B090C0Cu;
+constexpr int kRunBlocks = 31;
+template <uint32_t SEL>
+__device__ __forceinline__ void tally(float d1, float d2, uint32_t &n, uint32_t &mn) {
+    const uint32_t b1 = __float_as_uint(d1), b2 = __float_as_uint(d2);
+    n -= __builtin_amdgcn_perm(b2, b1, SEL);
+    mn = min(min(mn, b1), b2);
+}
+// the counts of the first and the next edge
+__device__ __forceinline__ void counts_of(uint32_t n, uint32_t &first, uint32_t &next) {
+    const uint32_t w = n * 0x01010101u;  // n_0 + 2^8 n_1 + 2^16 n_2 + 2^24 n_3
+    first = (w & 0xFFu) + ((w >> 8) & 0xFFu);
+    next = ((w >> 16) & 0xFFu) + (w >> 24);
+}
+
+// d of the 16 pairs a lane holds of a block: D[2 ri + cj] for rows 16 ri +
+// 4 (lane / 16) + v and column 16 cj + lane % 16.
+struct BlockD {
+    f32x4 d[4];
+};
+
+// LDS histogram: T[row] pairs put into a row (whole blocks into their bin, open
+// ones into the row below their first edge, chords of the table), a word per
+// lane column; N[edge] pairs above an edge.  The count of row r is T[r] +
+// N[r - 1] - N[r].
+struct Hist {
+    uint32_t *T, *N;
+    int32_t n_edges, cols;
+};
+
+__device__ __forceinline__ void add_row(const Hist &h, uint32_t row, uint32_t n) {
+    atomicAdd(h.T + row * static_cast<uint32_t>(h.cols) + (threadIdx.x & static_cast<uint32_t>(h.cols - 1)), n);
+}
+
+// Sum of x over the wave (every lane active), uniform.
+__device__ __forceinline__ uint32_t wave_total(uint32_t x) {
+#define PC_DPP_ADD(ctrl, rows) x += __builtin_amdgcn_update_dpp(0, x, ctrl, rows, 0xF, false)
+    PC_DPP_ADD(0x111, 0xF);  // row_shr 1, 2, 4, 8
+    PC_DPP_ADD(0x112, 0xF);
+    PC_DPP_ADD(0x114, 0xF);
+    PC_DPP_ADD(0x118, 0xF);
+    PC_DPP_ADD(0x142, 0xA);  // row_bcast 15, 31
+    PC_DPP_ADD(0x143, 0xC);
+#undef PC_DPP_ADD
+    return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(x), kWave - 1));
+}
+
+__device__ void clear_hist(const Hist &h) {
+    // N follows T
+    for (int r = static_cast<int>(threadIdx.x); r < (h.n_edges + 1) * h.cols + h.n_edges; r += kThreads) h.T[r] = 0u;
+}
+
+__device__ void flush_hist(const Hist &h, unsigned long long *counts) {
+    __syncthreads();
+    for (int r = static_cast<int>(threadIdx.x); r <= h.n_edges; r += kThreads) {
+        uint32_t v = 0;
+        for (int c = 0; c < h.cols; ++c) v += h.T[r * h.cols + ((c + r) & (h.cols - 1))];
+        if (r > 0) v += h.N[r - 1];
+        if (r < h.n_edges) v -= h.N[r];
+        if (v) atomicAdd(counts + r, static_cast<unsigned long long>(v));
+    }
+    __syncthreads();
+    clear_hist(h);
+}
+
+// Pairs too near an edge wait in LDS for their binary64 chord: the loads of a
+// pair's two points take some two thousand cycles, and a wave that fetched them
+// at once would hold up its workgroup in most items.  One pair per thread is
+// then done at a time, in the reference's order of operations.
+constexpr uint32_t kQueued = 64;
+struct Pending {
+    const double4 *a[kQueued], *b[kQueued];
+    uint32_t edge[kQueued];     // the edge, or kTableRow | the row the pair was counted in
+    uint32_t n;                 // may pass kQueued: the pairs beyond were done at once
+};
+constexpr uint32_t kTableRow = 1u << 31;
+
+__device__ __forceinline__ void recheck(const Hist &h, const double4 *pa, const double4 *pb, uint32_t edge,
+                                        const double *e64) {
+#pragma clang fp contract(off)
+    const double4 a = *pa, b = *pb;
+    const double dx = a.x - b.x, dy = a.y - b.y, dz = a.z - b.z;
+    double c = dx * dx;
+    c = c + dy * dy;
+    c = c + dz * dz;
+    if (edge & kTableRow) {
+        int lo = 0, hi = h.n_edges;  // number of edges at or below c
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (e64[mid] <= c) lo = mid + 1;
+            else hi = mid;
+        }
+        const uint32_t prov = edge & ~kTableRow;
+        if (static_cast<uint32_t>(lo) != prov) {
+            add_row(h, static_cast<uint32_t>(lo), 1u);
+            add_row(h, prov, 0xFFFFFFFFu);
+        }
+    } else {
+        if (c >= e64[edge]) atomicAdd(h.N + edge, 1u);
+    }
+}
+
+__device__ __forceinline__ void send(const Hist &h, Pending &pend, const double4 *a, const double4 *b, uint32_t edge,
+                                     const double *e64) {
+    const uint32_t at = atomicAdd(&pend.n, 1u);
+    if (at < kQueued) {
+        pend.a[at] = a;
+        pend.b[at] = b;
+        pend.edge[at] = edge;
+    } else {
+        recheck(h, a, b, edge, e64);
+    }
+}
+
+// One block against an edge del above the product's.
+template <uint32_t SEL, bool ADD>
+__device__ __forceinline__ void block_tally(const BlockD &D, float del, uint32_t &n, uint32_t &mn) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int v = 0; v < 4; v += 2) {
+            if (ADD) tally<SEL>(D.d[q][v] + del, D.d[q][v + 1] + del, n, mn);
+            else tally<SEL>(D.d[q][v], D.d[q][v + 1], n, mn);
+        }
+}
+
+// The products of block row bi against the column's j-points.
+__device__ __forceinline__ void block_products(const u32x4 (*As)[kWave], int bi, const u32x4 (&B)[2], float H, BlockD &D) {
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const u32x4 a0 = As[2 * bi][lane], a1 = As[2 * bi + 1][lane];
+    const f32x4 C = {H, H, H, H};
+    D.d[0] = product(a0, B[0], C);
+    D.d[1] = product(a0, B[1], C);
+    D.d[2] = product(a1, B[0], C);
+    D.d[3] = product(a1, B[1], C);
+}
+
+// The edge set's chord table in LDS (8 bytes a cell: the edge, the row below it).
+struct ChordTable {
+    const uint2 *cells;
+    uint32_t shift, key0;
+    float lo, hi;               // cells' range
+};
+__device__ __forceinline__ uint2 cell_of(const ChordTable &t, float c) {
+    const uint32_t key = __float_as_uint(__builtin_amdgcn_fmed3f(c, t.lo, t.hi));
+    return t.cells[(key >> t.shift) - t.key0];
+}
+
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) k_count_blocks(BParams p) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    __shared__ u32x4 As[kT / 16][kWave];      // 16 rows x 4 lane groups per set
+    __shared__ uint32_t blk[kThreads];        // open blocks: k0 - K0 | m << 16 | flags; 0: nothing to do
+    __shared__ Pending pend;
+    __shared__ uint64_t sh_next[2];
+    __shared__ unsigned long long sh_stat[6]; // pairs by edges (1, 2, 3, more), items with open, with few-edge blocks
+    const int tid0 = static_cast<int>(threadIdx.x);
+    const int wave = static_cast<int>(uni(threadIdx.x / kWave));
+
+    Hist h;
+    double *const e_lds = reinterpret_cast<double *>(lds);
+    ChordTable tbl;
+    uint2 *const cells = reinterpret_cast<uint2 *>(lds + 8 * p.max_edges);
+    h.T = reinterpret_cast<uint32_t *>(lds + 8 * (p.max_edges + p.max_cells));
+    h.cols = p.cols;
+    h.n_edges = 0;
+    tbl.cells = cells;
+    tbl.shift = tbl.key0 = 0;
+    tbl.lo = tbl.hi = 0.0f;
+    int cur_tab = -1, cur_job = -1;
+    bool has_table = false;
+    unsigned long long *cur_counts = nullptr;
+    uint32_t since_flush = 0, cur_seg = 0xFFFFFFFFu, cur_t = 0;
+    float4 gi[kPer];
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) gi[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+    uint32_t seen = 0;                        // pairs this lane sent to the re-check
+    uint32_t xs = 0;                          // thread 0's place in the queue's slices
+    uint64_t wi = 0, end = 0;
+    // A unit of work is a survivor, or where there are few of them a quarter (a
+    // column of blocks per wave) or a sixteenth (four blocks per wave) of one: a
+    // whole survivor is some 40 blocks per wave, and a launch needs several
+    // units per workgroup to end evenly.  Cut and whole: 28 / 73 us at 3
+    // survivors (1003 points), 120 / 141 us at 820 (10,000 + 10,000 points) with
+    // 1024 workgroups; from 4 survivors a workgroup on a whole one pays its
+    // fixed work once (2.05 / 2.02 ms at 38,861: no difference either way).
+    const uint64_t total = ld_uniform(p.n_items);
+    const uint32_t part_bits = total >= 4ull * gridDim.x ? 0u : total * 2u >= gridDim.x ? 2u : 4u;
+    if (tid0 < 6) sh_stat[tid0] = 0ull;
+    if (tid0 == 0) pend.n = 0u;
+
+    for (;; ++wi) {
+        // opaque per item: addresses made from it are recomputed rather than
+        // kept (and spilled) across the loop
+        int tid = tid0;
+        asm volatile("" : "+v"(tid));
+        const int lane = tid & (kWave - 1);
+        const int grp = lane >> 4;            // lane group: x, y, z, s
+        const bool last = grp == 3;
+        if (wi >= end) {
+            // Work queue: the units in eight slices, one per XCD; a workgroup
+            // takes a chunk at a time from its own slice, then from the
+            // others (consecutive survivors share the i-tile).
+            __syncthreads();
+            if (tid == 0) {
+                const uint64_t units = total << part_bits;
+                const uint64_t chunk = max<uint64_t>(1, min<uint64_t>(p.chunk, units / (8ull * gridDim.x)));
+                uint64_t a = 0, b = 0;
+                for (; xs < 8u; ++xs) {
+                    const uint32_t x = (blockIdx.x + xs) & 7u;
+                    const uint64_t s0 = units * x / 8u, s1 = units * (x + 1u) / 8u;
+                    const uint64_t c = atomicAdd(p.queue + x * kQueueStride, static_cast<unsigned long long>(chunk));
+                    if (s0 + c < s1) {
+                        a = s0 + c;
+                        b = min<uint64_t>(s1, a + chunk);
+                        break;
+                    }
+                }
+                sh_next[0] = a;
+                sh_next[1] = b;
+            }
+            __syncthreads();
+            wi = uni64(sh_next[0]);
+            end = uni64(sh_next[1]);
+            if (wi >= end) break;
+        }
+        // the unit's columns of blocks, and the wave's rows of them
+        const uint32_t part = static_cast<uint32_t>(wi) & ((1u << part_bits) - 1u);
+        const int first_col = part_bits == 0 ? wave : part_bits == 2 ? static_cast<int>(part) * kWaves + wave : static_cast<int>(part);
+        const uint32_t rows = part_bits == 4 ? 0xFu << (4 * wave) : kColMask;
+        // the wave that classifies the unit's blocks (all do their own where a unit is a whole survivor)
+        const bool classifies = part_bits == 0 || wave == static_cast<int>(part_bits == 2 ? part : part >> 2);
+        const uint64_t w0 = ld_uniform(p.items + (wi >> part_bits)), w1 = ld_uniform(p.tiles + (wi >> part_bits));
+        const uint32_t seg = static_cast<uint32_t>(w0);
+        const uint32_t K0 = static_cast<uint32_t>(w0 >> 32) & 2047u, M = static_cast<uint32_t>(w0 >> 43) & 2047u;
+        const uint32_t t = static_cast<uint32_t>(w1), u = static_cast<uint32_t>(w1 >> 32);
+        const SegDesc *sp = p.segs + seg;     // its fields come through scalar loads where they are used
+        const bool new_i = seg != cur_seg || t != cur_t;
+        cur_seg = seg;
+        cur_t = t;
+        const int64_t ibeg = static_cast<int64_t>(t) * kT, jbeg = static_cast<int64_t>(u) * kT;
+        const int32_t i_lim = static_cast<int32_t>(min<int64_t>(kT, ld_uniform(&sp->ni) - ibeg));
+        const int32_t j_lim = static_cast<int32_t>(min<int64_t>(kT, ld_uniform(&sp->nj) - jbeg));
+        const bool diag = ld_uniform(&sp->tri) != 0 && t == u;
+        // what the item reads: its i-points (kept while the i-tile stays), the
+        // wave's first column of j-points, the bounds
+        const float4 *jg = ld_uniform(&sp->jg) + jbeg;
+        if (new_i) {
+#pragma unroll
+            for (int r = 0; r < kPer; ++r) gi[r] = (ld_uniform(&sp->ig) + ibeg)[min(r * kThreads + tid, i_lim - 1)];
+        }
+        float4 gj[2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) gj[c] = jg[min(first_col * kG + 16 * c + (lane & 15), j_lim - 1)];
+        const int cbi = lane & (kN - 1), cbj = wave * (kWave / kN) + lane / kN;  // the block this lane classifies
+        const float4 si = (ld_uniform(&sp->ib32) + static_cast<int64_t>(t) * kN)[cbi];
+        const float4 sj = (ld_uniform(&sp->jb32) + static_cast<int64_t>(u) * kN)[cbj];
+        const double4 oi = ld_uniform(ld_uniform(&sp->ib) + t), oj = ld_uniform(ld_uniform(&sp->jb) + u);
+        const double Dx = oi.x - oj.x, Dy = oi.y - oj.y, Dz = oi.z - oj.z;
+        const double D2 = Dx * Dx + Dy * Dy + Dz * Dz;
+        // E in binary32, raised by 2^-16 for the roundings
+        const float R = uni_f(static_cast<float>(oi.w + oj.w) * (1.0f + 0x1p-20f));
+        const float Dl = uni_f(__builtin_amdgcn_sqrtf(static_cast<float>(D2)) * (1.0f + 0x1p-20f));
+        const float E = (R * (88.0f * Dl + 50.0f * R) * 0x1p-24f + (Dl + R) * (Dl + R) * 0x1p-48f + 0x1p-110f) * (1.0f + 0x1p-16f);
+        const double h_off = static_cast<double>(E) - D2;  // threshold of edge k: RN32(e64[k] + h_off)
+        const float fx = uni_f(static_cast<float>(Dx)), fy = uni_f(static_cast<float>(Dy)),
+                    fz = uni_f(static_cast<float>(Dz));
+        const uint32_t wbits = uni(__float_as_uint(2.0f * E * (1.0f + 0x1p-20f)));
+        __syncthreads();  // every wave is done with the last item's LDS
+
+        const int tab = ld_uniform(&sp->tab), job = ld_uniform(&sp->job);
+        const bool switched = tab != cur_tab || job != cur_job || since_flush >= p.flush_every;
+        const uint32_t waiting = min(uni(pend.n), kQueued);
+        if (waiting >= kQueued / 2 || (switched && waiting != 0u)) {
+            if (tid < static_cast<int>(waiting)) recheck(h, pend.a[tid], pend.b[tid], pend.edge[tid], e_lds);
+            __syncthreads();
+            if (tid == 0) pend.n = 0u;
+        }
+        if (switched) {
+            if (cur_job >= 0) flush_hist(h, cur_counts);
+            if (tab != cur_tab) {
+                const TableDesc *td = p.tabs + tab;
+                h.n_edges = ld_uniform(&td->n_edges);
+                h.N = h.T + (h.n_edges + 1) * h.cols;
+                const double *e64 = ld_uniform(&td->e64);
+                const uint2 *src = reinterpret_cast<const uint2 *>(ld_uniform(&td->lutb));
+                const int n_cells = ld_uniform(&td->b_cells);
+                has_table = n_cells > 0 && n_cells <= p.max_cells;
+                tbl.shift = ld_uniform(&td->b_shift);
+                tbl.key0 = ld_uniform(&td->b_key0);
+                tbl.lo = __uint_as_float(tbl.key0 << tbl.shift);
+                tbl.hi = __uint_as_float(((tbl.key0 + static_cast<uint32_t>(n_cells)) << tbl.shift) - 1u);
+                __syncthreads();
+                for (int k = tid; k < h.n_edges; k += kThreads) e_lds[k] = e64[k];
+                if (has_table)
+                    for (int k = tid; k < n_cells; k += kThreads) cells[k] = src[k];
+                clear_hist(h);
+                cur_tab = tab;
+            }
+            cur_job = job;
+            cur_counts = ld_uniform(&sp->counts);
+            since_flush = 0;
+            __syncthreads();  // the table and the cleared histogram
+        }
+        ++since_flush;
+
+        // ---- the i-tile, in the product's form
+#pragma unroll
+        for (int r = 0; r < kPer; ++r) {
+            const int i = r * kThreads + tid;
+            u32x4 *const at = &As[i >> 4][i & 15];
+            if (new_i) {
+                at[0] = slots_i(gi[r].x);
+                at[16] = slots_i(gi[r].y);
+                at[32] = slots_i(gi[r].z);
+            }
+            // g = (-2 a', |a'|^2): the product takes -s_a = D.g - |a'|^2
+            const float s = fmaf(fx, gi[r].x, fmaf(fy, gi[r].y, fmaf(fz, gi[r].z, -gi[r].w)));
+            at[48] = slots_si(i < i_lim ? s : kNever);
+        }
+        // ---- classification of the wave's 64 blocks
+        const float E_t = (E + 0x1p-22f * (Dl + R) * (Dl + R)) * (1.0f + 0x1p-16f);
+        if (classifies) {
+            const float vx = fx + (si.x - sj.x), vy = fy + (si.y - sj.y), vz = fz + (si.z - sj.z);
+            const float d = __builtin_amdgcn_sqrtf(fmaf(vx, vx, fmaf(vy, vy, vz * vz)));
+            // outward: 12 u (D + R) covers the roundings above
+            const float rs = (si.w + sj.w) * (1.0f + 0x1p-20f) + 0x1p-20f * (Dl + R);
+            const float lo = fmaxf(d - rs, 0.0f), hi = d + rs;
+            const double c_lo = static_cast<double>(lo * lo * (1.0f - 0x1p-18f));
+            const double c_hi = static_cast<double>(hi * hi * (1.0f + 0x1p-18f) + 0x1p-120f);
+            // edges of [K0, K0 + M) at or below each bound
+            uint32_t a = 0, b = 0;
+            for (uint32_t step = 1u << (31 - __builtin_clz(M)); step > 0; step >>= 1) {
+                if (a + step <= M && e_lds[K0 + a + step - 1] <= c_lo) a += step;
+                if (b + step <= M && e_lds[K0 + b + step - 1] <= c_hi) b += step;
+            }
+            const int32_t ni = min(max(i_lim - cbi * kG, 0), kG), nj = min(max(j_lim - cbj * kG, 0), kG);
+            uint32_t np = static_cast<uint32_t>(ni * nj);
+            const bool on_diag = diag && cbi == cbj;
+            if (diag && cbi >= cbj) np = on_diag ? static_cast<uint32_t>(ni * (ni - 1) / 2) : 0u;
+            if (part_bits == 4 && cbj != static_cast<int>(part)) np = 0u;
+            const uint32_t m = np ? b - a : 0u;
+            const bool near = has_table && lo * lo < E_t * pow2(27u - tbl.shift);
+            const bool by_table = m && (near || (m >= kTableEdges && has_table && np == kG * kG && !on_diag));
+            blk[cbj * kN + cbi] = m ? a | (m << 16) | (on_diag ? kDiagBlock : 0u) | (by_table ? kTableBlock : 0u) | (near ? kNearBlock : 0u) : 0u;
+            if (np && !by_table) add_row(h, K0 + a, np);
+            const uint64_t any = __builtin_amdgcn_ballot_w64(m != 0u);
+            const bool full = !diag && i_lim == kT && j_lim == kT && part_bits != 4;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint64_t s = __builtin_amdgcn_ballot_w64(k < 3 ? m == static_cast<uint32_t>(k + 1) : m > 3u);
+                uint32_t v = static_cast<uint32_t>(__builtin_popcountll(s)) * (kG * kG);
+                if (!full) {
+                    v = (s >> lane) & 1u ? np : 0u;
+                    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+                }
+                if (lane == 0 && v) atomicAdd(sh_stat + k, static_cast<unsigned long long>(v));
+            }
+            const uint64_t few = __builtin_amdgcn_ballot_w64(m - 1u < 3u);
+            if (tid == 0 && part == 0 && any) atomicAdd(sh_stat + 4, 1ull);
+            if (tid == 0 && part == 0 && few) atomicAdd(sh_stat + 5, 1ull);
+        }
+        __syncthreads();
+
+        // ---- the wave's columns of blocks; lane k holds the threshold of edge K0 + k
+        const float h_lane = static_cast<float>(e_lds[min(K0 + static_cast<uint32_t>(lane), static_cast<uint32_t>(h.n_edges - 1))] + h_off);
+        auto threshold = [&](uint32_t k) {
+            if (k < kWave) return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(h_lane), static_cast<int>(k)));
+            return uni_f(static_cast<float>(e_lds[K0 + k] + h_off));
+        };
+        uint32_t cnt = 0u;         // lane k: the wave's pairs above edge K0 + k
+        auto add_above = [&](uint32_t k, uint32_t pairs) {
+            if (k < kWave) cnt += lane == static_cast<int>(k) ? pairs : 0u;
+            else if (lane == 0)
+                atomicAdd(h.N + K0 + k, pairs);
+        };
+        // the lanes' counts of a pair of edges, K0 + k and the next
+        auto add_pair = [&](uint32_t n, uint32_t k) {
+            uint32_t c0, c1;
+            counts_of(n, c0, c1);
+            const uint32_t both = wave_total(c0 | (c1 << 16));  // at most 31 x 1024 each
+            add_above(k, both & 0xFFFFu);
+            if (both >> 16) add_above(k + 1u, both >> 16);
+        };
+        uint32_t n = 0u, kb = 0u;  // the run's counts of edges K0 + kb and the next (see tally)
+        int run = 0;               // blocks in it
+        auto flush_run = [&]() {
+            if (run) add_pair(n, kb);
+            n = 0u;
+            run = 0;
+        };
+        for (int cb = first_col; cb < kN; cb += part_bits == 0 ? kWaves : kN) {
+            const uint32_t desc = blk[cb * kN + (lane & (kN - 1))];
+            uint32_t open = ballot32(desc != 0u) & rows;
+            // the column's j-points as the product reads them
+            u32x4 B[2];
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const float4 g = gj[c];
+                const bool ok = cb * kG + 16 * c + (lane & 15) < j_lim;
+                // -s_b = -D.g - |b'|^2; the coordinates as -b' = g / 2
+                const float s = ok ? -fmaf(fx, g.x, fmaf(fy, g.y, fmaf(fz, g.z, g.w))) : kNever;
+                const float x = 0.5f * (grp == 0 ? g.x : grp == 1 ? g.y : g.z);
+                B[c] = slots_j(last ? s : x, last);
+            }
+            if (part_bits == 0 && cb + kWaves < kN) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) gj[c] = jg[min((cb + kWaves) * kG + 16 * c + (lane & 15), j_lim - 1)];
+            }
+            // a block's points in the tiles' ordered copies
+            auto point_i = [&](int bi, int s) { return ld_uniform(&sp->i64) + ibeg + (bi * kG + 16 * (s >> 3) + 4 * (lane >> 4) + (s & 3)); };
+            auto point_j = [&](int s) { return ld_uniform(&sp->j64) + jbeg + (cb * kG + 16 * ((s >> 2) & 1) + (lane & 15)); };
+            auto send_near = [&](const BlockD &D, float del, uint32_t k, int bi) {
+                uint32_t hits = 0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) hits |= __float_as_uint(D.d[q][v] + del) <= wbits ? 1u << (4 * q + v) : 0u;
+                seen += __popc(hits);
+                for (; hits; hits &= hits - 1u) {
+                    const int s = __builtin_ctz(hits);
+                    send(h, pend, point_i(bi, s), point_j(s), K0 + k, e_lds);
+                }
+            };
+            // blocks of one or two edges, those of the same edges together: a
+            // run holds edge kb, the next one, or both; its counts stay in n
+            // until another kb comes
+            uint32_t narrow = open & ~ballot32(desc >= (3u << 16));
+            open &= ~narrow;
+            while (narrow) {
+                const uint32_t key = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(desc), __builtin_ctz(narrow)));
+                uint32_t same = ballot32(desc == key) & narrow;
+                narrow &= ~same;
+                const uint32_t k0 = key & 0xFFFFu;
+                const bool two = (key >> 17) != 0u;
+                if (run + kN > kRunBlocks || (k0 != kb && (two || k0 != kb + 1u))) {
+                    flush_run();
+                    kb = k0;
+                }
+                run += __builtin_popcount(same);
+                const float H = threshold(k0);
+                if (two) {
+                    const float del = uni_f(threshold(k0 + 1u) - H);
+                    while (same) {
+                        const int bi = __builtin_ctz(same);
+                        same &= same - 1u;
+                        BlockD D;
+                        block_products(As, bi, B, H, D);
+                        uint32_t mn = 0xFFFFFFFFu;
+                        block_tally<kSelLo, false>(D, 0.0f, n, mn);
+                        block_tally<kSelHi, true>(D, del, n, mn);
+                        if (__builtin_expect(__builtin_amdgcn_ballot_w64(mn <= wbits) != 0, 0)) {
+#pragma unroll 1
+                            for (uint32_t r = 0; r < 2; ++r) send_near(D, r ? del : 0.0f, k0 + r, bi);
+                        }
+                    }
+                } else if (k0 == kb) {
+                    while (same) {
+                        const int bi = __builtin_ctz(same);
+                        same &= same - 1u;
+                        BlockD D;
+                        block_products(As, bi, B, H, D);
+                        uint32_t mn = 0xFFFFFFFFu;
+                        block_tally<kSelLo, false>(D, 0.0f, n, mn);
+                        if (__builtin_expect(__builtin_amdgcn_ballot_w64(mn <= wbits) != 0, 0)) send_near(D, 0.0f, k0, bi);
+                    }
+                } else {
+                    while (same) {
+                        const int bi = __builtin_ctz(same);
+                        same &= same - 1u;
+                        BlockD D;
+                        block_products(As, bi, B, H, D);
+                        uint32_t mn = 0xFFFFFFFFu;
+                        block_tally<kSelHi, false>(D, 0.0f, n, mn);
+                        if (__builtin_expect(__builtin_amdgcn_ballot_w64(mn <= wbits) != 0, 0)) send_near(D, 0.0f, k0, bi);
+                    }
+                }
+            }
+            // blocks of more edges, and those on the diagonal
+            while (open) {
+                const int bi = __builtin_ctz(open);
+                open &= open - 1u;
+                const uint32_t key = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(desc), bi));
+                const uint32_t k0 = key & 0xFFFFu, m = (key >> 16) & 0xFFFu;
+                BlockD D;
+                if (key & kTableBlock) {
+                    if (key & kNearBlock) {
+                        const float S = Dl + R, A = 0x1p-20f * S, A2 = 2.0f * A * A, B2 = 0x1p-83f * (S * S) * (S * S);
+                        const float q = A * pow2(28u - tbl.shift);
+                        const float floor_c = fmaxf(q * q, 0x1p-42f * S * S * pow2(28u - tbl.shift)) * (1.0f + 0x1p-10f);
+                        float4 pj[2];
+#pragma unroll
+                        for (int c = 0; c < 2; ++c) pj[c] = jg[min(cb * kG + 16 * c + (lane & 15), j_lim - 1)];
+#pragma unroll 1
+                        for (int r = 0; r < 8; ++r) {
+                            const int i = bi * kG + 16 * (r >> 2) + 4 * grp + (r & 3);
+                            const float4 g = (ld_uniform(&sp->ig) + ibeg)[min(i, i_lim - 1)];
+                            const float px = fmaf(-0.5f, g.x, fx), py = fmaf(-0.5f, g.y, fy), pz = fmaf(-0.5f, g.z, fz);
+#pragma unroll
+                            for (int c = 0; c < 2; ++c) {
+                                const int j = cb * kG + 16 * c + (lane & 15);
+                                const float dx = fmaf(0.5f, pj[c].x, px), dy = fmaf(0.5f, pj[c].y, py), dz = fmaf(0.5f, pj[c].z, pz);
+                                const float x = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+                                if (i < i_lim && j < j_lim && (!(key & kDiagBlock) || i < j)) {
+                                    const uint2 e = cell_of(tbl, x);
+                                    const float d = __uint_as_float(e.x) - x;
+                                    const uint32_t row = e.y + (__float_as_uint(d) >> 31);
+                                    add_row(h, row, 1u);
+                                    if (fmaf(d, d, -A2 * x) <= B2 || x <= floor_c) {
+                                        const int s = 8 * (r >> 2) + 4 * c + (r & 3);
+                                        ++seen;
+                                        send(h, pend, point_i(bi, s), point_j(s), row | kTableRow, e_lds);
+                                    }
+                                }
+                            }
+                        }
+                        continue;
+                    }
+                    const float H0 = threshold(k0);
+                    const float top = uni_f(static_cast<float>(static_cast<double>(H0) + D2));  // c = top - d
+                    const f32x4 C = {H0, H0, H0, H0};
+#pragma unroll 1
+                    for (int q = 0; q < 4; ++q) {
+                        const f32x4 d = product(As[2 * bi + (q >> 1)][lane], (q & 1) ? B[1] : B[0], C);
+                        uint2 e[4];
+                        float c[4];
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            c[v] = top - d[v];
+                            e[v] = cell_of(tbl, c[v]);
+                        }
+                        bool hit[4], any = false;
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            const float x = __uint_as_float(e[v].x) - c[v];
+                            e[v].y += __float_as_uint(x) >> 31;
+                            add_row(h, e[v].y, 1u);
+                            hit[v] = fabsf(x) <= E_t;
+                            any |= hit[v];
+                        }
+                        if (__builtin_expect(__builtin_amdgcn_ballot_w64(any) != 0, 0)) {
+#pragma unroll
+                            for (int v = 0; v < 4; ++v)
+                                if (hit[v]) {
+                                    ++seen;
+                                    send(h, pend, point_i(bi, 4 * q + v), point_j(4 * q + v), e[v].y | kTableRow, e_lds);
+                                }
+                        }
+                    }
+                    continue;
+                }
+                const float H0 = threshold(k0);
+                block_products(As, bi, B, H0, D);
+                if (key & kDiagBlock) {
+                    // only i < j counts
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            if (16 * (q >> 1) + 4 * grp + v >= 16 * (q & 1) + (lane & 15)) D.d[q][v] = kNever;
+                }
+                // the first two edges, then two at a time
+                uint32_t nq = 0u, mn = 0xFFFFFFFFu;
+                float d0 = 0.0f, d1 = m > 1 ? uni_f(threshold(k0 + 1u) - H0) : kNever;
+                block_tally<kSelLo, false>(D, 0.0f, nq, mn);
+                block_tally<kSelHi, true>(D, d1, nq, mn);
+                for (uint32_t q = 0;;) {
+                    add_pair(nq, k0 + q);
+                    if (__builtin_expect(__builtin_amdgcn_ballot_w64(mn <= wbits) != 0, 0)) {
+#pragma unroll 1
+                        for (uint32_t r = q; r < min(q + 2, m); ++r) send_near(D, r == q ? d0 : d1, k0 + r, bi);
+                    }
+                    q += 2;
+                    if (q >= m) break;
+                    nq = 0u;
+                    mn = 0xFFFFFFFFu;
+                    d0 = uni_f(threshold(k0 + q) - H0);
+                    block_tally<kSelLo, true>(D, d0, nq, mn);
+                    d1 = kNever;
+                    if (q + 1 < m) {
+                        d1 = uni_f(threshold(k0 + q + 1) - H0);
+                        block_tally<kSelHi, true>(D, d1, nq, mn);
+                    }
+                }
+            }
+        }
+        flush_run();
+        if (cnt) atomicAdd(h.N + K0 + lane, cnt);
+    }
+    __syncthreads();
+    if (tid0 < static_cast<int>(min(pend.n, kQueued))) recheck(h, pend.a[tid0], pend.b[tid0], pend.edge[tid0], e_lds);
+    if (cur_job >= 0) flush_hist(h, cur_counts);
+    for (int o = 32; o > 0; o >>= 1) seen += __shfl_xor(seen, o, kWave);
+    if ((tid0 & (kWave - 1)) == 0 && seen) atomicAdd(p.rechecked, static_cast<unsigned long long>(seen));
+    __syncthreads();
+    const unsigned long long pairs = sh_stat[0] + sh_stat[1] + sh_stat[2] + sh_stat[3];
+    if (tid0 == 0 && pairs) {
+        unsigned long long *st = p.stats + (blockIdx.x % kPruneStripes) * kPruneStripeWords;
+        atomicAdd(st + 1, pairs);
+        atomicAdd(st + 10, pairs);
+        atomicAdd(st + 6, sh_stat[3]);
+        for (int k = 0; k < 3; ++k) atomicAdd(st + 7 + k, sh_stat[k]);
+        atomicAdd(st + 3, sh_stat[5]);
+        atomicAdd(st + 4, sh_stat[4]);
+        atomicAdd(st + 5, sh_stat[4]);
+    }
+}
+
+// ---------------------------------------------------------------- bounds
+
+// Per tile of an ordered view, one workgroup: centre (normalised mean) and
+// radius, rounded outward; the Gram form of its points centred on it, (-2 b'_x,
+// -2 b'_y, -2 b'_z, |b'|^2) with b' = RN32(b - c); and per 32-point group the
+// mean relative to the tile centre, rounded to binary32, and the largest
+// distance from it.
+__global__ void __launch_bounds__(kThreads) k_block_bounds(const ViewDesc *__restrict__ views, int n_views) {
+    __shared__ double sh[kWaves][4];
+    int lo = 0, hi = n_views - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (views[mid].tile0 <= static_cast<int64_t>(blockIdx.x)) lo = mid;
+        else hi = mid - 1;
+    }
+    const ViewDesc &vw = views[lo];
+    const double4 *__restrict__ a64s = vw.a64s;
+    const int64_t n = vw.n, t = static_cast<int64_t>(blockIdx.x) - vw.tile0, b = t * kT;
+    const int tid = static_cast<int>(threadIdx.x), lane = tid & (kWave - 1), wave = tid / kWave;
+    double4 p[kPer];
+    bool ok[kPer];
+    double s[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        const int64_t i = b + r * kThreads + tid;
+        ok[r] = i < n;
+        p[r] = a64s[ok[r] ? i : b];
+        s[0] += ok[r] ? p[r].x : 0.0;
+        s[1] += ok[r] ? p[r].y : 0.0;
+        s[2] += ok[r] ? p[r].z : 0.0;
+    }
+    auto all = [&](double v, int k, bool largest) {
+        for (int o = 32; o > 0; o >>= 1) {
+            const double x = __shfl_xor(v, o, kWave);
+            v = largest ? fmax(v, x) : v + x;
+        }
+        if (lane == 0) sh[wave][k] = v;
+    };
+    for (int k = 0; k < 3; ++k) all(s[k], k, false);
+    __syncthreads();
+    for (int k = 0; k < 3; ++k) {
+        s[k] = 0.0;
+        for (int w = 0; w < kWaves; ++w) s[k] += sh[w][k];
+    }
+    const double norm = sqrt(s[0] * s[0] + s[1] * s[1] + s[2] * s[2]);
+    const double4 first = a64s[b];
+    const bool good = norm > 1e-6;
+    const double cx = good ? s[0] / norm : first.x, cy = good ? s[1] / norm : first.y, cz = good ? s[2] / norm : first.z;
+    double m = 0.0;
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        const double dx = p[r].x - cx, dy = p[r].y - cy, dz = p[r].z - cz;
+        if (ok[r]) m = fmax(m, dx * dx + dy * dy + dz * dz);
+    }
+    all(m, 3, true);
+    __syncthreads();
+    for (int w = 0; w < kWaves; ++w) m = fmax(m, sh[w][3]);
+    if (tid == 0) vw.bounds[t] = make_double4(cx, cy, cz, sqrt(m) * (1.0 + 0x1p-40) + 0x1p-60);
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        const double ex = p[r].x - cx, ey = p[r].y - cy, ez = p[r].z - cz;
+        if (ok[r]) {
+            const float x = static_cast<float>(ex), y = static_cast<float>(ey), z = static_cast<float>(ez);
+            vw.g32s[b + r * kThreads + tid] = make_float4(-2.0f * x, -2.0f * y, -2.0f * z, fmaf(z, z, fmaf(y, y, x * x)));
+        }
+        const uint64_t in = __ballot(ok[r]) & (lane < kG ? 0xFFFFFFFFull : ~0xFFFFFFFFull);
+        double gx = ok[r] ? ex : 0.0, gy = ok[r] ? ey : 0.0, gz = ok[r] ? ez : 0.0;
+        for (int o = kG / 2; o > 0; o >>= 1) {
+            gx += __shfl_xor(gx, o, kWave);
+            gy += __shfl_xor(gy, o, kWave);
+            gz += __shfl_xor(gz, o, kWave);
+        }
+        const double inv = 1.0 / fmax(static_cast<double>(__popcll(in)), 1.0);
+        const float mx = static_cast<float>(gx * inv), my = static_cast<float>(gy * inv), mz = static_cast<float>(gz * inv);
+        const double dx = ex - mx, dy = ey - my, dz = ez - mz;
+        double g2 = ok[r] ? dx * dx + dy * dy + dz * dz : 0.0;
+        for (int o = kG / 2; o > 0; o >>= 1) g2 = fmax(g2, __shfl_xor(g2, o, kWave));
+        if ((lane & (kG - 1)) == 0)
+            vw.groups[t * kN + (r * kThreads + tid) / kG] =
+                make_float4(mx, my, mz, __double2float_ru(sqrt(g2) * (1.0 + 0x1p-40) + 0x1p-60));
+    }
+}
+
+hipError_t launch_bounds(const ViewDesc *views, int n_views, int64_t tiles, hipStream_t st) {
+    if (n_views <= 0 || tiles <= 0) return hipSuccess;
+    if (tiles > 0x7FFFFFFF) return hipErrorInvalidValue;
+    k_block_bounds<<<dim3(static_cast<uint32_t>(tiles)), dim3(kThreads), 0, st>>>(views, n_views);
+    return hipGetLastError();
+}
+
+// ------------------------------------------------------------------ launch
+
+// The launch's LDS layout: the histogram's lane columns (at most `cols`, and
+// fewer for large edge sets) and whether the chord tables come along, so that
+// four workgroups fit a CU where that is possible (40 KB each; the largest edge
+// set, 1024 edges, takes 52 KB, under the 64 KB any kernel may have).
+void lds_layout(int32_t max_edges, int32_t max_cells, int32_t cols, int32_t *cols_out, int32_t *cells_out,
+                uint32_t *lds_bytes) {
+    auto bytes = [&](int32_t c, int32_t cells) { return static_cast<uint32_t>(8 * (max_edges + cells) + 4 * ((max_edges + 1) * c + max_edges)); };
+    static const uint32_t fixed = [] {
+        hipFuncAttributes a;
+        return hipFuncGetAttributes(&a, reinterpret_cast<const void *>(k_count_blocks)) == hipSuccess
+                   ? static_cast<uint32_t>(a.sharedSizeBytes) : 36u * 1024u;
+    }();
+    const uint32_t room = 40u * 1024u - std::min(fixed, 40u * 1024u);
+    int32_t c = 1;
+    while (c < cols && bytes(2 * c, max_cells) <= room) c *= 2;
+    if (bytes(c, max_cells) > room) max_cells = 0;
+    *cols_out = c;
+    *cells_out = max_cells;
+    *lds_bytes = bytes(c, max_cells);
+}
+
+hipError_t occupancy(uint32_t lds_bytes, int *per_cu) {
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_count_blocks, kThreads, lds_bytes);
+}
+
+hipError_t launch_count(const SegDesc *segs, const TableDesc *tabs, const uint64_t *items, const uint64_t *tiles,
+                        const unsigned long long *n_items, unsigned long long *queue, unsigned long long *rechecked,
+                        unsigned long long *stats, int32_t max_edges, int32_t max_cells, int32_t cols, uint32_t lds_bytes,
+                        int chunk, uint64_t flush_cap, int grid, hipStream_t st) {
+    BParams p;
+    p.segs = segs;
+    p.tabs = tabs;
+    p.items = items;
+    p.tiles = tiles;
+    p.n_items = n_items;
+    p.queue = queue;
+    p.rechecked = rechecked;
+    p.stats = stats;
+    // a word of the histogram grows by at most 512 x 512 per item
+    constexpr uint64_t kCap = 0xFFFFFFFFull / (static_cast<uint64_t>(kT) * kT);
+    p.flush_every = static_cast<uint32_t>(flush_cap > 0 && flush_cap < kCap ? flush_cap : kCap);
+    p.max_edges = max_edges;
+    p.max_cells = max_cells;
+    p.cols = cols;
+    p.chunk = chunk;
+    k_count_blocks<<<dim3(grid), dim3(kThreads), lds_bytes, st>>>(p);
+    return hipGetLastError();
+}
+
+}  // namespace blk
+
+}  // namespace pc

@@ -85,6 +85,13 @@ struct LutEntryC {
     uint32_t hi_bits, wc;
 };
 
+// Cell of the block kernel's chord table (see build_lutb): chords below e (or
+// with e = +inf all of the cell) belong to `row`, those above to the next.
+struct LutEntryB {
+    float e;
+    uint32_t row;
+};
+
 // Cell lookup entry of the binary64 kernel: c >= e -> off_hi, else off_lo.
 struct LutEntry64 {
     uint32_t off_lo, off_hi;
@@ -109,6 +116,11 @@ struct TableDesc {
     // matrix-core, and the vector few-edge paths' fused (h, W) pairs, plain
     // and Gram (mixed only; device)
     const float *band, *band_g, *fband, *fband_g;
+    // the block kernel's chord table (LutEntryB[], or b_cells = 0): cell =
+    // (bits of the chord >> b_shift) - b_key0, chords outside clamped
+    const void *lutb;
+    uint32_t b_shift, b_key0;
+    int32_t b_cells, b_pad;
 };
 
 // A survivor work item (one tile pair left after whole-tile-pair binning), as
@@ -121,6 +133,10 @@ struct TableDesc {
 //   bit  61      vector path, chords in Gram form centred on the j-tile
 //   bit  62      matrix-core path centred on the j-tile
 //   bit  63      matrix-core path
+//
+// For the block kernel (pc_blocks.hip) an entry is bits 0..31 the segment,
+// 32..42 K0 and 43..53 M, the edges inside the tile pair's interval, and the
+// word beside it holds the tiles (of kBlockTile points), t | u << 32.
 constexpr int kItemBits = 40;
 constexpr int kFewMax = 3;  // at most 3: m has two bits
 #ifndef PC_FEWCUT
@@ -145,6 +161,12 @@ static_assert(kSubs >= 1 && kSubs <= 4, "at most four 16-bit sub-block fields pe
 constexpr uint32_t kSubWhole = 1u << 13;
 constexpr uint32_t kSubGram = 1u << 14;
 
+// The block kernel's tiles, and the 32-point groups whose bounds it classifies
+// 32 x 32 blocks by.
+constexpr int kBlockTile = 512;
+constexpr int kGroup = 32;
+constexpr int kGroups = kBlockTile / kGroup;
+
 // A binary32 cell table (see pc_tables.cpp).
 struct Lut32 {
     uint32_t clamp_lo = 0, clamp_hi = 0, shift = 0;
@@ -161,9 +183,11 @@ struct SegDesc {
     const float4 *i32, *j32;          // spatially ordered binary32 points
     const double4 *i64, *j64;         // the same points in binary64
     const double4 *ib, *jb;           // tile bounds (centre, radius) of each side
-    const float4 *jg;                 // j side in Gram form, centred on its own tile
+    const float4 *ig, *jg;            // the points in Gram form, centred on their own tile
                                       // (-2 b'_x, -2 b'_y, -2 b'_z, |b'|^2)
     const double4 *jb_sub;            // bounds of the j side's sub-blocks, kSubs per tile
+    const float4 *ib32, *jb32;        // bounds of the 32-point groups, kGroups per tile (block kernel):
+                                      // (centre - tile centre, radius)
     int64_t i0, ni, j0, nj;
     int64_t tiles_i, tiles_j;
     int64_t prow0;          // first row of the segment in the prune pass's row space
@@ -179,7 +203,6 @@ struct SegDesc {
 struct SrcDesc {
     const double *ra, *dec;
     double4 *a64;
-    float4 *a32;            // binary32 copy, or null
     int *err;               // validity flag
     uint32_t *ext;          // kExtWords zeroed words: the extent on each cube face (see k_convert)
     int64_t n;
@@ -196,6 +219,7 @@ struct ViewDesc {
     double4 *a64s;          // ordered copies: binary64,
     float4 *a32s, *g32s;    // binary32 (or null), Gram form centred on the tile (or null)
     double4 *bounds;        // of its tiles, then of their sub-blocks
+    float4 *groups;         // of their 32-point groups (or null)
     int64_t n, hist0, blk0, tile0, tiles;  // blk0, tile0: first block of the ordering, of the bounds launch
     uint32_t buckets;
     uint32_t points0;       // points of the views before
@@ -217,6 +241,9 @@ struct HostTable {
     // differences d = h - c (fused_bands), direct and tile-centred chords
     std::vector<float> fh, fw, fh_g, fw_g;
     Lut32 lut32;
+    // block kernel's chord table; empty when no cell size suits the edges
+    std::vector<LutEntryB> lutb;
+    uint32_t b_shift = 0, b_key0 = 0;
     // fp64 kernel
     uint32_t clamp_lo64 = 0, clamp_hi64 = 0, shift64 = 0;
     std::vector<LutEntry64> lut64;

@@ -107,9 +107,8 @@ __device__ void add_extent(uint32_t *ext, bool ok, const FacePoint &p) {
 
 // -------------------------------------------------------------- conversion
 
-// RA/Dec (degrees, binary64) -> unit vectors: binary64 (x, y, z, 0) and (where
-// asked for) its round-to-nearest binary32 copy, and the source's extent.
-// Invalid inputs (non-finite, |Dec| > 90) set *err and produce the vector of
+// RA/Dec (degrees, binary64) -> unit vectors, binary64 (x, y, z, 0), and the
+// source's extent.  Invalid inputs (non-finite, |Dec| > 90) set *err and produce the vector of
 // (0, 0).
 __global__ void __launch_bounds__(256) k_convert(const SrcDesc *__restrict__ srcs, int n_srcs) {
 #pragma clang fp contract(off)
@@ -132,7 +131,6 @@ __global__ void __launch_bounds__(256) k_convert(const SrcDesc *__restrict__ src
         const double y = cd * sa;
         const double z = sd;
         s.a64[i] = make_double4(x, y, z, 0.0);
-        if (s.a32) s.a32[i] = make_float4(static_cast<float>(x), static_cast<float>(y), static_cast<float>(z), 0.0f);
         p = face_point(x, y, z);
     }
     add_extent(s.ext, in, p);
@@ -588,7 +586,7 @@ __device__ __forceinline__ uint32_t count_le(P e, int32_t n, double c) {
 struct PruneOut {
     int32_t bin;
     uint64_t pairs;
-    uint64_t tags;  // bits 40..63 of the survivor entry
+    uint64_t tags;  // bits 40..63 of the survivor entry (block kernel: bits 32..53)
     uint64_t sub;   // sub-block word of a split item, else 0
 };
 
@@ -617,14 +615,15 @@ __device__ __forceinline__ void chord_interval(const double4 &bi, const double4 
 // bound at most 4 ulp below its value, so D - r_I - r_J > far_l (1 + 0.49e-12);
 // every pair is at least that far apart, and its binary64 squared chord
 // (5 ulp) stays above e[n_edges - 1].
-template <typename P>
+template <bool BLOCKS, typename P>
 __device__ __forceinline__ PruneOut prune_item(const SegDesc &sd, int64_t t, int64_t u, const double4 &bi,
                                                const double4 &bj, P e, int32_t n_edges, double far_l,
                                                int32_t mfma_ok, int32_t split_ok) {
     PruneOut o;
     o.sub = 0;
-    const int64_t ni = min<int64_t>(kTile, sd.ni - t * kTile);
-    const int64_t nj = min<int64_t>(kTile, sd.nj - u * kTile);
+    constexpr int kT = BLOCKS ? kBlockTile : kTile;
+    const int64_t ni = min<int64_t>(kT, sd.ni - t * kT);
+    const int64_t nj = min<int64_t>(kT, sd.nj - u * kT);
     const bool diag = sd.tri && t == u;
     o.pairs = diag ? static_cast<uint64_t>(ni * (ni - 1) / 2) : static_cast<uint64_t>(ni * nj);
     {
@@ -658,6 +657,10 @@ __device__ __forceinline__ PruneOut prune_item(const SegDesc &sd, int64_t t, int
     // edges inside the interval: k_lo .. k_hi-1; few of them are compared one
     // by one instead of through the cell table
     const uint32_t m = k_hi - k_lo;
+    if (BLOCKS) {
+        o.tags = (static_cast<uint64_t>(k_lo) << 32) | (static_cast<uint64_t>(m) << 43);
+        return o;
+    }
     static_assert(PC_FEWCUT >= 1 && PC_FEWCUT <= kFewMax, "few-edge cut");
     const bool is_few = m <= static_cast<uint32_t>(PC_FEWCUT);
     // few-edge full tiles whose chord lower bound is at least twice the
@@ -755,6 +758,11 @@ __device__ __forceinline__ void load_col(const SegDesc &sd, int64_t r, int64_t c
 // atomic and writes them in a second pass (the decision is recomputed), and
 // flushes its histogram and statistics with one atomic per non-zero entry --
 // global atomics on a few shared counters would otherwise serialise the pass.
+//
+// BLOCKS: for the block kernel, which looks at every survivor block by block
+// itself: survivors carry their segment, edges and tiles, no sub-blocks are
+// judged here and no statistics kept but the number of survivors.
+template <bool BLOCKS>
 __global__ void __launch_bounds__(kPruneThreads) k_prune(const SegDesc *__restrict__ segs, int32_t n_segs,
                                                const TableDesc *__restrict__ tabs,
                                                uint64_t *__restrict__ survivors, uint64_t *__restrict__ sub_out,
@@ -829,12 +837,16 @@ __global__ void __launch_bounds__(kPruneThreads) k_prune(const SegDesc *__restri
         if (c0 + kPruneThreads < cols) load_col(sd, r, c0 + kPruneThreads + tid, nxt);
         bool survive = false;
         if (cur.valid) {
-            const PruneOut o = prune_item(sd, cur.t, cur.u, cur.bi, cur.bj, e_lds, n_edges, far_l, mfma_ok, split_ok);
+            const PruneOut o =
+                prune_item<BLOCKS>(sd, cur.t, cur.u, cur.bi, cur.bj, e_lds, n_edges, far_l, mfma_ok, split_ok);
             survive = o.bin < 0;
             if (o.bin == n_edges) {
                 above += o.pairs;
             } else if (o.bin >= 0) {
                 atomicAdd(&h_lds[o.bin], static_cast<unsigned long long>(o.pairs));
+            } else if (BLOCKS) {
+                st[0] += 1ull;
+                survive = true;
             } else if (o.sub) {
                 // the kernel forms a split item's chords in Gram form when
                 // every open sub-block allows it
@@ -906,16 +918,18 @@ __global__ void __launch_bounds__(kPruneThreads) k_prune(const SegDesc *__restri
             const uint64_t kept = it < kPruneMaskSteps ? s_mask[it][wave] : ~0ull;
             if (kept == 0) continue;
             bool survive = false;
-            uint64_t tags = 0, sub = 0, q = 0;
+            uint64_t tags = 0, sub = 0, q = 0, tu = 0;
             if ((kept >> lane) & 1u) {
                 PruneCol k;
                 load_col(sd, r, c0 + tid, k);
                 if (k.valid) {
-                    const PruneOut o = prune_item(sd, k.t, k.u, k.bi, k.bj, e_lds, n_edges, far_l, mfma_ok, split_ok);
+                    const PruneOut o =
+                        prune_item<BLOCKS>(sd, k.t, k.u, k.bi, k.bj, e_lds, n_edges, far_l, mfma_ok, split_ok);
                     survive = o.bin < 0 && (o.sub == 0 || open_subs(o.sub) != 0);
                     tags = o.tags;
                     sub = o.sub;
                     q = k.q;
+                    tu = static_cast<uint64_t>(k.t) | (static_cast<uint64_t>(k.u) << 32);
                 }
             }
             const uint64_t sm = __ballot(survive);
@@ -927,8 +941,8 @@ __global__ void __launch_bounds__(kPruneThreads) k_prune(const SegDesc *__restri
                 at = __shfl(at, __ffsll(static_cast<long long>(sm)) - 1, kWave);
                 if (survive) {
                     const uint64_t slot = s_base + at + __popcll(below);
-                    survivors[slot] = (sd.item0 + q) | tags;
-                    if (sub_out) sub_out[slot] = sub;
+                    survivors[slot] = (BLOCKS ? static_cast<uint64_t>(s) : sd.item0 + q) | tags;
+                    if (sub_out) sub_out[slot] = BLOCKS ? tu : sub;
                 }
             }
         }
@@ -957,11 +971,12 @@ hipError_t launch_bounds(const ViewDesc *views, int n_views, int64_t tiles, hipS
 
 hipError_t launch_prune(const SegDesc *segs, int32_t n_segs, const TableDesc *tabs, int64_t total_rows,
                         uint64_t *survivors, uint64_t *sub, unsigned long long *meta, int32_t mfma_ok,
-                        int32_t split_ok, hipStream_t st) {
+                        int32_t split_ok, bool blocks, hipStream_t st) {
     if (total_rows <= 0) return hipSuccess;
     if (total_rows > 0x7FFFFFFF) return hipErrorInvalidValue;
-    k_prune<<<dim3(static_cast<uint32_t>(total_rows)), dim3(kPruneThreads), 0, st>>>(segs, n_segs, tabs, survivors, sub, meta,
-                                                                          mfma_ok, split_ok);
+    const auto k = blocks ? k_prune<true> : k_prune<false>;
+    k<<<dim3(static_cast<uint32_t>(total_rows)), dim3(kPruneThreads), 0, st>>>(segs, n_segs, tabs, survivors, sub, meta,
+                                                                                mfma_ok, split_ok);
     return hipGetLastError();
 }
 

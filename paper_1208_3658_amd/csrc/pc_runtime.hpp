@@ -43,6 +43,7 @@ struct DevTable {
     const float *d_fband_g = nullptr; // the same for tile-centred Gram chords
     const void *d_lut32 = nullptr;
     const void *d_lutc = nullptr;
+    const void *d_lutb = nullptr;
     const void *d_lut64 = nullptr;
     ~DevTable();
 };
@@ -53,7 +54,7 @@ int get_table(const double *theta, int32_t n_edges, std::shared_ptr<DevTable> *o
 // lutc | lut64 at the offsets below (256-byte aligned), built on the host.
 struct TableBlob {
     std::vector<unsigned char> bytes;
-    size_t o_band = 0, o_band_g = 0, o_fband = 0, o_fband_g = 0, o_lut32 = 0, o_lutc = 0, o_lut64 = 0;
+    size_t o_band = 0, o_band_g = 0, o_fband = 0, o_fband_g = 0, o_lut32 = 0, o_lutc = 0, o_lut64 = 0, o_lutb = 0;
 };
 void table_blob(const HostTable &h, TableBlob *out);
 // points t's device pointers into a copy of the blob at `base` (t does not own it)
@@ -63,11 +64,13 @@ void table_place(DevTable *t, const TableBlob &b, unsigned char *base);
 struct Resident {
     void *d_mem = nullptr;
     double4 *a64 = nullptr;     // caller order
-    float4 *a32 = nullptr;      // caller order
     double4 *a64s = nullptr;    // spatially ordered copy
     float4 *a32s = nullptr;
     float4 *g32s = nullptr;     // ordered copy in Gram form, centred on its tile
     double4 *bounds = nullptr;  // tile bounds of the ordered copy
+    float4 *g512 = nullptr;     // the same for the block kernel's tiles: Gram form,
+    double4 *b512 = nullptr;    // bounds,
+    float4 *groups = nullptr;   // bounds of the 32-point groups
     uint32_t *ext = nullptr;    // extent on each cube face (kExtWords)
     int64_t n = 0;
     int device = 0;
@@ -122,6 +125,7 @@ struct LaunchTune {
     int chunk = 4;
     bool matrix_cores = false;
     int tile = 256;  // points per tile, 128 or 256 (0: 256)
+    bool vector = false;  // tile 256: the vector kernel instead of the block kernel (testing)
 };
 
 // Runs the jobs in one persistent launch on `st` and blocks until the host

@@ -311,6 +311,48 @@ void build_lut32(const std::vector<float> &lo, const std::vector<float> &hi, uin
     }
 }
 
+// ---- the block kernel's chord table ----------------------------------------
+//
+// Cells are runs of 2^S binary32 values (2^(23-S) a binade).  An edge belongs to
+// every cell it lies in or within a quarter cell of: to [mn - q(mn), mx + q(mx)]
+// with q(x) = x 2^(S-26), at most a quarter of the narrower cell next to x.  A
+// chord known to within E_t of its exact value, E_t <= q(c) / 2 (so E_t <= q(mn):
+// c < 2 mn), is then placed by its cell's edge alone unless it is within E_t of
+// that edge: any other edge is farther than E_t from it.  The coarsest S that leaves no cell with two edges,
+// within kMaxLutCells cells; none: no table.  One cell more at each end takes
+// the chords outside.
+void build_lutb(HostTable &t) {
+    t.lutb.clear();
+    const int n = static_cast<int>(t.e64.size());
+    int first = 0;
+    while (first < n && t.e64[first] < 0x1p-100) ++first;  // edges at (or next to) 0
+    if (first == n || (first > 0 && t.e64[first - 1] > 0.0)) return;
+    for (int s = 22; s >= 12; --s) {
+        const uint32_t c0 = (f2u(static_cast<float>(t.e64[first])) >> s) - 1, c1 = (f2u(static_cast<float>(t.e64[n - 1])) >> s) + 1;
+        if (c1 - c0 + 1 > static_cast<uint32_t>(kMaxLutCells)) return;
+        std::vector<LutEntryB> cells;
+        bool ok = true;
+        int below = first, above = first;  // edges under the cell's reach, edges not past it
+        for (uint32_t c = c0; c <= c1 && ok; ++c) {
+            const double q = std::ldexp(1.0, s - 26);
+            const double mn = static_cast<double>(u2f(c << s)) * (1.0 - q), mx = static_cast<double>(u2f((c + 1) << s)) * (1.0 + q);
+            while (below < n && t.e64[below] < mn) ++below;
+            while (above < n && t.e64[above] <= mx) ++above;
+            ok = above - below <= 1;
+            LutEntryB e;
+            e.e = above > below ? static_cast<float>(t.e64[below]) : std::numeric_limits<float>::infinity();
+            e.row = static_cast<uint32_t>(below);
+            cells.push_back(e);
+        }
+        if (ok) {
+            t.lutb = cells;
+            t.b_shift = static_cast<uint32_t>(s);
+            t.b_key0 = c0;
+            return;
+        }
+    }
+}
+
 // ---- binary64 cell table ------------------------------------------------
 //
 // Cell key = high 32 bits of c64 clamped; cell = key >> S.  For a cell with
@@ -453,6 +495,7 @@ bool build_table(const double *theta_deg, int n_edges, HostTable &t, std::string
             t.lut32.compact.push_back({f2u(e.hi), w | e.off_lo});
         }
     }
+    build_lutb(t);
     build_lut64(t);
     return true;
 }
