@@ -1,11 +1,10 @@
 // pc_aperture.hip -- aperture-mass maps (Sec. 3, Eq. 3-5) on gfx950.
 //
 // The paper's GPU method gives each reconstruction point its own thread,
-// which loops over the galaxies near that point.  Here a wavefront owns an
-// 8 x 8 block of grid points (one per lane) and streams the galaxies near the
-// block through scalar loads: every galaxy is wave-uniform, so it reaches all
-// 64 lanes from SGPRs with no LDS and no vector memory traffic.  Galaxies are
-// first ordered by the cell of a square search lattice; the galaxies a block
+// which loops over the galaxies near that point.  Here a workgroup of four
+// waves owns a block of 8 x 8 (or 16 x 16) grid points, every wave all of them
+// and a quarter of the galaxies near the block: each galaxy is wave-uniform and
+// reaches all 64 lanes from SGPRs.  Galaxies are first ordered by the cell of a square search lattice; the galaxies a block
 // can see lie, row of cells by row of cells, in one contiguous range each,
 // trimmed to the filter disc around the block.
 //
@@ -44,7 +43,11 @@ size_t scan_sums_words(int64_t m);
 
 namespace {
 
-constexpr int kApWaves = 4;            // waves per workgroup: 2 x 2 blocks sharing one filter table
+constexpr int kApWaves = 4;            // waves per workgroup: they share a block's galaxies and one filter table
+constexpr int kApRows = 64;            // rows of cells whose galaxy ranges a workgroup holds at a time
+constexpr int kApMaxParts = 16;        // workgroups per block at most,
+constexpr int kApPerCu = 64;           // and per CU wanted (see block_parts)
+constexpr int kApGroup = 4;            // galaxies whose weights one scalar load fetches
 constexpr int kQCells = 1024;          // filter table cells over x in [0, 1], and one at x = 1
 constexpr int kApFlush = 64;           // galaxies summed in binary32 before the binary64 add
 constexpr uint32_t kNoCell = 0xFFFFFFFFu;
@@ -52,13 +55,14 @@ constexpr int64_t kMaxCells = int64_t(1) << 22;
 constexpr double kMaxExtent = 1e15;     // lattice extent limit (binary32 offsets stay finite)
 thread_local int t_ap_force_p = 0;      // points per lane forced for testing (0: chosen per launch)
 
-// One galaxy as the map kernel reads it (32 bytes, one scalar load).
-struct alignas(32) ApGal {
-    double x, y;  // position
-    float a;      // -e1
-    float a2;     // 2 e1
-    float b2;     // -2 e2
-    float ee;     // e1^2 + e2^2 (binary64, rounded once)
+// The ellipticity of one galaxy as the map kernel reads it: 16 bytes, so that
+// one scalar load takes kApGroup galaxies.  The positions are an array of their
+// own, read 64 at a time by the lanes.
+struct alignas(16) ApWeight {
+    float a;   // -e1
+    float a2;  // 2 e1
+    float b2;  // -2 e2
+    float ee;  // e1^2 + e2^2 (binary64, rounded once)
 };
 
 // Square search lattice: cell (cx, cy) covers [ox + cx s, ox + (cx+1) s) x ...
@@ -69,25 +73,31 @@ struct Lattice {
 };
 
 struct ApParams {
-    const ApGal *gal;
+    const double2 *pos;     // galaxy positions
+    const ApWeight *wgt;    // and weights, readable 2 kApGroup entries past the last galaxy
     const uint32_t *start;  // ncx * ncy + 1 cell starts
     const float4 *qtab;     // kQCells + 1 cubics (c0, c1, c2, c3): Q = c0 + t (c1 + t (c2 + t c3))
     Lattice lat;
     double x0, y0, gdx, gdy;
-    int32_t nx, ny, tiles_x, n_tiles, per_xcd;  // tiles: groups of 2 x 2 blocks
-    double theta;     // filter radius
+    int32_t nx, ny, tiles_x, n_tiles, per_xcd;  // tiles: blocks of 8P x 8P points
+    int32_t parts;    // workgroups per block
     double r2;        // theta^2 (binary64), the cut
     double reach;     // theta with a relative margin for the cell search
     float k_x;        // x = r k_x = r / theta, clamped to [0, 1]; table position s = kQCells x
     float r2f;        // theta^2 rounded to binary32: the provisional cut
     float band;       // |f2 - r2f| <= band: the binary32 |d|^2 cannot decide the cut
     float near0;      // f2 <= near0: a galaxy near the point, decided and weighted in binary64
+    float in2;        // bounds of |d|^2, with a margin for their use in binary32 (see cut_bands):
+    float near2;      //   below in2 f2 is below r2f - band, above near2 it is above near0,
+    float out2;       //   above out2 it is above r2f + band
     float nbig;       // -1 / band: clamp(fma(f2 - r2f, nbig, 1/2)) is 1 inside, 0 outside
     float f2_in, f2_out;  // r2f -+ 2 band: where a pair decided in binary64 is moved
     double n_gal;
     double *map;
     double *snr;
     uint32_t *n_in;
+    double2 *part_s;        // parts > 1: each part's two sums and count per point
+    uint32_t *part_n;
     unsigned long long *stats;  // [pairs tested, pairs inside]
 };
 
@@ -140,7 +150,7 @@ __global__ void __launch_bounds__(256) k_ap_place(const double *__restrict__ X, 
                                                   const double *__restrict__ E1, const double *__restrict__ E2,
                                                   const uint32_t *__restrict__ keys, const uint32_t *__restrict__ idx,
                                                   const uint32_t *__restrict__ start, int64_t n_cells, int64_t n,
-                                                  ApGal *__restrict__ gal) {
+                                                  double2 *__restrict__ pos, ApWeight *__restrict__ wgt) {
     const int64_t p = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (p >= n || p >= static_cast<int64_t>(start[n_cells])) return;
     const uint32_t i = idx[p];
@@ -149,14 +159,13 @@ __global__ void __launch_bounds__(256) k_ap_place(const double *__restrict__ X, 
     uint32_t rank = 0;
     for (uint32_t q = lo; q < hi; ++q) rank += idx[q] < i ? 1u : 0u;
     const double e1 = E1[i], e2 = E2[i];
-    ApGal g;
-    g.x = X[i];
-    g.y = Y[i];
+    pos[lo + rank] = make_double2(X[i], Y[i]);
+    ApWeight g;
     g.a = static_cast<float>(-e1);
     g.a2 = static_cast<float>(2.0 * e1);
     g.b2 = static_cast<float>(-2.0 * e2);
     g.ee = static_cast<float>(e1 * e1 + e2 * e2);
-    gal[lo + rank] = g;
+    wgt[lo + rank] = g;
 }
 
 // ------------------------------------------------------------------ map
@@ -210,13 +219,29 @@ __device__ __forceinline__ float q_table(float s, uint32_t tab) {
     return fmaf(fmaf(fmaf(c.w, t, c.z), t, c.y), t, c.x);
 }
 
-// One wave owns a block of (8P) x (8P) grid points: lane (lx, ly) = (lane % 8,
-// lane / 8) holds the P x P points (lx + 8a, ly + 8b), so every galaxy read
-// (wave-uniform, scalar loads) is used for P^2 independent pairs per lane.
-// Four waves (2 x 2 blocks) per workgroup share the filter table in LDS.
-// Groups are dealt to the eight XCDs in contiguous strips (the hardware
-// assigns workgroup b to XCD b mod 8), so neighbouring blocks, which read
-// mostly the same galaxies, share an L2.
+// A workgroup of four waves owns a block of (8P) x (8P) grid points: lane (lx,
+// ly) = (lane % 8, lane / 8) of every wave holds the P x P points (lx + 8a, ly +
+// 8b), so every galaxy read is used for P^2 independent pairs per lane.  The
+// galaxies near the block come in runs of at most 64 that share a row of cells;
+// the waves take the runs in turn, and their sums are added in order at the end.
+// Blocks are dealt to the eight XCDs in contiguous strips (the hardware assigns
+// workgroup b to XCD b mod 8), so neighbouring blocks, which read mostly the
+// same galaxies, share an L2.
+//
+// What bounds it: vector instructions, 20 per pair for galaxies inside every
+// aperture of the block and 27 (P = 2) or 29 for the others, at about 18 and 22
+// cycles of a CU per wave of pairs; the filter's 16-byte LDS reads, 8 cycles and
+// 2 (P = 2) to 5 of bank conflicts, run beside them.  The inner galaxies' step
+// needs no cut, no factor and no clamp; each lane classifies one galaxy of a run
+// from its offset, 90% of the visited ones are inner for 2048 x 2048 points of
+// 32 arcmin apertures (16 x 16 blocks), 45% for 512 x 512 of 8 (8 x 8).  The
+// four waves of a block, against one wave per block: shorter workgroups, so that
+// the last ones end together, and for small maps four times the waves.  Map
+// kernel, the one-wave form without classes / this one: 252.6 / 190.6 ms and
+// 2.38 / 1.67 ms on those two maps of 1M galaxies, 1.33 / 0.077 ms for 20,000
+// galaxies on 96 x 80 points (120 blocks, 16 workgroups each).  Weights by
+// scalar loads four galaxies ahead of their use: the loop's waits share one
+// counter with the LDS reads, so a load per galaxy would be waited for at once.
 //
 // Per pair, in binary32: the galaxy and the point relative to a reference
 // point of the block (the galaxy's offset is formed once per galaxy in
@@ -242,41 +267,70 @@ __device__ __forceinline__ float q_table(float s, uint32_t tab) {
 // widened to decide every pair in binary64 (grid spacing far beyond theta)
 // r2f - 2 band is negative, and the raise keeps the weights of such moved
 // pairs finite.
+// The galaxies [x, y) of one row of cells that the block may see.
+__device__ __forceinline__ uint2 ap_row(const ApParams &p, int cy, double gxl, double gxh, double gyl, double gyh) {
+    const Lattice &L = p.lat;
+    const double slack = L.s * 1e-9;  // covers rounding of the cell coordinates
+    // vertical gap between this row of cells and the block; the row's
+    // galaxies within reach of the block lie within w of it horizontally
+    const double rlo = L.oy + static_cast<double>(cy) * L.s;
+    const double dv = fmax(0.0, fmax(rlo - gyh, gyl - (rlo + L.s)) - slack);
+    const double w2 = p.reach * p.reach - dv * dv;
+    if (!(w2 > 0.0)) return make_uint2(0u, 0u);
+    const double w = sqrt(w2) + slack;
+    const int cx0 = cell_index(gxl - w, L.ox, L.inv_s, L.ncx);
+    const int cx1 = cell_index(gxh + w, L.ox, L.inv_s, L.ncx);
+    const uint32_t *const start = p.start + static_cast<size_t>(cy) * static_cast<size_t>(L.ncx);
+    return make_uint2(start[cx0], start[cx1 + 1]);
+}
+
+// The outputs at grid point o (Eq. 3 and 5) from its sums.
+__device__ __forceinline__ void ap_store(const ApParams &p, int64_t o, double S1, double S2, uint32_t cnt) {
+    p.map[o] = S1 / p.n_gal;
+    if (p.snr) p.snr[o] = S2 > 0.0 ? (1.4142135623730951 * S1) / sqrt(S2) : __builtin_nan("");
+    if (p.n_in) p.n_in[o] = cnt;
+}
+
 template <int P, bool RAISE>
 __global__ void __launch_bounds__(64 * kApWaves) __attribute__((amdgpu_waves_per_eu(P == 2 ? 4 : 7)))
 k_ap_map(const ApParams p) {
     constexpr int BS = 8 * P;   // block side in points
     constexpr int K = P * P;    // points per lane
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    using lds_f4 = __attribute__((address_space(3))) const f32x4;
+    using WeightU = const __attribute__((address_space(4))) f32x4;  // wave-uniform: scalar loads
     __shared__ float4 qtab[kQCells + 1];
-    const int lane = static_cast<int>(threadIdx.x) & 63;
-    // wave-uniform (a scalar register): the block, its galaxy ranges and the
-    // galaxy loop are the same for every lane of the wave
-    const int wave = static_cast<int>(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+    __shared__ uint2 rows[kApRows];
+    const int tid = static_cast<int>(threadIdx.x);
+    const int lane = tid & 63;
+    const int wave = static_cast<int>(__builtin_amdgcn_readfirstlane(tid >> 6));
     const int b = static_cast<int>(blockIdx.x);
     const int tile = (b & 7) * p.per_xcd + (b >> 3);
     if (tile >= p.n_tiles) return;  // the whole workgroup: before any barrier
-    for (int k = static_cast<int>(threadIdx.x); k <= kQCells; k += 64 * kApWaves) qtab[k] = p.qtab[k];
-    __syncthreads();
+    for (int k = tid; k <= kQCells; k += 64 * kApWaves) qtab[k] = p.qtab[k];
     const int tx = tile % p.tiles_x, ty = tile / p.tiles_x;
-    const int ix0 = tx * 2 * BS + (wave & 1) * BS, iy0 = ty * 2 * BS + (wave >> 1) * BS;
-    // a block of the group past the grid's edge has no points
-    if (ix0 >= p.nx || iy0 >= p.ny) return;
+    const int ix0 = tx * BS, iy0 = ty * BS;
     const int ix1 = min(ix0 + BS - 1, p.nx - 1), iy1 = min(iy0 + BS - 1, p.ny - 1);
     // the block's reference point: its centre (any binary64 value serves)
     const double xb = p.x0 + (static_cast<double>(ix0) + 0.5 * (BS - 1)) * p.gdx;
     const double yb = p.y0 + (static_cast<double>(iy0) + 0.5 * (BS - 1)) * p.gdy;
-    int ixk[K], iyk[K];
-    bool valid[K];
+    // grid indexes of the lane's point k; lanes past the grid edge repeat a
+    // point.  Formed where they are needed (the rare branch and the end) from a
+    // copy of the lane number that the compiler cannot see through: held over
+    // the galaxy loop they would spill.
+    auto point_x = [&](int l, int k) { return ix0 + (l & 7) + 8 * (k % P); };
+    auto point_y = [&](int l, int k) { return iy0 + (l >> 3) + 8 * (k / P); };
+    auto hidden_lane = [&]() {
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        return l;
+    };
     float Xg[K], Yg[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int ixl = ix0 + (lane & 7) + 8 * (k % P), iyl = iy0 + (lane >> 3) + 8 * (k / P);
-        valid[k] = ixl <= ix1 && iyl <= iy1;
-        ixk[k] = min(ixl, ix1);  // lanes past the grid edge repeat a point
-        iyk[k] = min(iyl, iy1);
         // the grid point as the definition forms it (product, then sum)
-        const double xg = p.x0 + static_cast<double>(ixk[k]) * p.gdx;
-        const double yg = p.y0 + static_cast<double>(iyk[k]) * p.gdy;
+        const double xg = p.x0 + static_cast<double>(min(point_x(lane, k), ix1)) * p.gdx;
+        const double yg = p.y0 + static_cast<double>(min(point_y(lane, k), iy1)) * p.gdy;
         Xg[k] = static_cast<float>(xg - xb);
         Yg[k] = static_cast<float>(yg - yb);
     }
@@ -287,7 +341,10 @@ k_ap_map(const ApParams p) {
                static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
                    (__attribute__((address_space(3))) const float4 *)(qtab)))};
     asm("" : "+v"(C.k_x), "+v"(C.r2f), "+v"(C.band), "+v"(C.near0), "+v"(C.nbig), "+v"(C.f2_in), "+v"(C.f2_out));
-    const double slack = L.s * 1e-9;  // covers rounding of the cell coordinates
+    const float k_s = p.k_x * static_cast<float>(kQCells);
+    // the block's reach from its reference point
+    const float bx = static_cast<float>(fmax(xb - gxl, gxh - xb)) * (1.0f + 0x1p-22f);
+    const float by = static_cast<float>(fmax(yb - gyl, gyh - yb)) * (1.0f + 0x1p-22f);
 
     double S1[K], S2[K];
     uint32_t cnt[K];
@@ -297,141 +354,299 @@ k_ap_map(const ApParams p) {
         S2[k] = 0.0;
         cnt[k] = 0u;
     }
+    uint32_t all = 0;  // galaxies inside every aperture of the block
     uint64_t tested = 0;
-    const int cy0 = cell_index(gyl - p.reach - slack, L.oy, L.inv_s, L.ncy);
-    const int cy1 = cell_index(gyh + p.reach + slack, L.oy, L.inv_s, L.ncy);
-    for (int cy = cy0; cy <= cy1; ++cy) {
-        // vertical gap between this row of cells and the block; the row's
-        // galaxies within reach of the block lie within w of it horizontally
-        const double rlo = L.oy + static_cast<double>(cy) * L.s;
-        const double dv = fmax(0.0, fmax(rlo - gyh, gyl - (rlo + L.s)) - slack);
-        const double w2 = p.reach * p.reach - dv * dv;
-        if (!(w2 > 0.0)) continue;
-        const double w = sqrt(w2) + slack;
-        const int cx0 = cell_index(gxl - w, L.ox, L.inv_s, L.ncx);
-        const int cx1 = cell_index(gxh + w, L.ox, L.inv_s, L.ncx);
-        const uint32_t row = static_cast<uint32_t>(cy) * static_cast<uint32_t>(L.ncx);
-        const uint32_t g_begin = p.start[row + static_cast<uint32_t>(cx0)];
-        const uint32_t g_end = p.start[row + static_cast<uint32_t>(cx1) + 1u];
-        tested += g_end - g_begin;
-        for (uint32_t c0 = g_begin; c0 < g_end; c0 += kApFlush) {
-            const uint32_t c1 = min(c0 + static_cast<uint32_t>(kApFlush), g_end);
-            float a1[K], a2[K], cntf[K];
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                a1[k] = 0.0f;
-                a2[k] = 0.0f;
-                cntf[k] = 0.0f;
+    const int cy0 = cell_index(gyl - p.reach - L.s * 1e-9, L.oy, L.inv_s, L.ncy);
+    const int cy1 = cell_index(gyh + p.reach + L.s * 1e-9, L.oy, L.inv_s, L.ncy);
+    // the wave's turn among the runs of the block
+    const uint32_t turns = static_cast<uint32_t>(p.parts) * kApWaves;
+    uint32_t skip = blockIdx.y * kApWaves + static_cast<uint32_t>(wave);
+    for (int cyb = cy0; cyb <= cy1; cyb += kApRows) {
+        const int n_rows = min(cy1 - cyb + 1, kApRows);
+        __syncthreads();
+        if (tid < n_rows) rows[tid] = ap_row(p, cyb + tid, gxl, gxh, gyl, gyh);
+        __syncthreads();
+        for (int ri = 0; ri < n_rows; ++ri) {
+            const uint32_t g_begin = __builtin_amdgcn_readfirstlane(rows[ri].x);
+            const uint32_t g_end = __builtin_amdgcn_readfirstlane(rows[ri].y);
+            tested += g_end - g_begin;
+            const uint32_t runs = (g_end - g_begin + kApFlush - 1) / kApFlush;
+            if (skip >= runs) {
+                skip -= runs;
+                continue;
             }
-            // galaxies go through scalar registers, each loaded one galaxy
-            // ahead of its use
-            ApGal Gn = p.gal[c0];
-            for (uint32_t g = c0; g < c1; ++g) {
-                const ApGal G = Gn;
-                Gn = p.gal[min(g + 1u, c1 - 1u)];
-                const float X = static_cast<float>(G.x - xb), Y = static_cast<float>(G.y - yb);
-                float fdx[K], fdy[K], py[K], f2[K];
-                float near = FLT_MAX, low = FLT_MAX;
+            uint32_t run = skip;
+            for (; run < runs; run += turns) {
+                const uint32_t c0 = g_begin + run * kApFlush;
+                const uint32_t c1 = min(c0 + static_cast<uint32_t>(kApFlush), g_end);
+                // lane l: offset of galaxy c0 + l from the reference point
+                const double2 at = p.pos[min(c0 + static_cast<uint32_t>(lane), c1 - 1u)];
+                const float XL = static_cast<float>(at.x - xb), YL = static_cast<float>(at.y - yb);
+                auto offset = [&](float v, int j) {
+                    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), j));
+                };
+                // Galaxies by their offset from the block: beyond every
+                // aperture (left out: their factor is 0), inside every
+                // aperture and near no point ("inner"), or neither.
+                uint64_t inner, some;
+                {
+                    const float fx = fabsf(XL) + bx, fy = fabsf(YL) + by;
+                    const float gx = fmaxf(fabsf(XL) - bx, 0.0f), gy = fmaxf(fabsf(YL) - by, 0.0f);
+                    const float gap2 = fmaf(gx, gx, gy * gy);
+                    const bool have = c0 + static_cast<uint32_t>(lane) < c1;
+                    inner = __builtin_amdgcn_ballot_w64(have && fmaf(fx, fx, fy * fy) < p.in2 && gap2 > p.near2);
+                    some = __builtin_amdgcn_ballot_w64(have && !(gap2 > p.out2));
+                }
+                float a1[K], a2[K], cntf[K];
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
-                    fdx[k] = X - Xg[k];
-                    fdy[k] = Y - Yg[k];
-                    py[k] = fdy[k] * fdy[k];
-                    f2[k] = fmaf(fdx[k], fdx[k], py[k]);
-                    near = fminf(near, fabsf(f2[k] - C.r2f));
-                    low = fminf(low, f2[k]);
+                    a1[k] = 0.0f;
+                    a2[k] = 0.0f;
+                    cntf[k] = 0.0f;
                 }
-                if (__builtin_expect(__builtin_amdgcn_ballot_w64(near <= C.band || low <= C.near0) != 0, 0)) {
-                    // rare: a pair of the wave that f2 cannot decide is
-                    // decided by the binary64 definition (0 < dx*dx + dy*dy <
-                    // theta^2, no fused multiply-add, grid point formed as
-                    // above) and its f2 moved to the matching side of r2f (by
-                    // at most `band`); a galaxy near its point, if inside, is
-                    // weighted here from its binary64 offset and left out of
-                    // the binary32 step below
+                all += static_cast<uint32_t>(__builtin_popcountll(inner));
+                // An inner galaxy: f2 is normal and below r2f - band, x below
+                // 1, so the general step's tests and its factor 1 fall away,
+                // and r k_x kQCells is one product (kQCells a power of two).
+                auto step_inner = [&](int j, const f32x4 W) {
+                    const float X = offset(XL, j), Y = offset(YL, j);
+                    float fdx[K], fdy[K], py[K], rinv[K], t[K];
+                    f32x4 cq[K];
 #pragma unroll
                     for (int k = 0; k < K; ++k) {
-                        const double xg = p.x0 + static_cast<double>(ixk[k]) * p.gdx;
-                        const double yg = p.y0 + static_cast<double>(iyk[k]) * p.gdy;
-                        const double ddx = G.x - xg, ddy = G.y - yg;
-                        const double d2 = ddx * ddx + ddy * ddy;
-                        const bool inside = d2 < p.r2 && d2 > 0.0;
-                        const bool near_point = f2[k] <= C.near0;
-                        if (near_point && inside) {
-                            const double c2 = (ddx * ddx - ddy * ddy) / d2, s2 = (ddx * ddy) / d2;
-                            const float et = static_cast<float>(static_cast<double>(G.a) * c2 +
-                                                                static_cast<double>(G.b2) * s2);
-                            const float qn = q_table(table_pos(static_cast<float>(sqrt(d2)), C.k_x), C.tab);
-                            a1[k] = fmaf(qn, et, a1[k]);
-                            a2[k] = fmaf(qn * qn, G.ee, a2[k]);
-                            cnt[k] += 1u;
+                        fdx[k] = X - Xg[k];
+                        fdy[k] = Y - Yg[k];
+                        py[k] = fdy[k] * fdy[k];
+                        const float f2 = fmaf(fdx[k], fdx[k], py[k]);
+                        rinv[k] = __builtin_amdgcn_rsqf(f2);
+                        const float s = (f2 * rinv[k]) * k_s;
+                        cq[k] = *(lds_f4 *)(uintptr_t)(C.tab + (static_cast<uint32_t>(s) << 4));
+                        t[k] = __builtin_amdgcn_fractf(s);
+                    }
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        const float q = fmaf(fmaf(fmaf(cq[k].w, t[k], cq[k].z), t[k], cq[k].y), t[k], cq[k].x);
+                        const float rr = rinv[k] * rinv[k];
+                        const float in = fmaf(W.y, py[k], W.z * (fdx[k] * fdy[k]));
+                        a1[k] = fmaf(q, fmaf(rr, in, W.x), a1[k]);
+                        a2[k] = fmaf(q * q, W.w, a2[k]);
+                    }
+                };
+                struct Sep {
+                    float dx[K], dy[K], py[K], f2[K];
+                };
+                auto separate = [&](int j, Sep &d, float &near, float &low) {
+                    const float X = offset(XL, j), Y = offset(YL, j);
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        d.dx[k] = X - Xg[k];
+                        d.dy[k] = Y - Yg[k];
+                        d.py[k] = d.dy[k] * d.dy[k];
+                        d.f2[k] = fmaf(d.dx[k], d.dx[k], d.py[k]);
+                        near = fminf(near, fabsf(d.f2[k] - C.r2f));
+                        low = fminf(low, d.f2[k]);
+                    }
+                };
+                auto undecided = [&](float near, float low) {
+                    return __builtin_amdgcn_ballot_w64(near <= C.band || low <= C.near0) != 0;
+                };
+                // inside: w = 1, outside: w = 0, exactly (|f2 - r2f| > band
+                // here, or f2 was moved to 2 band from r2f); plain arithmetic,
+                // no compare.  Every value below is finite: f2 is positive and
+                // normal (see RAISE).
+                auto weigh = [&](const Sep &d, const f32x4 W) {
+                    float rinv[K], t[K], wt[K];
+                    f32x4 cq[K];
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        wt[k] = fma_clamp01(d.f2[k] - C.r2f, C.nbig);
+                        cntf[k] += wt[k];
+                        const float f2c = RAISE ? max_f32(d.f2[k], C.near0) : d.f2[k];
+                        rinv[k] = __builtin_amdgcn_rsqf(f2c);
+                        const float sk = table_pos(f2c * rinv[k], C.k_x);
+                        cq[k] = *(lds_f4 *)(uintptr_t)(C.tab + (static_cast<uint32_t>(sk) << 4));
+                        t[k] = __builtin_amdgcn_fractf(sk);
+                    }
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        float qk = fmaf(fmaf(fmaf(cq[k].w, t[k], cq[k].z), t[k], cq[k].y), t[k], cq[k].x);
+                        qk *= wt[k];
+                        const float rr = rinv[k] * rinv[k];
+                        const float in = fmaf(W.y, d.py[k], W.z * (d.dx[k] * d.dy[k]));
+                        const float et = fmaf(rr, in, W.x);
+                        a1[k] = fmaf(qk, et, a1[k]);
+                        a2[k] = fmaf(qk * qk, W.w, a2[k]);
+                    }
+                };
+                auto step = [&](int j, const f32x4 W) {
+                    Sep d;
+                    float near = FLT_MAX, low = FLT_MAX;
+                    separate(j, d, near, low);
+                    if (__builtin_expect(undecided(near, low), 0)) {
+                        // rare: a pair of the wave that f2 cannot decide is
+                        // decided by the binary64 definition (0 < dx*dx +
+                        // dy*dy < theta^2, no fused multiply-add, grid point
+                        // formed as above) and its f2 moved to the matching
+                        // side of r2f (by at most `band`); a galaxy near its
+                        // point, if inside, is weighted here from its binary64
+                        // offset and left out of the binary32 step below
+                        const double2 G = p.pos[c0 + static_cast<uint32_t>(j)];
+                        const int l = hidden_lane();
+#pragma unroll
+                        for (int k = 0; k < K; ++k) {
+                            const double xg = p.x0 + static_cast<double>(min(point_x(l, k), ix1)) * p.gdx;
+                            const double yg = p.y0 + static_cast<double>(min(point_y(l, k), iy1)) * p.gdy;
+                            const double ddx = G.x - xg, ddy = G.y - yg;
+                            const double d2 = ddx * ddx + ddy * ddy;
+                            const bool inside = d2 < p.r2 && d2 > 0.0;
+                            const bool near_point = d.f2[k] <= C.near0;
+                            if (near_point && inside) {
+                                const double c2 = (ddx * ddx - ddy * ddy) / d2, s2 = (ddx * ddy) / d2;
+                                const float et = static_cast<float>(static_cast<double>(W.x) * c2 +
+                                                                    static_cast<double>(W.z) * s2);
+                                const float qn = q_table(table_pos(static_cast<float>(sqrt(d2)), C.k_x), C.tab);
+                                a1[k] = fmaf(qn, et, a1[k]);
+                                a2[k] = fmaf(qn * qn, W.w, a2[k]);
+                                cnt[k] += 1u;
+                            }
+                            const float moved = (inside && !near_point) ? C.f2_in : C.f2_out;
+                            if (fabsf(d.f2[k] - C.r2f) <= C.band || near_point) d.f2[k] = moved;
                         }
-                        const bool undecided = fabsf(f2[k] - C.r2f) <= C.band || near_point;
-                        const float moved = (inside && !near_point) ? C.f2_in : C.f2_out;
-                        f2[k] = undecided ? moved : f2[k];
+                    }
+                    weigh(d, W);
+                };
+                // In order, kApGroup at a time.
+                constexpr uint32_t kGroupMask = (1u << kApGroup) - 1u;
+                const int n = static_cast<int>(c1 - c0);
+                WeightU *const w = (WeightU *)(p.wgt + c0);
+                f32x4 wn[kApGroup], wc[kApGroup];
+#pragma unroll
+                for (int j = 0; j < kApGroup; ++j) wn[j] = w[j];
+                auto next_weights = [&](int i) {
+#pragma unroll
+                    for (int j = 0; j < kApGroup; ++j) {
+                        wc[j] = wn[j];
+                        wn[j] = w[i + kApGroup + j];
+                    }
+                };
+                for (int i = 0; i < n; i += kApGroup) {
+                    uint32_t in = static_cast<uint32_t>(inner >> i) & kGroupMask;
+                    while (in == kGroupMask) {
+                        next_weights(i);
+#pragma unroll
+                        for (int j = 0; j < kApGroup; ++j) step_inner(i + j, wc[j]);
+                        i += kApGroup;
+                        in = i < n ? static_cast<uint32_t>(inner >> i) & kGroupMask : 0u;
+                    }
+                    if (i >= n) break;
+                    next_weights(i);
+                    uint32_t todo = static_cast<uint32_t>(some >> i) & kGroupMask;
+                    // with one point per lane, a whole group in the general
+                    // step (its tests shared)
+                    if (K == 1 && todo != 0u && i + kApGroup <= n) {
+                        Sep d[kApGroup];
+                        float near = FLT_MAX, low = FLT_MAX;
+#pragma unroll
+                        for (int j = 0; j < kApGroup; ++j) separate(i + j, d[j], near, low);
+                        if (__builtin_expect(!undecided(near, low), 1)) {
+                            // weigh() counts the inner ones again
+                            all -= static_cast<uint32_t>(__builtin_popcount(in));
+#pragma unroll
+                            for (int j = 0; j < kApGroup; ++j) weigh(d[j], wc[j]);
+                            continue;
+                        }
+                    }
+                    for (; todo; todo &= todo - 1u) {
+                        const int j = __builtin_ctz(todo);
+                        if ((in >> j) & 1u)
+                            step_inner(i + j, w[i + j]);
+                        else
+                            step(i + j, w[i + j]);
                     }
                 }
-                // inside: w = 1, outside: w = 0, exactly (|f2 - r2f| > band
-                // here, or f2 was moved to 2 band from r2f); plain
-                // arithmetic, no compare.  Every value below is finite: f2 is
-                // positive and normal (see RAISE).
-                float rinv[K], q[K], wt[K];
-                uint32_t addr[K];
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
-                    wt[k] = fma_clamp01(f2[k] - C.r2f, C.nbig);
-                    cntf[k] += wt[k];
-                    const float f2c = RAISE ? max_f32(f2[k], C.near0) : f2[k];
-                    rinv[k] = __builtin_amdgcn_rsqf(f2c);
-                    const float sk = table_pos(f2c * rinv[k], C.k_x);
-                    addr[k] = C.tab + (static_cast<uint32_t>(sk) << 4);
-                    q[k] = __builtin_amdgcn_fractf(sk);  // position in the cell, for now
-                }
-                typedef float f32x4 __attribute__((ext_vector_type(4)));
-                using lds_f4 = __attribute__((address_space(3))) const f32x4;
-                f32x4 cq[K];
-#pragma unroll
-                for (int k = 0; k < K; ++k) cq[k] = *(lds_f4 *)(uintptr_t)(addr[k]);
-#pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    const float t = q[k];
-                    float qk = fmaf(fmaf(fmaf(cq[k].w, t, cq[k].z), t, cq[k].y), t, cq[k].x);
-                    qk *= wt[k];
-                    const float rr = rinv[k] * rinv[k];
-                    const float inner = fmaf(G.a2, py[k], G.b2 * (fdx[k] * fdy[k]));
-                    const float et = fmaf(rr, inner, G.a);
-                    a1[k] = fmaf(qk, et, a1[k]);
-                    a2[k] = fmaf(qk * qk, G.ee, a2[k]);
+                    S1[k] += static_cast<double>(a1[k]);
+                    S2[k] += static_cast<double>(a2[k]);
+                    cnt[k] += static_cast<uint32_t>(cntf[k]);  // at most 64, exact
                 }
             }
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                S1[k] += static_cast<double>(a1[k]);
-                S2[k] += static_cast<double>(a2[k]);
-                cnt[k] += static_cast<uint32_t>(cntf[k]);  // at most 64, exact
-            }
+            skip = run - runs;
         }
     }
+#pragma unroll
+    for (int k = 0; k < K; ++k) cnt[k] += all;
+    const int own = hidden_lane();
+    // the waves' sums, added in wave order (in the filter table's place)
+    constexpr int kPts = 64 * K;
+    static_assert((kApWaves - 1) * kPts * (sizeof(double2) + sizeof(uint32_t)) <= sizeof(qtab), "space for the sums");
+    double2 *const sum = reinterpret_cast<double2 *>(qtab);
+    uint32_t *const num = reinterpret_cast<uint32_t *>(sum + (kApWaves - 1) * kPts);
+    __syncthreads();
+    if (wave > 0) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            sum[(wave - 1) * kPts + k * 64 + lane] = make_double2(S1[k], S2[k]);
+            num[(wave - 1) * kPts + k * 64 + lane] = cnt[k];
+        }
+    }
+    __syncthreads();
+    if (wave > 0) return;
     uint32_t in_lane = 0, lanes = 0;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        if (valid[k]) {
-            const int64_t o = static_cast<int64_t>(iyk[k]) * p.nx + ixk[k];
-            p.map[o] = S1[k] / p.n_gal;
-            if (p.snr) p.snr[o] = S2[k] > 0.0 ? (1.4142135623730951 * S1[k]) / sqrt(S2[k]) : __builtin_nan("");
-            if (p.n_in) p.n_in[o] = cnt[k];
+        for (int w = 0; w < kApWaves - 1; ++w) {
+            const double2 v = sum[w * kPts + k * 64 + lane];
+            S1[k] += v.x;
+            S2[k] += v.y;
+            cnt[k] += num[w * kPts + k * 64 + lane];
+        }
+        if (point_x(own, k) <= ix1 && point_y(own, k) <= iy1) {
+            const int64_t o = static_cast<int64_t>(point_y(own, k)) * p.nx + point_x(own, k);
             in_lane += cnt[k];
             lanes += 1u;
+            if (p.parts > 1) {
+                const int64_t m = static_cast<int64_t>(p.nx) * p.ny;
+                p.part_s[blockIdx.y * m + o] = make_double2(S1[k], S2[k]);
+                p.part_n[blockIdx.y * m + o] = cnt[k];
+            } else {
+                ap_store(p, o, S1[k], S2[k], cnt[k]);
+            }
         }
     }
-    if (p.stats) {
-        const uint32_t in_wave = wave_sum_u32(in_lane);
+    // one atomic per workgroup and counter at most: thousands of them on one
+    // address take longer than a small map
+    if (blockIdx.y == 0) {
         const uint32_t pts = wave_sum_u32(lanes);
-        if (lane == 0) {
-            atomicAdd(p.stats + 0, static_cast<unsigned long long>(tested) * pts);
-            atomicAdd(p.stats + 1, static_cast<unsigned long long>(in_wave));
-        }
+        if (lane == 0) atomicAdd(p.stats + 0, static_cast<unsigned long long>(tested) * pts);
     }
+    if (p.parts == 1) {
+        const uint32_t in_block = wave_sum_u32(in_lane);
+        if (lane == 0) atomicAdd(p.stats + 1, static_cast<unsigned long long>(in_block));
+    }
+}
+
+// Blocks of several workgroups: the parts' sums of each point, added in order.
+__global__ void __launch_bounds__(256) k_ap_finish(const ApParams p) {
+    const int64_t m = static_cast<int64_t>(p.nx) * p.ny;
+    const int64_t o = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    double S1 = 0.0, S2 = 0.0;
+    uint32_t cnt = 0;
+    if (o < m) {
+        for (int k = 0; k < p.parts; ++k) {
+            const double2 v = p.part_s[k * m + o];
+            S1 += v.x;
+            S2 += v.y;
+            cnt += p.part_n[k * m + o];
+        }
+        ap_store(p, o, S1, S2, cnt);
+    }
+    __shared__ uint32_t in[4];
+    const uint32_t in_wave = wave_sum_u32(cnt);
+    if ((threadIdx.x & 63u) == 0u) in[threadIdx.x >> 6] = in_wave;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        atomicAdd(p.stats + 1, static_cast<unsigned long long>(in[0]) + in[1] + in[2] + in[3]);
 }
 
 // ------------------------------------------------------------------- host
@@ -581,6 +796,19 @@ int points_per_lane(const pc_grid *g, double theta, int cus) {
     return 16.0 * std::max(g->dx, g->dy) <= 0.25 * theta && blocks16 >= 16.0 * cus ? 2 : 1;
 }
 
+// Workgroups per block: a grid of few blocks leaves CUs idle, or one or two
+// workgroups on each, which latency then bounds.  kApPerCu workgroups per CU
+// (nine times what fits at once) also let large and small blocks even out; more
+// than kApMaxParts of a block cost more in the final sum than they gain.
+// Map kernel and sum with at most 1 / 4 / 8 / 16 / 32 parts: 301 / 105 / 77 / 77 /
+// 80 us at 120 blocks, 1.77 / 1.73 / 1.70 / 1.69 / 1.71 ms at 4096; from 16384 blocks
+// on there is one part (191 ms at 16384 blocks of 16 x 16 points).
+int block_parts(int32_t n_tiles, int cus) {
+    int parts = 1;
+    while (parts < kApMaxParts && static_cast<int64_t>(n_tiles) * parts < int64_t(kApPerCu) * cus) parts *= 2;
+    return parts;
+}
+
 // The binary32 cut and its guard bands.  Notation: u = 2^-24, v = 2^-53;
 // (xb, yb) a block's reference point, every point of the block within hx
 // (hy) of it; D = |d| exactly, DX = x_i - x_p exactly.  The kernel forms
@@ -613,7 +841,8 @@ int points_per_lane(const pc_grid *g, double theta, int cus) {
 // points and of the reference point.  Where the increasing condition fails
 // (grid spacing beyond ~1e6 theta), band is made large enough that every pair
 // with f2 below r2f + band is decided in binary64.
-void cut_bands(const pc_grid *g, double theta, double r2, int P, float *r2f, float *band, float *near0) {
+void cut_bands(const pc_grid *g, double theta, double r2, int P, float *r2f, float *band, float *near0,
+               float *in2, float *near2, float *out2) {
     const double u = std::ldexp(1.0, -24), v = std::ldexp(1.0, -53), u1 = u + 2.0 * v, w = u * (2.0 + u);
     const double ext_x = std::fabs(g->x0) + (g->nx + 8.0 * P) * g->dx;
     const double ext_y = std::fabs(g->y0) + (g->ny + 8.0 * P) * g->dy;
@@ -636,6 +865,18 @@ void cut_bands(const pc_grid *g, double theta, double r2, int P, float *r2f, flo
     *band = up(2.0 * G + floor_abs);
     const double dn = std::ldexp(std::sqrt(cx * cx + cy * cy), 17);
     *near0 = up(2.0 * std::max(dn * dn + B(dn), B(1e-150)) + floor_abs);
+    // Bounds for whole blocks (D the distance to any point of the block): D^2 <=
+    // r2f - 2 band has f2 <= D^2 + B(D) < r2f - band, as B(D) <= G <= band / 2;
+    // D^2 >= r2f + 2 band has f2 >= D^2 - B(D) > r2f + band where D^2 - B(D)
+    // increases and band is below r2 / 100 (then B(D) <= 1.05 G at that D); D^2
+    // >= 4 near0 (D > 2 Dn) has f2 > near0, as B(D) / D^2 falls with D and is
+    // below 2^-14 from Dn on.  The kernel compares binary32 sums of squares, good
+    // to 10^-6 for in2 and out2 and, as 2 sqrt(near0) is above hx / 23, to 10^-4
+    // for near2.
+    const double r = static_cast<double>(*r2f), bd = static_cast<double>(*band);
+    *in2 = static_cast<float>((r - 2.0 * bd) * (r > 2.0 * bd ? 1.0 - 1e-5 : 1.0 + 1e-5));
+    *out2 = 2.0 * (1.0 - qa) * theta0 >= qb && bd <= 0.01 * r2 ? up((r + 2.0 * bd) * (1.0 + 1e-5)) : INFINITY;
+    *near2 = up(4.0 * static_cast<double>(*near0) * (1.0 + 1e-3));
 }
 
 }  // namespace
@@ -669,6 +910,12 @@ extern "C" int pc_aperture_mass(const pc_shear_catalog *cat, const pc_grid *grid
     if (rc) return rc;
     const int64_t n_cells = int64_t(L.ncx) * L.ncy;
 
+    const int P = points_per_lane(grid, theta_max, di->cus);
+    const int32_t side = 8 * P;
+    const int32_t tiles_x = (grid->nx + side - 1) / side;
+    const int32_t n_tiles = tiles_x * ((grid->ny + side - 1) / side);
+    const int parts = block_parts(n_tiles, di->cus);
+
     // work space
     const bool host_in = !cat->on_device, host_out = !out_on_device;
     const size_t nn = static_cast<size_t>(n > 0 ? n : 1);
@@ -676,12 +923,15 @@ extern "C" int pc_aperture_mass(const pc_shear_catalog *cat, const pc_grid *grid
     const size_t o_in = host_in ? take(&size, 4 * sizeof(double) * nn) : 0;
     const size_t o_keys = take(&size, sizeof(uint32_t) * nn);
     const size_t o_idx = take(&size, sizeof(uint32_t) * nn);
-    const size_t o_gal = take(&size, sizeof(ApGal) * nn);
+    const size_t o_pos = take(&size, sizeof(double2) * nn);
+    const size_t o_wgt = take(&size, sizeof(ApWeight) * (nn + 2 * kApGroup));
     const size_t o_start = take(&size, sizeof(uint32_t) * static_cast<size_t>(n_cells + 1));
     const size_t o_cursor = take(&size, sizeof(uint32_t) * static_cast<size_t>(n_cells));
     const size_t o_sums = take(&size, sizeof(uint32_t) * scan_sums_words(n_cells + 1));
     const size_t o_flag = take(&size, 4 * sizeof(uint32_t));
     const size_t o_stats = take(&size, 2 * sizeof(unsigned long long));
+    const size_t o_part_s = take(&size, parts > 1 ? sizeof(double2) * static_cast<size_t>(parts) * static_cast<size_t>(m) : 0);
+    const size_t o_part_n = take(&size, parts > 1 ? sizeof(uint32_t) * static_cast<size_t>(parts) * static_cast<size_t>(m) : 0);
     const size_t o_qtab = take(&size, sizeof(float4) * (kQCells + 1));
     const size_t o_out = host_out ? take(&size, (2 * sizeof(double) + sizeof(uint32_t)) * static_cast<size_t>(m)) : 0;
     DevMem ws;
@@ -705,7 +955,8 @@ extern "C" int pc_aperture_mass(const pc_shear_catalog *cat, const pc_grid *grid
     }
     uint32_t *keys = reinterpret_cast<uint32_t *>(base + o_keys);
     uint32_t *idx = reinterpret_cast<uint32_t *>(base + o_idx);
-    ApGal *gal = reinterpret_cast<ApGal *>(base + o_gal);
+    double2 *pos = reinterpret_cast<double2 *>(base + o_pos);
+    ApWeight *wgt = reinterpret_cast<ApWeight *>(base + o_wgt);
     uint32_t *start = reinterpret_cast<uint32_t *>(base + o_start);
     uint32_t *cursor = reinterpret_cast<uint32_t *>(base + o_cursor);
     uint32_t *sums = reinterpret_cast<uint32_t *>(base + o_sums);
@@ -729,7 +980,7 @@ extern "C" int pc_aperture_mass(const pc_shear_catalog *cat, const pc_grid *grid
                "cell cursors");
         k_ap_scatter<<<dim3(gn), dim3(256), 0, st>>>(keys, n, cursor, idx);
         AP_HIP(hipGetLastError(), "k_ap_scatter");
-        k_ap_place<<<dim3(gn), dim3(256), 0, st>>>(X, Y, E1, E2, keys, idx, start, n_cells, n, gal);
+        k_ap_place<<<dim3(gn), dim3(256), 0, st>>>(X, Y, E1, E2, keys, idx, start, n_cells, n, pos, wgt);
         AP_HIP(hipGetLastError(), "k_ap_place");
     }
     uint32_t h_flag = 0;
@@ -745,7 +996,8 @@ extern "C" int pc_aperture_mass(const pc_shear_catalog *cat, const pc_grid *grid
         d_nin = reinterpret_cast<uint32_t *>(d_snr + m);
     }
     ApParams p;
-    p.gal = gal;
+    p.pos = pos;
+    p.wgt = wgt;
     p.start = start;
     p.lat = L;
     p.x0 = grid->x0;
@@ -754,19 +1006,18 @@ extern "C" int pc_aperture_mass(const pc_shear_catalog *cat, const pc_grid *grid
     p.gdy = grid->dy;
     p.nx = grid->nx;
     p.ny = grid->ny;
-    const int P = points_per_lane(grid, theta_max, di->cus);
-    const int group_side = 16 * P;  // 2 x 2 blocks of 8P x 8P points
-    p.tiles_x = (grid->nx + group_side - 1) / group_side;
-    const int tiles_y = (grid->ny + group_side - 1) / group_side;
-    p.n_tiles = p.tiles_x * tiles_y;
+    p.tiles_x = tiles_x;
+    p.n_tiles = n_tiles;
     p.per_xcd = (p.n_tiles + 7) / 8;
-    p.theta = theta_max;
+    p.parts = parts;
+    p.part_s = parts > 1 ? reinterpret_cast<double2 *>(base + o_part_s) : nullptr;
+    p.part_n = parts > 1 ? reinterpret_cast<uint32_t *>(base + o_part_n) : nullptr;
     p.r2 = theta_max * theta_max;
     p.reach = theta_max * (1.0 + 1e-9);
     // RN32(kQCells / theta) / kQCells: exact (a power of two, no subnormal
     // for theta below the extent limit)
     p.k_x = static_cast<float>(static_cast<double>(kQCells) / theta_max) / static_cast<float>(kQCells);
-    cut_bands(grid, theta_max, p.r2, P, &p.r2f, &p.band, &p.near0);
+    cut_bands(grid, theta_max, p.r2, P, &p.r2f, &p.band, &p.near0, &p.in2, &p.near2, &p.out2);
     p.nbig = -1.0f / p.band;
     p.f2_in = p.r2f - 2.0f * p.band;
     p.f2_out = p.r2f + 2.0f * p.band;
@@ -787,7 +1038,7 @@ extern "C" int pc_aperture_mass(const pc_shear_catalog *cat, const pc_grid *grid
     // f2 needs no raise when every value it can take in the binary32 step is
     // positive and normal (see k_ap_map)
     const bool raise = !(p.f2_in >= FLT_MIN);
-    const dim3 grid_dim(static_cast<uint32_t>(8 * p.per_xcd)), block_dim(64 * kApWaves);
+    const dim3 grid_dim(static_cast<uint32_t>(8 * p.per_xcd), static_cast<uint32_t>(parts)), block_dim(64 * kApWaves);
     if (P == 2 && !raise)
         k_ap_map<2, false><<<grid_dim, block_dim, 0, st>>>(p);
     else if (P == 2)
@@ -797,6 +1048,10 @@ extern "C" int pc_aperture_mass(const pc_shear_catalog *cat, const pc_grid *grid
     else
         k_ap_map<1, true><<<grid_dim, block_dim, 0, st>>>(p);
     AP_HIP(hipGetLastError(), "k_ap_map");
+    if (parts > 1) {
+        k_ap_finish<<<dim3(static_cast<uint32_t>((m + 255) / 256)), dim3(256), 0, st>>>(p);
+        AP_HIP(hipGetLastError(), "k_ap_finish");
+    }
     if (timing) AP_HIP(hipEventRecord(ev.b, st), "hipEventRecord");
 
     unsigned long long h_stats[2] = {0, 0};
