@@ -40,12 +40,15 @@
 // points it was 70% of the kernel's vector instructions.
 //
 // What bounds it: vector instructions and matrix products, which a SIMD does
-// not overlap (1M workload: 71% + 19% of the SIMDs' cycles, 61 vector
-// instructions per block).  Counting kernel, this one against the vector kernel
-// of 256-point tiles on the same ordering: 24.0 / 42.7 ms on the 1M workload,
-// 130 / 212 ms for 1M x 1M points in 254 bins, 16.5 / 21.0 ms for 64 mocks x
-// 300,000 randoms, 0.12 / 0.29 ms for 10,000 + 10,000 points, 0.028 / 0.134 ms
-// for 1003 points.
+// not overlap: together some 85% of the cycles, the rest waits for LDS and at
+// the tile pair's barriers.  A block of one edge takes 34 vector instructions
+// and four products (about 47 cycles of a CU), of two 57, through the table 151,
+// by differences 97 per half; the item's and the columns' shares are 15 to 27 per
+// block.  Counting kernel, this one against the vector kernel of 256-point tiles
+// on the same ordering: 22.5 / 42.7 ms on the 1M workload, 127 / 212 ms for 1M x 1M
+// points in 254 bins, 13.8 / 21.0 ms for 64 mocks x 300,000 randoms, 1.63 / 2.2 ms
+// for 300,000 x 400,000 resident points in 24 even bins, 0.10 / 0.29 ms for 10,000
+// + 10,000 points, 0.024 / 0.134 ms for 1003 points.
 //
 // Error bound (u = 2^-24, v = 2^-53, R = r_I + r_J the tiles' radii, D = |D|).
 // For an edge inside the tile pair's interval |h - D^2| <= R (2D + R) to
@@ -71,12 +74,12 @@
 // kernel's forms have 28 and 0.5 to 2.2 (differences), 2.8 and 0.23 to 0.76
 // (tile-centred Gram).
 //
-// Blocks of five edges and more (near tiles, sparse catalogues) look each chord
+// Blocks of three edges and more (near tiles, sparse catalogues) look each chord
 // up in a table instead: c' = RN(RN(h) - d) is within E_t = E + 4 u (D + R)^2 of the
 // chord, its cell holds at most one edge, and a chord within E_t of that edge
 // goes to binary64.  The table needs E_t below an eighth of a cell (see
 // build_lutb); blocks that reach below that (near ones: E grows with the tiles'
-// size, not with the chord) form their chords from differences, (D + a') - b'
+// size, not with the chord) form their chords from differences, (D - b') + a'
 // per coordinate, whose error follows the chord: the difference vector is off
 // by at most u (2D + 2R + sqrt(c)) <= 3 u (D + R), three roundings square it, and
 // the table's edge and the final difference add two: below A sqrt(c) + B with
@@ -106,11 +109,11 @@ constexpr uint32_t kDiagBlock = 1u << 31;   // block descriptor: on the diagonal
 constexpr uint32_t kTableBlock = 1u << 30;  // block descriptor: chords go through the table
 constexpr uint32_t kNearBlock = 1u << 29;   // with kTableBlock: chords from differences
 // Edges from which a whole block goes through the table: one edge costs a block
-// the same half add and minimum per pair, the table one LDS read per pair whatever
-// their number.  Counting kernel with the line at 3 / 5 / 8 / never: 2.05 / 2.04 /
-// 2.47 / 3.17 ms for 300,000 x 400,000 points, 16.9 / 16.5 / 17.6 / 18.8 ms for 64
-// mocks, 24.2 / 24.0 / 24.1 / 24.7 ms on the 1M workload.
-constexpr uint32_t kTableEdges = 5;
+// the same half add and minimum per pair, the table nine instructions and two
+// LDS accesses per pair whatever their number.  Counting kernel with the line at
+// 3 / 4 / 5 / 6: 1.63 / 1.68 / 1.67 / 1.77 ms for 300,000 x 400,000 points, 13.8 / 14.0 /
+// 14.6 / 15.1 ms for 64 mocks, 22.5 / 22.6 / 22.7 / 23.0 ms on the 1M workload.
+constexpr uint32_t kTableEdges = 3;
 constexpr uint32_t kOnes = 0x3F803F80u;     // two bf16 ones
 
 struct BParams {
@@ -205,7 +208,8 @@ __device__ __forceinline__ void tally(float d1, float d2, uint32_t &n, uint32_t 
 }
 // the counts of the first and the next edge
 __device__ __forceinline__ void counts_of(uint32_t n, uint32_t &first, uint32_t &next) {
-    const uint32_t w = n * 0x01010101u;  // n_0 + 2^8 n_1 + 2^16 n_2 + 2^24 n_3
+    uint32_t w = n + (n << 8);  // n 0x01010101 = n_0 + 2^8 n_1 + 2^16 n_2 + 2^24 n_3,
+    w += w << 16;               // without the quarter-rate multiply
     first = (w & 0xFFu) + ((w >> 8) & 0xFFu);
     next = ((w >> 16) & 0xFFu) + (w >> 24);
 }
@@ -271,6 +275,10 @@ struct Pending {
     uint32_t n;                 // may pass kQueued: the pairs beyond were done at once
 };
 constexpr uint32_t kTableRow = 1u << 31;
+// Table look-ups of a lane in flight: one at a time each waits for its LDS read
+// (with 4 / 8 / 16: 1.83 / 1.78 / 1.70 ms for 300,000 x 400,000 points, 16.0 / 15.6 /
+// 15.6 ms for 64 mocks; 16 leaves no registers for the rest).
+constexpr int kLook = 8;
 
 __device__ __forceinline__ void recheck(const Hist &h, const double4 *pa, const double4 *pb, uint32_t edge,
                                         const double *e64) {
@@ -332,15 +340,30 @@ __device__ __forceinline__ void block_products(const u32x4 (*As)[kWave], int bi,
     D.d[3] = product(a1, B[1], C);
 }
 
-// The edge set's chord table in LDS (8 bytes a cell: the edge, the row below it).
+// The edge set's chord table in LDS (8 bytes a cell: the edge, and the row below
+// it as its byte offset in the histogram, row << row_shift).
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+using LdsU = __attribute__((address_space(3))) uint32_t;
+using LdsCell = const __attribute__((address_space(3))) u32x2;
+__device__ __forceinline__ uint32_t lds_addr(const void *p) {
+    return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void *)(p)));
+}
 struct ChordTable {
-    const uint2 *cells;
+    uint32_t base;              // LDS address of cell 0, less 8 key0
     uint32_t shift, key0;
+    uint32_t row_shift;
     float lo, hi;               // cells' range
 };
-__device__ __forceinline__ uint2 cell_of(const ChordTable &t, float c) {
+__device__ __forceinline__ u32x2 cell_of(const ChordTable &t, float c) {
     const uint32_t key = __float_as_uint(__builtin_amdgcn_fmed3f(c, t.lo, t.hi));
-    return t.cells[(key >> t.shift) - t.key0];
+    return *(LdsCell *)(uintptr_t)(((key >> t.shift) << 3) + t.base);
+}
+// the byte offset of the row of a chord that differs from its cell's edge by x
+__device__ __forceinline__ uint32_t row_offset(const ChordTable &t, u32x2 e, float x) {
+    return ((__float_as_uint(x) >> 31) << t.row_shift) + e.y;
+}
+__device__ __forceinline__ void add_offset(uint32_t lds, uint32_t n) {
+    __hip_atomic_fetch_add((LdsU *)(uintptr_t)lds, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) k_count_blocks(BParams p) {
@@ -360,16 +383,13 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
     h.T = reinterpret_cast<uint32_t *>(lds + 8 * (p.max_edges + p.max_cells));
     h.cols = p.cols;
     h.n_edges = 0;
-    tbl.cells = cells;
-    tbl.shift = tbl.key0 = 0;
+    tbl.base = tbl.shift = tbl.key0 = 0;
+    tbl.row_shift = 2u + static_cast<uint32_t>(__builtin_ctz(static_cast<uint32_t>(p.cols)));
     tbl.lo = tbl.hi = 0.0f;
     int cur_tab = -1, cur_job = -1;
     bool has_table = false;
     unsigned long long *cur_counts = nullptr;
     uint32_t since_flush = 0, cur_seg = 0xFFFFFFFFu, cur_t = 0;
-    float4 gi[kPer];
-#pragma unroll
-    for (int r = 0; r < kPer; ++r) gi[r] = make_float4(0.f, 0.f, 0.f, 0.f);
     uint32_t seen = 0;                        // pairs this lane sent to the re-check
     uint32_t xs = 0;                          // thread 0's place in the queue's slices
     uint64_t wi = 0, end = 0;
@@ -379,7 +399,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
     // units per workgroup to end evenly.  Cut and whole: 28 / 73 us at 3
     // survivors (1003 points), 120 / 141 us at 820 (10,000 + 10,000 points) with
     // 1024 workgroups; from 4 survivors a workgroup on a whole one pays its
-    // fixed work once (2.05 / 2.02 ms at 38,861: no difference either way).
+    // fixed work once (no difference either way at 38,861).
     const uint64_t total = ld_uniform(p.n_items);
     const uint32_t part_bits = total >= 4ull * gridDim.x ? 0u : total * 2u >= gridDim.x ? 2u : 4u;
     if (tid0 < 6) sh_stat[tid0] = 0ull;
@@ -441,7 +461,8 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
         // what the item reads: its i-points (kept while the i-tile stays), the
         // wave's first column of j-points, the bounds
         const float4 *jg = ld_uniform(&sp->jg) + jbeg;
-        if (new_i) {
+        float4 gi[kPer];
+        {
 #pragma unroll
             for (int r = 0; r < kPer; ++r) gi[r] = (ld_uniform(&sp->ig) + ibeg)[min(r * kThreads + tid, i_lim - 1)];
         }
@@ -484,12 +505,16 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
                 has_table = n_cells > 0 && n_cells <= p.max_cells;
                 tbl.shift = ld_uniform(&td->b_shift);
                 tbl.key0 = ld_uniform(&td->b_key0);
+                tbl.base = lds_addr(cells) - 8u * tbl.key0;
                 tbl.lo = __uint_as_float(tbl.key0 << tbl.shift);
                 tbl.hi = __uint_as_float(((tbl.key0 + static_cast<uint32_t>(n_cells)) << tbl.shift) - 1u);
                 __syncthreads();
                 for (int k = tid; k < h.n_edges; k += kThreads) e_lds[k] = e64[k];
                 if (has_table)
-                    for (int k = tid; k < n_cells; k += kThreads) cells[k] = src[k];
+                    for (int k = tid; k < n_cells; k += kThreads) {
+                        const uint2 e = src[k];
+                        cells[k] = make_uint2(e.x, e.y << tbl.row_shift);
+                    }
                 clear_hist(h);
                 cur_tab = tab;
             }
@@ -565,6 +590,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
             return uni_f(static_cast<float>(e_lds[K0 + k] + h_off));
         };
         uint32_t cnt = 0u;         // lane k: the wave's pairs above edge K0 + k
+        const uint32_t column = lds_addr(h.T) + 4u * static_cast<uint32_t>(tid & (h.cols - 1));
         auto add_above = [&](uint32_t k, uint32_t pairs) {
             if (k < kWave) cnt += lane == static_cast<int>(k) ? pairs : 0u;
             else if (lane == 0)
@@ -616,6 +642,20 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
                 for (; hits; hits &= hits - 1u) {
                     const int s = __builtin_ctz(hits);
                     send(h, pend, point_i(bi, s), point_j(s), K0 + k, e_lds);
+                }
+            };
+            // of the lane's pairs s0 .. s0 + kLook - 1, counted at `at`, those of hits
+            auto send_rows = [&](uint32_t hits, const uint32_t (&at)[kLook], int bi, int s0) {
+                seen += __popc(hits);
+                for (; hits; hits &= hits - 1u) {
+                    const int v = __builtin_ctz(hits);
+                    uint32_t o = at[0];
+#pragma unroll
+                    for (int w = 1; w < kLook; ++w) {
+                        asm("" : "+v"(o));  // no indexed array: it would be written to scratch on every pass
+                        o = v == w ? at[w] : o;
+                    }
+                    send(h, pend, point_i(bi, s0 + v), point_j(s0 + v), (o >> tbl.row_shift) | kTableRow, e_lds);
                 }
             };
             // blocks of one or two edges, those of the same edges together: a
@@ -684,63 +724,73 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
                         const float S = Dl + R, A = 0x1p-20f * S, A2 = 2.0f * A * A, B2 = 0x1p-83f * (S * S) * (S * S);
                         const float q = A * pow2(28u - tbl.shift);
                         const float floor_c = fmaxf(q * q, 0x1p-42f * S * S * pow2(28u - tbl.shift)) * (1.0f + 0x1p-10f);
-                        float4 pj[2];
+                        const float A2n = -A2;
+                        float px[2], py[2], pz[2];
+                        int32_t below[2];  // i-points (of the tile) that the lane's j-points pair with
 #pragma unroll
-                        for (int c = 0; c < 2; ++c) pj[c] = jg[min(cb * kG + 16 * c + (lane & 15), j_lim - 1)];
+                        for (int c = 0; c < 2; ++c) {
+                            const int j = cb * kG + 16 * c + (lane & 15);
+                            const float4 g = jg[min(j, j_lim - 1)];
+                            px[c] = fmaf(0.5f, g.x, fx);
+                            py[c] = fmaf(0.5f, g.y, fy);
+                            pz[c] = fmaf(0.5f, g.z, fz);
+                            below[c] = j >= j_lim ? 0 : (key & kDiagBlock) ? min(j, i_lim) : i_lim;
+                        }
 #pragma unroll 1
-                        for (int r = 0; r < 8; ++r) {
-                            const int i = bi * kG + 16 * (r >> 2) + 4 * grp + (r & 3);
-                            const float4 g = (ld_uniform(&sp->ig) + ibeg)[min(i, i_lim - 1)];
-                            const float px = fmaf(-0.5f, g.x, fx), py = fmaf(-0.5f, g.y, fy), pz = fmaf(-0.5f, g.z, fz);
+                        for (int r = 0; r < 8; r += 4) {
+                            float4 g[4];
+                            const int i0 = bi * kG + 4 * r + 4 * grp;
 #pragma unroll
-                            for (int c = 0; c < 2; ++c) {
-                                const int j = cb * kG + 16 * c + (lane & 15);
-                                const float dx = fmaf(0.5f, pj[c].x, px), dy = fmaf(0.5f, pj[c].y, py), dz = fmaf(0.5f, pj[c].z, pz);
-                                const float x = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-                                if (i < i_lim && j < j_lim && (!(key & kDiagBlock) || i < j)) {
-                                    const uint2 e = cell_of(tbl, x);
-                                    const float d = __uint_as_float(e.x) - x;
-                                    const uint32_t row = e.y + (__float_as_uint(d) >> 31);
-                                    add_row(h, row, 1u);
-                                    if (fmaf(d, d, -A2 * x) <= B2 || x <= floor_c) {
-                                        const int s = 8 * (r >> 2) + 4 * c + (r & 3);
-                                        ++seen;
-                                        send(h, pend, point_i(bi, s), point_j(s), row | kTableRow, e_lds);
-                                    }
-                                }
+                            for (int v = 0; v < 4; ++v) g[v] = (ld_uniform(&sp->ig) + ibeg)[min(i0 + v, i_lim - 1)];
+                            float x[8], d[8];
+                            u32x2 e[8];
+                            uint32_t at[8], hits = 0;
+#pragma unroll
+                            for (int v = 0; v < 8; ++v) {
+                                const float4 &a = g[v & 3];
+                                const float dx = fmaf(-0.5f, a.x, px[v >> 2]), dy = fmaf(-0.5f, a.y, py[v >> 2]),
+                                            dz = fmaf(-0.5f, a.z, pz[v >> 2]);
+                                x[v] = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+                                e[v] = cell_of(tbl, x[v]);
                             }
+#pragma unroll
+                            for (int v = 0; v < 8; ++v) {
+                                d[v] = __uint_as_float(e[v].x) - x[v];
+                                at[v] = row_offset(tbl, e[v], d[v]);
+                                const bool ok = i0 + (v & 3) < below[v >> 2];
+                                add_offset(at[v] + column, ok ? 1u : 0u);
+                                if (ok && (fmaf(d[v], d[v], A2n * x[v]) <= B2 || x[v] <= floor_c)) hits |= 1u << v;
+                            }
+                            send_rows(hits, at, bi, 2 * r);
                         }
                         continue;
                     }
                     const float H0 = threshold(k0);
                     const float top = uni_f(static_cast<float>(static_cast<double>(H0) + D2));  // c = top - d
-                    const f32x4 C = {H0, H0, H0, H0};
-#pragma unroll 1
-                    for (int q = 0; q < 4; ++q) {
-                        const f32x4 d = product(As[2 * bi + (q >> 1)][lane], (q & 1) ? B[1] : B[0], C);
-                        uint2 e[4];
-                        float c[4];
+                    block_products(As, bi, B, H0, D);
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            c[v] = top - d[v];
+                    for (int q = 0; q < 16; q += kLook) {
+                        float c[kLook];
+                        u32x2 e[kLook];
+                        uint32_t at[kLook];
+                        float least = INFINITY;
+#pragma unroll
+                        for (int v = 0; v < kLook; ++v) {
+                            c[v] = top - D.d[(q + v) >> 2][v & 3];
                             e[v] = cell_of(tbl, c[v]);
                         }
-                        bool hit[4], any = false;
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const float x = __uint_as_float(e[v].x) - c[v];
-                            e[v].y += __float_as_uint(x) >> 31;
-                            add_row(h, e[v].y, 1u);
-                            hit[v] = fabsf(x) <= E_t;
-                            any |= hit[v];
+                        for (int v = 0; v < kLook; ++v) {
+                            c[v] = __uint_as_float(e[v].x) - c[v];
+                            at[v] = row_offset(tbl, e[v], c[v]);
+                            add_offset(at[v] + column, 1u);
+                            least = fminf(least, fabsf(c[v]));
                         }
-                        if (__builtin_expect(__builtin_amdgcn_ballot_w64(any) != 0, 0)) {
+                        if (__builtin_expect(__builtin_amdgcn_ballot_w64(least <= E_t) != 0, 0)) {
+                            uint32_t hits = 0;
 #pragma unroll
-                            for (int v = 0; v < 4; ++v)
-                                if (hit[v]) {
-                                    ++seen;
-                                    send(h, pend, point_i(bi, 4 * q + v), point_j(4 * q + v), e[v].y | kTableRow, e_lds);
-                                }
+                            for (int v = 0; v < kLook; ++v) hits |= fabsf(c[v]) <= E_t ? 1u << v : 0u;
+                            send_rows(hits, at, bi, q);
                         }
                     }
                     continue;
