@@ -23,6 +23,7 @@ namespace pc {
 
 // preparation steps that do not depend on the tile size (pc_prep.hip)
 hipError_t launch_zero(void *p, size_t bytes, hipStream_t st);
+hipError_t launch_zero_put(void *p, size_t bytes, void *dst, const void *src, size_t n, hipStream_t st);
 int64_t convert_blocks(int64_t n);
 int64_t order_blocks(int64_t n);
 uint32_t order_buckets(int64_t n, int per_point);
@@ -56,8 +57,8 @@ void lds_layout(int32_t max_edges, int32_t max_cells, int32_t cols, int32_t *col
 hipError_t occupancy(uint32_t lds_bytes, int *per_cu);
 hipError_t launch_count(const SegDesc *segs, const TableDesc *tabs, const uint64_t *items, const uint64_t *tiles,
                         const unsigned long long *n_items, unsigned long long *queue, unsigned long long *rechecked,
-                        unsigned long long *stats, int32_t max_edges, int32_t max_cells, int32_t cols, uint32_t lds_bytes,
-                        int chunk, uint64_t flush_cap, int grid, hipStream_t st);
+                        unsigned long long *stats, unsigned long long *counts, const unsigned long long *copies,
+                        int64_t count_words, int32_t max_edges, int32_t max_cells, int32_t cols, uint32_t lds_bytes, int chunk, uint64_t flush_cap, int grid, hipStream_t st);
 }
 namespace t128 { PC_TILE_STEPS }
 #undef PC_TILE_STEPS
@@ -814,6 +815,30 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         const float4 *groups = nullptr;       // kGroups per tile (block kernel)
     };
     std::vector<ViewPtrs> vp(views.size());
+    // LDS of the block kernel, and whether every edge set's chord table is in it
+    int32_t max_edges = 0, max_cells = 0, bcols = 0;
+    uint32_t blocks_lds = 0;
+    bool ordered = !blocks;
+    if (blocks) {
+        bool all = true;
+        for (auto &t : tabs) {
+            max_edges = std::max(max_edges, static_cast<int32_t>(t->host.e64.size()));
+            max_cells = std::max(max_cells, static_cast<int32_t>(t->host.lutb.size()));
+            all = all && !t->host.lutb.empty();
+        }
+        blk::lds_layout(max_edges, max_cells, lt.cols ? std::min(lt.cols, 16) : 16, &bcols, &max_cells, &blocks_lds);
+        // Few pairs are counted in the caller's order: unordered groups prune
+        // nothing and put every block through the chord table (hence only with
+        // one), but the four ordering launches cost more than that.  Whole
+        // calls, ordered / caller's order: 100 / 79 us for the pairs of 1003
+        // points, 111 / 95 of 4096, 123 / 110 of 6000; 122 / 108 for 4096 x 4096,
+        // 156 / 144 for 8192 x 8192 in bins of all scales, but 131 / 136 where the
+        // bins end at 2 degrees and the order lets most pairs go.
+        ordered = !all || max_cells == 0;
+        double pairs = 0.0;
+        for (const SegDesc &sd : segs) pairs += static_cast<double>(sd.ni) * static_cast<double>(sd.nj) * (sd.tri ? 0.5 : 1.0);
+        ordered = ordered || pairs > kUnorderedPairs;
+    }
     std::vector<ViewDesc> vds;
     int64_t ord_blocks = 0, all_tiles = 0;
     uint32_t points = 0;
@@ -836,7 +861,8 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         d.ext = src_ext[vw.src];
         d.keys = reinterpret_cast<uint32_t *>(W + (blocks ? 0 : o_region) + vw.o_keys);
         d.hist = reinterpret_cast<uint32_t *>(W + o_region) + vw.hist0;
-        d.a64s = reinterpret_cast<double4 *>(W + vw.o_a64s);
+        // (read only where the order is the caller's)
+        d.a64s = ordered ? reinterpret_cast<double4 *>(W + vw.o_a64s) : const_cast<double4 *>(d.src);
         d.a32s = need_a32 ? reinterpret_cast<float4 *>(W + vw.o_a32s) : nullptr;
         d.g32s = need_g32 ? reinterpret_cast<float4 *>(W + vw.o_g32s) : nullptr;
         d.bounds = reinterpret_cast<double4 *>(W + vw.o_bounds);
@@ -937,14 +963,20 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     put(b_srcs, vds.data(), sizeof(ViewDesc) * vds.size());
     put(b_srcs + b_views, segs.data(), b_segs);
     put(b_srcs + b_views + b_segs, tds.data(), b_tabs);
-    PC_HIP(hipMemcpyAsync(W + o_desc, desc.data(), desc.size(), hipMemcpyHostToDevice, st), "H2D descriptors");
+    if (desc.size() <= kPutBytes) {
+        PC_HIP(launch_zero_put(W + o_res, zero_bytes, W + o_desc, desc.data(), desc.size(), st), "zero results");
+    } else {
+        PC_HIP(hipMemcpyAsync(W + o_desc, desc.data(), desc.size(), hipMemcpyHostToDevice, st), "H2D descriptors");
+        PC_HIP(launch_zero(W + o_res, zero_bytes, st), "zero results");
+    }
     const SrcDesc *d_srcs = reinterpret_cast<const SrcDesc *>(W + o_desc);
     const ViewDesc *d_views = reinterpret_cast<const ViewDesc *>(W + o_desc + b_srcs);
-    PC_HIP(launch_zero(W + o_res, zero_bytes, st), "zero results");
     PC_HIP(launch_convert(d_srcs, static_cast<int>(sds.size()), conv_blocks, st), "convert");
-    PC_HIP(launch_order(d_views, static_cast<int>(vds.size()), ord_blocks, reinterpret_cast<uint32_t *>(W + o_region),
-                        hist_words, reinterpret_cast<uint32_t *>(W + o_sums), st),
-           "order");
+    if (ordered)
+        PC_HIP(launch_order(d_views, static_cast<int>(vds.size()), ord_blocks,
+                            reinterpret_cast<uint32_t *>(W + o_region), hist_words,
+                            reinterpret_cast<uint32_t *>(W + o_sums), st),
+               "order");
     PC_HIP(T.launch_bounds(d_views, static_cast<int>(vds.size()), all_tiles, st), "bounds");
     unsigned long long *meta = reinterpret_cast<unsigned long long *>(W + o_meta);
 
@@ -959,19 +991,15 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
             PC_HIP(T.launch_prune(d_segs, static_cast<int32_t>(segs.size()), d_tabs, prune_rows, surv,
                                 split ? sub_words : nullptr, meta, mc ? 1 : 0, split ? 1 : 0, blocks, st),
                    "prune");
-            PC_HIP(launch_add_copies(reinterpret_cast<unsigned long long *>(W + o_res) + kMetaWords,
-                                     reinterpret_cast<const unsigned long long *>(W + o_pcopies),
-                                     static_cast<int64_t>(count_words), kPruneStripes, st),
-                   "add prune counts");
+            if (!blocks)  // (the block kernel adds them itself)
+                PC_HIP(launch_add_copies(reinterpret_cast<unsigned long long *>(W + o_res) + kMetaWords,
+                                         reinterpret_cast<const unsigned long long *>(W + o_pcopies),
+                                         static_cast<int64_t>(count_words), kPruneStripes, st),
+                       "add prune counts");
         }
         int per_cu = 0;
-        int32_t max_edges = 0, max_cells = 0, bcols = 0;
         if (blocks) {
-            for (auto &t : tabs) {
-                max_edges = std::max(max_edges, static_cast<int32_t>(t->host.e64.size()));
-                max_cells = std::max(max_cells, static_cast<int32_t>(t->host.lutb.size()));
-            }
-            blk::lds_layout(max_edges, max_cells, lt.cols ? std::min(lt.cols, 16) : 16, &bcols, &max_cells, &lds_bytes);
+            lds_bytes = blocks_lds;
             PC_HIP(blk::occupancy(lds_bytes, &per_cu), "occupancy");
         } else {
             PC_HIP(T.count_occupancy(fp64, mc, compact, lds_bytes, &per_cu), "occupancy");
@@ -992,7 +1020,9 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         }
         if (blocks)
             PC_HIP(blk::launch_count(d_segs, d_tabs, surv, sub_words, meta, meta + kQueueBase, meta + 7,
-                                     meta + kPruneStatBase, max_edges, max_cells, bcols, lds_bytes, lt.chunk, t_flush_cap,
+                                     meta + kPruneStatBase, reinterpret_cast<unsigned long long *>(W + o_res) + kMetaWords,
+                                     reinterpret_cast<const unsigned long long *>(W + o_pcopies),
+                                     static_cast<int64_t>(count_words), max_edges, max_cells, bcols, lds_bytes, lt.chunk, t_flush_cap,
                                      grid, st),
                    "block kernel");
         else

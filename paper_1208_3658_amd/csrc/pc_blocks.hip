@@ -125,6 +125,9 @@ struct BParams {
     unsigned long long *queue;              // 8 zeroed counters kQueueStride words apart
     unsigned long long *rechecked;
     unsigned long long *stats;              // the statistics stripes (see k_prune)
+    unsigned long long *counts;             // all jobs' counters, count_words of them, and
+    const unsigned long long *copies;       // kPruneStripes copies with the prune pass's whole tile pairs
+    int64_t count_words;
     uint32_t flush_every;                   // items between flushes, so that no 32-bit word can wrap
     int32_t max_edges, max_cells;           // of the launch's tables: LDS layout (max_cells 0: no table)
     int32_t cols;                           // lane columns of the histogram (power of two)
@@ -403,6 +406,13 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
     const uint64_t total = ld_uniform(p.n_items);
     const uint32_t part_bits = total >= 4ull * gridDim.x ? 0u : total * 2u >= gridDim.x ? 2u : 4u;
     if (tid0 < 6) sh_stat[tid0] = 0ull;
+    for (int64_t w = static_cast<int64_t>(blockIdx.x) * kThreads + tid0; w < p.count_words;
+         w += static_cast<int64_t>(gridDim.x) * kThreads) {
+        unsigned long long v = 0;
+#pragma unroll
+        for (int s = 0; s < kPruneStripes; ++s) v += p.copies[s * p.count_words + w];
+        if (v) atomicAdd(p.counts + w, v);
+    }
     if (tid0 == 0) pend.n = 0u;
 
     for (;; ++wi) {
@@ -971,8 +981,8 @@ hipError_t occupancy(uint32_t lds_bytes, int *per_cu) {
 
 hipError_t launch_count(const SegDesc *segs, const TableDesc *tabs, const uint64_t *items, const uint64_t *tiles,
                         const unsigned long long *n_items, unsigned long long *queue, unsigned long long *rechecked,
-                        unsigned long long *stats, int32_t max_edges, int32_t max_cells, int32_t cols, uint32_t lds_bytes,
-                        int chunk, uint64_t flush_cap, int grid, hipStream_t st) {
+                        unsigned long long *stats, unsigned long long *counts, const unsigned long long *copies,
+                        int64_t count_words, int32_t max_edges, int32_t max_cells, int32_t cols, uint32_t lds_bytes, int chunk, uint64_t flush_cap, int grid, hipStream_t st) {
     BParams p;
     p.segs = segs;
     p.tabs = tabs;
@@ -982,6 +992,9 @@ hipError_t launch_count(const SegDesc *segs, const TableDesc *tabs, const uint64
     p.queue = queue;
     p.rechecked = rechecked;
     p.stats = stats;
+    p.counts = counts;
+    p.copies = copies;
+    p.count_words = count_words;
     // a word of the histogram grows by at most 512 x 512 per item
     constexpr uint64_t kCap = 0xFFFFFFFFull / (static_cast<uint64_t>(kT) * kT);
     p.flush_every = static_cast<uint32_t>(flush_cap > 0 && flush_cap < kCap ? flush_cap : kCap);

@@ -42,6 +42,13 @@ constexpr int kMaxEdges = 1024;       // theta edges per table
 // atomics on one address serialise, and every workgroup has some to add.
 constexpr int kPruneStats = 12;
 constexpr int kPruneStripes = 16;
+
+// pairs of a call up to which the block kernel takes catalogues in the caller's
+// order (see run_batch)
+constexpr double kUnorderedPairs = 16777216.0;
+
+// descriptors up to this size go to the device as a kernel's arguments
+constexpr size_t kPutBytes = 2048;
 constexpr int kPruneStripeWords = 16;
 constexpr int kPruneStatBase = 32;
 // The counting kernel's work queue: eight counters (one per XCD slice), each

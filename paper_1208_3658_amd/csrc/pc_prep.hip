@@ -9,6 +9,7 @@
 // is binned as a whole without visiting its pairs (the paper, Sec. 2.2: time
 // is saved by not computing separations outside the binned range).
 #include <algorithm>
+#include <cstring>
 
 #include "pc_internal.hpp"
 #include "pc_math.h"
@@ -369,6 +370,18 @@ __global__ void __launch_bounds__(256) k_zero_u128(uint4 *p, int64_t n4) {
         p[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
+// The same, and the descriptors of a small call by value: a copy from the host's
+// memory takes a transfer of its own (about 10 us of a call of 113 us).
+struct PutData {
+    uint4 v[kPutBytes / 16];
+};
+__global__ void __launch_bounds__(256) k_zero_put(uint4 *p, int64_t n4, uint4 *dst, int n_put, const PutData d) {
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n4;
+         i += static_cast<int64_t>(gridDim.x) * blockDim.x)
+        p[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (blockIdx.x == 0 && static_cast<int>(threadIdx.x) < n_put) dst[threadIdx.x] = d.v[threadIdx.x];
+}
+
 // Ordering counters of a view of n points (a multiple of 4; at least one per
 // face).
 uint32_t order_buckets(int64_t n, int per_point) {
@@ -390,6 +403,19 @@ hipError_t launch_zero(void *p, size_t bytes, hipStream_t st) {
     const int64_t n4 = static_cast<int64_t>(bytes / 16);
     const int64_t blocks = std::min<int64_t>((n4 + 255) / 256, 4096);
     k_zero_u128<<<dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, st>>>(static_cast<uint4 *>(p), n4);
+    return hipGetLastError();
+}
+
+// Zeroes as launch_zero does and writes `n` (at most kPutBytes) bytes at `src`,
+// host memory, to the 16-byte aligned dst, up to 15 bytes more behind them.
+hipError_t launch_zero_put(void *p, size_t bytes, void *dst, const void *src, size_t n, hipStream_t st) {
+    if (n > kPutBytes) return hipErrorInvalidValue;
+    PutData d = {};
+    if (n) memcpy(&d, src, n);
+    const int64_t n4 = static_cast<int64_t>(bytes / 16);
+    const int64_t blocks = std::min<int64_t>(std::max<int64_t>((n4 + 255) / 256, 1), 4096);
+    k_zero_put<<<dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, st>>>(
+        static_cast<uint4 *>(p), n4, static_cast<uint4 *>(dst), static_cast<int>((n + 15) / 16), d);
     return hipGetLastError();
 }
 
