@@ -85,6 +85,7 @@
 // the table's edge and the final difference add two: below A sqrt(c) + B with
 // A = 16 u (D + R), B = 64 u^2 (D + R)^2.
 #include <algorithm>
+#include <type_traits>
 
 #include "pc_internal.hpp"
 
@@ -107,6 +108,7 @@ constexpr uint32_t kColMask = (1u << kN) - 1u;
 constexpr float kNever = 1e30f;             // added to d of a pair that counts nowhere
 constexpr uint32_t kDiagBlock = 1u << 31;   // block descriptor: on the diagonal, only i < j counts
 constexpr uint32_t kTableBlock = 1u << 30;  // block descriptor: chords go through the table
+constexpr uint32_t kInRange = 1u << 28;     // with kTableBlock: every chord falls into the table's cells
 constexpr uint32_t kNearBlock = 1u << 29;   // with kTableBlock: chords from differences
 // Edges from which a whole block goes through the table: one edge costs a block
 // the same half add and minimum per pair, the table nine instructions and two
@@ -357,8 +359,9 @@ struct ChordTable {
     uint32_t row_shift;
     float lo, hi;               // cells' range
 };
+template <bool CLAMP>
 __device__ __forceinline__ u32x2 cell_of(const ChordTable &t, float c) {
-    const uint32_t key = __float_as_uint(__builtin_amdgcn_fmed3f(c, t.lo, t.hi));
+    const uint32_t key = __float_as_uint(CLAMP ? __builtin_amdgcn_fmed3f(c, t.lo, t.hi) : c);
     return *(LdsCell *)(uintptr_t)(((key >> t.shift) << 3) + t.base);
 }
 // the byte offset of the row of a chord that differs from its cell's edge by x
@@ -573,7 +576,8 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
             const uint32_t m = np ? b - a : 0u;
             const bool near = has_table && lo * lo < E_t * pow2(27u - tbl.shift);
             const bool by_table = m && (near || (m >= kTableEdges && has_table && np == kG * kG && !on_diag));
-            blk[cbj * kN + cbi] = m ? a | (m << 16) | (on_diag ? kDiagBlock : 0u) | (by_table ? kTableBlock : 0u) | (near ? kNearBlock : 0u) : 0u;
+            const bool in_range = lo * lo * (1.0f - 0x1p-18f) - E_t > tbl.lo && hi * hi * (1.0f + 0x1p-18f) + E_t < tbl.hi;
+            blk[cbj * kN + cbi] = m ? a | (m << 16) | (on_diag ? kDiagBlock : 0u) | (by_table ? kTableBlock : 0u) | (near ? kNearBlock : 0u) | (by_table && in_range ? kInRange : 0u) : 0u;
             if (np && !by_table) add_row(h, K0 + a, np);
             const uint64_t any = __builtin_amdgcn_ballot_w64(m != 0u);
             const bool full = !diag && i_lim == kT && j_lim == kT && part_bits != 4;
@@ -655,13 +659,13 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
                 }
             };
             // of the lane's pairs s0 .. s0 + kLook - 1, counted at `at`, those of hits
-            auto send_rows = [&](uint32_t hits, const uint32_t (&at)[kLook], int bi, int s0) {
+            auto send_rows = [&](uint32_t hits, const auto &at, int bi, int s0) {
                 seen += __popc(hits);
                 for (; hits; hits &= hits - 1u) {
                     const int v = __builtin_ctz(hits);
                     uint32_t o = at[0];
 #pragma unroll
-                    for (int w = 1; w < kLook; ++w) {
+                    for (int w = 1; w < static_cast<int>(sizeof(at) / sizeof(at[0])); ++w) {
                         asm("" : "+v"(o));  // no indexed array: it would be written to scratch on every pass
                         o = v == w ? at[w] : o;
                     }
@@ -761,7 +765,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
                                 const float dx = fmaf(-0.5f, a.x, px[v >> 2]), dy = fmaf(-0.5f, a.y, py[v >> 2]),
                                             dz = fmaf(-0.5f, a.z, pz[v >> 2]);
                                 x[v] = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-                                e[v] = cell_of(tbl, x[v]);
+                                e[v] = cell_of<true>(tbl, x[v]);
                             }
 #pragma unroll
                             for (int v = 0; v < 8; ++v) {
@@ -778,31 +782,37 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
                     const float H0 = threshold(k0);
                     const float top = uni_f(static_cast<float>(static_cast<double>(H0) + D2));  // c = top - d
                     block_products(As, bi, B, H0, D);
+                    auto look_up = [&](auto clamp) {
 #pragma unroll
-                    for (int q = 0; q < 16; q += kLook) {
-                        float c[kLook];
-                        u32x2 e[kLook];
-                        uint32_t at[kLook];
-                        float least = INFINITY;
+                        for (int q = 0; q < 16; q += kLook) {
+                            float c[kLook];
+                            u32x2 e[kLook];
+                            uint32_t at[kLook];
+                            float least = INFINITY;
 #pragma unroll
-                        for (int v = 0; v < kLook; ++v) {
-                            c[v] = top - D.d[(q + v) >> 2][v & 3];
-                            e[v] = cell_of(tbl, c[v]);
+                            for (int v = 0; v < kLook; ++v) {
+                                c[v] = top - D.d[(q + v) >> 2][v & 3];
+                                e[v] = cell_of<decltype(clamp)::value>(tbl, c[v]);
+                            }
+#pragma unroll
+                            for (int v = 0; v < kLook; ++v) {
+                                c[v] = __uint_as_float(e[v].x) - c[v];
+                                at[v] = row_offset(tbl, e[v], c[v]);
+                                add_offset(at[v] + column, 1u);
+                                least = fminf(least, fabsf(c[v]));
+                            }
+                            if (__builtin_expect(__builtin_amdgcn_ballot_w64(least <= E_t) != 0, 0)) {
+                                uint32_t hits = 0;
+#pragma unroll
+                                for (int v = 0; v < kLook; ++v) hits |= fabsf(c[v]) <= E_t ? 1u << v : 0u;
+                                send_rows(hits, at, bi, q);
+                            }
                         }
-#pragma unroll
-                        for (int v = 0; v < kLook; ++v) {
-                            c[v] = __uint_as_float(e[v].x) - c[v];
-                            at[v] = row_offset(tbl, e[v], c[v]);
-                            add_offset(at[v] + column, 1u);
-                            least = fminf(least, fabsf(c[v]));
-                        }
-                        if (__builtin_expect(__builtin_amdgcn_ballot_w64(least <= E_t) != 0, 0)) {
-                            uint32_t hits = 0;
-#pragma unroll
-                            for (int v = 0; v < kLook; ++v) hits |= fabsf(c[v]) <= E_t ? 1u << v : 0u;
-                            send_rows(hits, at, bi, q);
-                        }
-                    }
+                    };
+                    // (without the clamp 131 instructions a block instead of 151: 1.61 / 1.66 ms
+                    // for 300,000 x 400,000 points, 13.5 / 13.8 ms for 64 mocks)
+                    if (key & kInRange) look_up(std::false_type());
+                    else look_up(std::true_type());
                     continue;
                 }
                 const float H0 = threshold(k0);
