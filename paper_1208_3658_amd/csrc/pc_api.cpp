@@ -54,8 +54,8 @@ namespace blk {
 hipError_t launch_bounds(const ViewDesc *views, int n_views, int64_t tiles, hipStream_t st);
 void lds_layout(int32_t max_edges, int32_t max_cells, int32_t cols, int32_t *cols_out, int32_t *cells_out,
                 uint32_t *lds_bytes);
-hipError_t occupancy(uint32_t lds_bytes, int *per_cu);
-hipError_t launch_count(const SegDesc *segs, const TableDesc *tabs, const uint64_t *items, const uint64_t *tiles,
+hipError_t occupancy(bool global_table, uint32_t lds_bytes, int *per_cu);
+hipError_t launch_count(bool global_table, const SegDesc *segs, const TableDesc *tabs, const uint64_t *items, const uint64_t *tiles,
                         const unsigned long long *n_items, unsigned long long *queue, unsigned long long *rechecked,
                         unsigned long long *stats, unsigned long long *counts, const unsigned long long *copies,
                         int64_t count_words, int32_t max_edges, int32_t max_cells, int32_t cols, uint32_t lds_bytes, int chunk, uint64_t flush_cap, int grid, hipStream_t st);
@@ -818,6 +818,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     // LDS of the block kernel, and whether every edge set's chord table is in it
     int32_t max_edges = 0, max_cells = 0, bcols = 0;
     uint32_t blocks_lds = 0;
+    bool global_table = false;
     bool ordered = !blocks;
     if (blocks) {
         bool all = true;
@@ -826,6 +827,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
             max_cells = std::max(max_cells, static_cast<int32_t>(t->host.lutb.size()));
             all = all && !t->host.lutb.empty();
         }
+        const bool any = max_cells > 0;
         blk::lds_layout(max_edges, max_cells, lt.cols ? std::min(lt.cols, 16) : 16, &bcols, &max_cells, &blocks_lds);
         // Few pairs are counted in the caller's order: unordered groups prune
         // nothing and put every block through the chord table (hence only with
@@ -834,6 +836,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         // points, 111 / 95 of 4096, 123 / 110 of 6000; 122 / 108 for 4096 x 4096,
         // 156 / 144 for 8192 x 8192 in bins of all scales, but 131 / 136 where the
         // bins end at 2 degrees and the order lets most pairs go.
+        global_table = any && max_cells == 0;
         ordered = !all || max_cells == 0;
         double pairs = 0.0;
         for (const SegDesc &sd : segs) pairs += static_cast<double>(sd.ni) * static_cast<double>(sd.nj) * (sd.tri ? 0.5 : 1.0);
@@ -1000,7 +1003,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         int per_cu = 0;
         if (blocks) {
             lds_bytes = blocks_lds;
-            PC_HIP(blk::occupancy(lds_bytes, &per_cu), "occupancy");
+            PC_HIP(blk::occupancy(global_table, lds_bytes, &per_cu), "occupancy");
         } else {
             PC_HIP(T.count_occupancy(fp64, mc, compact, lds_bytes, &per_cu), "occupancy");
         }
@@ -1019,7 +1022,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
             PC_HIP(hipEventRecord(t_ev0, st), "hipEventRecord");
         }
         if (blocks)
-            PC_HIP(blk::launch_count(d_segs, d_tabs, surv, sub_words, meta, meta + kQueueBase, meta + 7,
+            PC_HIP(blk::launch_count(global_table, d_segs, d_tabs, surv, sub_words, meta, meta + kQueueBase, meta + 7,
                                      meta + kPruneStatBase, reinterpret_cast<unsigned long long *>(W + o_res) + kMetaWords,
                                      reinterpret_cast<const unsigned long long *>(W + o_pcopies),
                                      static_cast<int64_t>(count_words), max_edges, max_cells, bcols, lds_bytes, lt.chunk, t_flush_cap,

@@ -116,6 +116,11 @@ constexpr uint32_t kNearBlock = 1u << 29;   // with kTableBlock: chords from dif
 // 3 / 4 / 5 / 6: 1.63 / 1.68 / 1.67 / 1.77 ms for 300,000 x 400,000 points, 13.8 / 14.0 /
 // 14.6 / 15.1 ms for 64 mocks, 22.5 / 22.6 / 22.7 / 23.0 ms on the 1M workload.
 constexpr uint32_t kTableEdges = 3;
+// The same with the table in global memory: large edge sets, whose histogram has
+// one or two lane columns for 64 lanes' adds.  1M x 1M points in 254 bins with the
+// line at 4 / 5 / 6 / 8 / 10: 115.2 / 105.3 / 103.0 / 102.8 / 103.9 ms, without the table
+// 127 ms (tiles next to each other have tens of edges a block).
+constexpr uint32_t kTableEdgesG = 8;
 constexpr uint32_t kOnes = 0x3F803F80u;     // two bf16 ones
 
 struct BParams {
@@ -345,8 +350,9 @@ __device__ __forceinline__ void block_products(const u32x4 (*As)[kWave], int bi,
     D.d[3] = product(a1, B[1], C);
 }
 
-// The edge set's chord table in LDS (8 bytes a cell: the edge, and the row below
-// it as its byte offset in the histogram, row << row_shift).
+// The edge set's chord table (8 bytes a cell: the edge, the row below it): in
+// LDS, or with GT in global memory, where the lookups of a block, a few adjacent
+// cells, come from the nearest cache.
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 using LdsU = __attribute__((address_space(3))) uint32_t;
 using LdsCell = const __attribute__((address_space(3))) u32x2;
@@ -354,24 +360,27 @@ __device__ __forceinline__ uint32_t lds_addr(const void *p) {
     return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void *)(p)));
 }
 struct ChordTable {
-    uint32_t base;              // LDS address of cell 0, less 8 key0
+    const unsigned char *cells; // GT: cell 0
+    uint32_t base;              // otherwise its LDS address, less 8 key0
     uint32_t shift, key0;
-    uint32_t row_shift;
+    uint32_t row_shift;         // a row's bytes in the histogram, as a power of two
     float lo, hi;               // cells' range
 };
-template <bool CLAMP>
+template <bool GT, bool CLAMP>
 __device__ __forceinline__ u32x2 cell_of(const ChordTable &t, float c) {
     const uint32_t key = __float_as_uint(CLAMP ? __builtin_amdgcn_fmed3f(c, t.lo, t.hi) : c);
+    if (GT) return *reinterpret_cast<const u32x2 *>(t.cells + static_cast<uint32_t>((key >> t.shift) - t.key0) * 8u);
     return *(LdsCell *)(uintptr_t)(((key >> t.shift) << 3) + t.base);
 }
 // the byte offset of the row of a chord that differs from its cell's edge by x
 __device__ __forceinline__ uint32_t row_offset(const ChordTable &t, u32x2 e, float x) {
-    return ((__float_as_uint(x) >> 31) << t.row_shift) + e.y;
+    return ((__float_as_uint(x) >> 31) + e.y) << t.row_shift;
 }
 __device__ __forceinline__ void add_offset(uint32_t lds, uint32_t n) {
     __hip_atomic_fetch_add((LdsU *)(uintptr_t)lds, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+template <bool GT>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) k_count_blocks(BParams p) {
     extern __shared__ __align__(16) unsigned char lds[];
     __shared__ u32x4 As[kT / 16][kWave];      // 16 rows x 4 lane groups per set
@@ -389,6 +398,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
     h.T = reinterpret_cast<uint32_t *>(lds + 8 * (p.max_edges + p.max_cells));
     h.cols = p.cols;
     h.n_edges = 0;
+    tbl.cells = nullptr;
     tbl.base = tbl.shift = tbl.key0 = 0;
     tbl.row_shift = 2u + static_cast<uint32_t>(__builtin_ctz(static_cast<uint32_t>(p.cols)));
     tbl.lo = tbl.hi = 0.0f;
@@ -515,7 +525,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
                 const double *e64 = ld_uniform(&td->e64);
                 const uint2 *src = reinterpret_cast<const uint2 *>(ld_uniform(&td->lutb));
                 const int n_cells = ld_uniform(&td->b_cells);
-                has_table = n_cells > 0 && n_cells <= p.max_cells;
+                has_table = n_cells > 0 && (GT || n_cells <= p.max_cells);
                 tbl.shift = ld_uniform(&td->b_shift);
                 tbl.key0 = ld_uniform(&td->b_key0);
                 tbl.base = lds_addr(cells) - 8u * tbl.key0;
@@ -523,11 +533,9 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
                 tbl.hi = __uint_as_float(((tbl.key0 + static_cast<uint32_t>(n_cells)) << tbl.shift) - 1u);
                 __syncthreads();
                 for (int k = tid; k < h.n_edges; k += kThreads) e_lds[k] = e64[k];
-                if (has_table)
-                    for (int k = tid; k < n_cells; k += kThreads) {
-                        const uint2 e = src[k];
-                        cells[k] = make_uint2(e.x, e.y << tbl.row_shift);
-                    }
+                if (GT) tbl.cells = reinterpret_cast<const unsigned char *>(src);
+                else if (has_table)
+                    for (int k = tid; k < n_cells; k += kThreads) cells[k] = src[k];
                 clear_hist(h);
                 cur_tab = tab;
             }
@@ -575,7 +583,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
             if (part_bits == 4 && cbj != static_cast<int>(part)) np = 0u;
             const uint32_t m = np ? b - a : 0u;
             const bool near = has_table && lo * lo < E_t * pow2(27u - tbl.shift);
-            const bool by_table = m && (near || (m >= kTableEdges && has_table && np == kG * kG && !on_diag));
+            const bool by_table = m && (near || (m >= (GT ? kTableEdgesG : kTableEdges) && has_table && np == kG * kG && !on_diag));
             const bool in_range = lo * lo * (1.0f - 0x1p-18f) - E_t > tbl.lo && hi * hi * (1.0f + 0x1p-18f) + E_t < tbl.hi;
             blk[cbj * kN + cbi] = m ? a | (m << 16) | (on_diag ? kDiagBlock : 0u) | (by_table ? kTableBlock : 0u) | (near ? kNearBlock : 0u) | (by_table && in_range ? kInRange : 0u) : 0u;
             if (np && !by_table) add_row(h, K0 + a, np);
@@ -765,7 +773,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
                                 const float dx = fmaf(-0.5f, a.x, px[v >> 2]), dy = fmaf(-0.5f, a.y, py[v >> 2]),
                                             dz = fmaf(-0.5f, a.z, pz[v >> 2]);
                                 x[v] = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-                                e[v] = cell_of<true>(tbl, x[v]);
+                                e[v] = cell_of<GT, true>(tbl, x[v]);
                             }
 #pragma unroll
                             for (int v = 0; v < 8; ++v) {
@@ -792,7 +800,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
 #pragma unroll
                             for (int v = 0; v < kLook; ++v) {
                                 c[v] = top - D.d[(q + v) >> 2][v & 3];
-                                e[v] = cell_of<decltype(clamp)::value>(tbl, c[v]);
+                                e[v] = cell_of<GT, decltype(clamp)::value>(tbl, c[v]);
                             }
 #pragma unroll
                             for (int v = 0; v < kLook; ++v) {
@@ -973,23 +981,26 @@ void lds_layout(int32_t max_edges, int32_t max_cells, int32_t cols, int32_t *col
     auto bytes = [&](int32_t c, int32_t cells) { return static_cast<uint32_t>(8 * (max_edges + cells) + 4 * ((max_edges + 1) * c + max_edges)); };
     static const uint32_t fixed = [] {
         hipFuncAttributes a;
-        return hipFuncGetAttributes(&a, reinterpret_cast<const void *>(k_count_blocks)) == hipSuccess
+        return hipFuncGetAttributes(&a, reinterpret_cast<const void *>(k_count_blocks<false>)) == hipSuccess
                    ? static_cast<uint32_t>(a.sharedSizeBytes) : 36u * 1024u;
     }();
     const uint32_t room = 40u * 1024u - std::min(fixed, 40u * 1024u);
     int32_t c = 1;
-    while (c < cols && bytes(2 * c, max_cells) <= room) c *= 2;
     if (bytes(c, max_cells) > room) max_cells = 0;
+    while (c < cols && bytes(2 * c, max_cells) <= room) c *= 2;
     *cols_out = c;
     *cells_out = max_cells;
     *lds_bytes = bytes(c, max_cells);
 }
 
-hipError_t occupancy(uint32_t lds_bytes, int *per_cu) {
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_count_blocks, kThreads, lds_bytes);
+// (global_table: the sets' chord tables do not fit into LDS at four workgroups a
+// CU; three workgroups with them took 115 ms where this takes 103)
+hipError_t occupancy(bool global_table, uint32_t lds_bytes, int *per_cu) {
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        per_cu, global_table ? k_count_blocks<true> : k_count_blocks<false>, kThreads, lds_bytes);
 }
 
-hipError_t launch_count(const SegDesc *segs, const TableDesc *tabs, const uint64_t *items, const uint64_t *tiles,
+hipError_t launch_count(bool global_table, const SegDesc *segs, const TableDesc *tabs, const uint64_t *items, const uint64_t *tiles,
                         const unsigned long long *n_items, unsigned long long *queue, unsigned long long *rechecked,
                         unsigned long long *stats, unsigned long long *counts, const unsigned long long *copies,
                         int64_t count_words, int32_t max_edges, int32_t max_cells, int32_t cols, uint32_t lds_bytes, int chunk, uint64_t flush_cap, int grid, hipStream_t st) {
@@ -1012,7 +1023,8 @@ hipError_t launch_count(const SegDesc *segs, const TableDesc *tabs, const uint64
     p.max_cells = max_cells;
     p.cols = cols;
     p.chunk = chunk;
-    k_count_blocks<<<dim3(grid), dim3(kThreads), lds_bytes, st>>>(p);
+    if (global_table) k_count_blocks<true><<<dim3(grid), dim3(kThreads), lds_bytes, st>>>(p);
+    else k_count_blocks<false><<<dim3(grid), dim3(kThreads), lds_bytes, st>>>(p);
     return hipGetLastError();
 }
 
