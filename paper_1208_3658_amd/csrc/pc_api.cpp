@@ -54,8 +54,8 @@ namespace blk {
 hipError_t launch_bounds(const ViewDesc *views, int n_views, int64_t tiles, hipStream_t st);
 void lds_layout(int32_t max_edges, int32_t max_cells, int32_t cols, int32_t *cols_out, int32_t *cells_out,
                 uint32_t *lds_bytes);
-hipError_t occupancy(bool global_table, uint32_t lds_bytes, int *per_cu);
-hipError_t launch_count(bool global_table, const SegDesc *segs, const TableDesc *tabs, const uint64_t *items, const uint64_t *tiles,
+hipError_t occupancy(bool fp64, bool global_table, uint32_t lds_bytes, int *per_cu);
+hipError_t launch_count(bool fp64, bool global_table, const SegDesc *segs, const TableDesc *tabs, const uint64_t *items, const uint64_t *tiles,
                         const unsigned long long *n_items, unsigned long long *queue, unsigned long long *rechecked,
                         unsigned long long *stats, unsigned long long *counts, const unsigned long long *copies,
                         int64_t count_words, int32_t max_edges, int32_t max_cells, int32_t cols, uint32_t lds_bytes, int chunk, uint64_t flush_cap, int grid, hipStream_t st);
@@ -287,6 +287,10 @@ TableDesc table_desc(const DevTable &t, bool fp64) {
     const HostTable &h = t.host;
     d.e64 = t.d_e64;
     d.n_edges = static_cast<int32_t>(h.e64.size());
+    d.lutb = t.d_lutb;
+    d.b_shift = h.b_shift;
+    d.b_key0 = h.b_key0;
+    d.b_cells = static_cast<int32_t>(h.lutb.size());
     if (fp64) {
         d.cols = h.cols64;
         d.lut = t.d_lut64;
@@ -310,10 +314,6 @@ TableDesc table_desc(const DevTable &t, bool fp64) {
         d.band_g = t.d_band_g;
         d.fband = t.d_fband;
         d.fband_g = t.d_fband_g;
-        d.lutb = t.d_lutb;
-        d.b_shift = h.b_shift;
-        d.b_key0 = h.b_key0;
-        d.b_cells = static_cast<int32_t>(h.lutb.size());
     }
     return d;
 }
@@ -441,7 +441,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     // the block kernel runs the mixed mode's pruned launches.  The vector
     // kernels stay for 128-point tiles, for visiting every pair, for
     // PC_MATRIX_CORES and for binary64.
-    const bool blocks = prune && !fp64 && !mc && lt.tile != 128 && !lt.vector;
+    const bool blocks = prune && !mc && lt.tile != 128 && !lt.vector;
     const TileOps &T = blocks ? kTileBlocks : lt.tile == 128 ? kTile128 : kTile256;
     const int tile = T.tile;
     // host-side validation first, so bad arguments are reported as such
@@ -557,7 +557,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
             if (need_a32) v.o_a32s = ar.take(sizeof(float4) * static_cast<size_t>(n + kJPad));
             if (need_g32) v.o_g32s = ar.take(sizeof(float4) * static_cast<size_t>(n + kJPad));
             v.o_bounds = ar.take(sizeof(double4) * static_cast<size_t>(n_tiles(n, tile) * (1 + T.subs)));
-            if (blocks) v.o_keys = ar.take(sizeof(uint32_t) * static_cast<size_t>(n));
+            if (blocks && !fp64) v.o_keys = ar.take(sizeof(uint32_t) * static_cast<size_t>(n));
             if (blocks) v.o_groups = ar.take(sizeof(float4) * static_cast<size_t>(n_tiles(n, tile) * kGroups));
         }
         const int id = static_cast<int>(views.size());
@@ -712,7 +712,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     // split survivors: the prune pass looks at the j-tile's sub-blocks too
     // (mixed mode); their descriptions sit beside the survivors
     // (block kernel: the survivors' tiles do)
-    const bool split = PC_SPLIT && prune && !fp64;
+    const bool split = prune && (blocks || (PC_SPLIT && !fp64));
     // the ordering's counters (and keys, where the ordered copies take more
     // room) are done with when the prune pass writes the survivors: one region
     // holds the one, then the other
@@ -726,15 +726,15 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     }
     order_bytes = sizeof(uint32_t) * static_cast<size_t>(hist_words);
     for (View &v : views) {
-        if (v.resident_full || v.e <= v.b || blocks) continue;
+        if (v.resident_full || v.e <= v.b || (blocks && !fp64)) continue;
         v.o_keys = order_bytes;  // from the region's start
         order_bytes += sizeof(uint32_t) * static_cast<size_t>((v.e - v.b + 63) & ~int64_t(63));
     }
-    // (16 bytes per pair of 256-point tiles also where the block kernel's larger
-    // tiles leave a quarter of them)
-    const size_t surv_bytes = sizeof(uint64_t) * std::max<uint64_t>(prune ? std::max(items, limit_items) : 1, 1);
-    const size_t o_region =
-        ar.take(std::max(order_bytes, surv_bytes + (split ? sizeof(uint64_t) * std::max<uint64_t>(std::max(items, limit_items), 1) : 0)));
+    // (mixed mode: 16 bytes per pair of 256-point tiles also where the block
+    // kernel's larger tiles leave a quarter of them)
+    const uint64_t slots = std::max<uint64_t>(prune ? (blocks && fp64 ? items : std::max(items, limit_items)) : 1, 1);
+    const size_t surv_bytes = sizeof(uint64_t) * slots;
+    const size_t o_region = ar.take(std::max(order_bytes, surv_bytes * (split ? 2 : 1)));
     const size_t o_surv = o_region, o_sub = o_region + surv_bytes;
     const size_t zero_bytes = (o_region - o_res + sizeof(uint32_t) * static_cast<size_t>(hist_words) + 15) & ~size_t(15);
     const size_t o_sums = ar.take(sizeof(uint32_t) * std::max<size_t>(scan_sums_words(hist_words), 4));
@@ -862,7 +862,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         ViewDesc d;
         d.src = src_a64[vw.src] + vw.b;
         d.ext = src_ext[vw.src];
-        d.keys = reinterpret_cast<uint32_t *>(W + (blocks ? 0 : o_region) + vw.o_keys);
+        d.keys = reinterpret_cast<uint32_t *>(W + (blocks && !fp64 ? 0 : o_region) + vw.o_keys);
         d.hist = reinterpret_cast<uint32_t *>(W + o_region) + vw.hist0;
         // (read only where the order is the caller's)
         d.a64s = ordered ? reinterpret_cast<double4 *>(W + vw.o_a64s) : const_cast<double4 *>(d.src);
@@ -1003,7 +1003,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         int per_cu = 0;
         if (blocks) {
             lds_bytes = blocks_lds;
-            PC_HIP(blk::occupancy(global_table, lds_bytes, &per_cu), "occupancy");
+            PC_HIP(blk::occupancy(fp64, global_table, lds_bytes, &per_cu), "occupancy");
         } else {
             PC_HIP(T.count_occupancy(fp64, mc, compact, lds_bytes, &per_cu), "occupancy");
         }
@@ -1022,7 +1022,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
             PC_HIP(hipEventRecord(t_ev0, st), "hipEventRecord");
         }
         if (blocks)
-            PC_HIP(blk::launch_count(global_table, d_segs, d_tabs, surv, sub_words, meta, meta + kQueueBase, meta + 7,
+            PC_HIP(blk::launch_count(fp64, global_table, d_segs, d_tabs, surv, sub_words, meta, meta + kQueueBase, meta + 7,
                                      meta + kPruneStatBase, reinterpret_cast<unsigned long long *>(W + o_res) + kMetaWords,
                                      reinterpret_cast<const unsigned long long *>(W + o_pcopies),
                                      static_cast<int64_t>(count_words), max_edges, max_cells, bcols, lds_bytes, lt.chunk, t_flush_cap,

@@ -121,6 +121,7 @@ constexpr uint32_t kTableEdges = 3;
 // line at 4 / 5 / 6 / 8 / 10: 115.2 / 105.3 / 103.0 / 102.8 / 103.9 ms, without the table
 // 127 ms (tiles next to each other have tens of edges a block).
 constexpr uint32_t kTableEdgesG = 8;
+constexpr uint32_t kTableEdges64 = 5;
 constexpr uint32_t kOnes = 0x3F803F80u;     // two bf16 ones
 
 struct BParams {
@@ -380,10 +381,11 @@ __device__ __forceinline__ void add_offset(uint32_t lds, uint32_t n) {
     __hip_atomic_fetch_add((LdsU *)(uintptr_t)lds, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-template <bool GT>
+template <bool GT, bool F64>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) k_count_blocks(BParams p) {
     extern __shared__ __align__(16) unsigned char lds[];
-    __shared__ u32x4 As[kT / 16][kWave];      // 16 rows x 4 lane groups per set
+    __shared__ u32x4 As[F64 ? 1 : kT / 16][kWave];  // 16 rows x 4 lane groups per set
+    __shared__ double Ai[3][F64 ? kT : 1];    // F64: the i-tile's coordinates
     __shared__ uint32_t blk[kThreads];        // open blocks: k0 - K0 | m << 16 | flags; 0: nothing to do
     __shared__ Pending pend;
     __shared__ uint64_t sh_next[2];
@@ -484,14 +486,17 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
         // what the item reads: its i-points (kept while the i-tile stays), the
         // wave's first column of j-points, the bounds
         const float4 *jg = ld_uniform(&sp->jg) + jbeg;
-        float4 gi[kPer];
-        {
+        float4 gi[kPer], gj[2];
+        double4 di[kPer];
+        if constexpr (F64) {
+#pragma unroll
+            for (int r = 0; r < kPer; ++r) di[r] = (ld_uniform(&sp->i64) + ibeg)[min(r * kThreads + tid, i_lim - 1)];
+        } else {
 #pragma unroll
             for (int r = 0; r < kPer; ++r) gi[r] = (ld_uniform(&sp->ig) + ibeg)[min(r * kThreads + tid, i_lim - 1)];
-        }
-        float4 gj[2];
 #pragma unroll
-        for (int c = 0; c < 2; ++c) gj[c] = jg[min(first_col * kG + 16 * c + (lane & 15), j_lim - 1)];
+            for (int c = 0; c < 2; ++c) gj[c] = jg[min(first_col * kG + 16 * c + (lane & 15), j_lim - 1)];
+        }
         const int cbi = lane & (kN - 1), cbj = wave * (kWave / kN) + lane / kN;  // the block this lane classifies
         const float4 si = (ld_uniform(&sp->ib32) + static_cast<int64_t>(t) * kN)[cbi];
         const float4 sj = (ld_uniform(&sp->jb32) + static_cast<int64_t>(u) * kN)[cbj];
@@ -550,6 +555,12 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
 #pragma unroll
         for (int r = 0; r < kPer; ++r) {
             const int i = r * kThreads + tid;
+            if constexpr (F64) {
+                Ai[0][i] = di[r].x;
+                Ai[1][i] = di[r].y;
+                Ai[2][i] = di[r].z;
+                continue;
+            }
             u32x4 *const at = &As[i >> 4][i & 15];
             if (new_i) {
                 at[0] = slots_i(gi[r].x);
@@ -582,8 +593,8 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
             if (diag && cbi >= cbj) np = on_diag ? static_cast<uint32_t>(ni * (ni - 1) / 2) : 0u;
             if (part_bits == 4 && cbj != static_cast<int>(part)) np = 0u;
             const uint32_t m = np ? b - a : 0u;
-            const bool near = has_table && lo * lo < E_t * pow2(27u - tbl.shift);
-            const bool by_table = m && (near || (m >= (GT ? kTableEdgesG : kTableEdges) && has_table && np == kG * kG && !on_diag));
+            const bool near = !F64 && has_table && lo * lo < E_t * pow2(27u - tbl.shift);
+            const bool by_table = m && (near || (F64 ? m >= kTableEdges64 && has_table : m >= (GT ? kTableEdgesG : kTableEdges) && has_table && np == kG * kG && !on_diag));
             const bool in_range = lo * lo * (1.0f - 0x1p-18f) - E_t > tbl.lo && hi * hi * (1.0f + 0x1p-18f) + E_t < tbl.hi;
             blk[cbj * kN + cbi] = m ? a | (m << 16) | (on_diag ? kDiagBlock : 0u) | (by_table ? kTableBlock : 0u) | (near ? kNearBlock : 0u) | (by_table && in_range ? kInRange : 0u) : 0u;
             if (np && !by_table) add_row(h, K0 + a, np);
@@ -611,6 +622,14 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
             if (k < kWave) return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(h_lane), static_cast<int>(k)));
             return uni_f(static_cast<float>(e_lds[K0 + k] + h_off));
         };
+        const double e_lane = F64 ? e_lds[min(K0 + static_cast<uint32_t>(lane), static_cast<uint32_t>(h.n_edges - 1))] : 0.0;
+        auto edge = [&](uint32_t k) {  // F64: edge K0 + k
+            const uint64_t bits = __double_as_longlong(e_lane);
+            if (k < kWave)
+                return __hiloint2double(__builtin_amdgcn_readlane(static_cast<int>(bits >> 32), static_cast<int>(k)),
+                                        __builtin_amdgcn_readlane(static_cast<int>(bits), static_cast<int>(k)));
+            return __longlong_as_double(static_cast<long long>(uni64(static_cast<uint64_t>(__double_as_longlong(e_lds[K0 + k])))));
+        };
         uint32_t cnt = 0u;         // lane k: the wave's pairs above edge K0 + k
         const uint32_t column = lds_addr(h.T) + 4u * static_cast<uint32_t>(tid & (h.cols - 1));
         auto add_above = [&](uint32_t k, uint32_t pairs) {
@@ -636,6 +655,92 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
         for (int cb = first_col; cb < kN; cb += part_bits == 0 ? kWaves : kN) {
             const uint32_t desc = blk[cb * kN + (lane & (kN - 1))];
             uint32_t open = ballot32(desc != 0u) & rows;
+            if constexpr (F64) {
+                // lane (li, lj) holds the block's pairs (li + 8 a, lj + 8 b)
+                const int li = lane & 7, lj = lane >> 3;
+                double jx[4], jy[4], jz[4];
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const double4 q = (ld_uniform(&sp->j64) + jbeg)[min(cb * kG + lj + 8 * b, j_lim - 1)];
+                    jx[b] = q.x;
+                    jy[b] = q.y;
+                    jz[b] = q.z;
+                }
+                while (open) {
+                    const int bi = __builtin_ctz(open);
+                    open &= open - 1u;
+                    const uint32_t key = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(desc), bi));
+                    const uint32_t k0 = key & 0xFFFFu, m = (key >> 16) & 0xFFFu;
+                    double c[16];
+                    {
+#pragma clang fp contract(off)
+#pragma unroll
+                        for (int a = 0; a < 4; ++a) {
+                            const int i = bi * kG + li + 8 * a;
+                            const double x = Ai[0][i], y = Ai[1][i], z = Ai[2][i];
+#pragma unroll
+                            for (int b = 0; b < 4; ++b) {
+                                const double dx = x - jx[b], dy = y - jy[b], dz = z - jz[b];
+                                double v = dx * dx;
+                                v = v + dy * dy;
+                                c[4 * a + b] = v + dz * dz;
+                            }
+                        }
+                    }
+                    if ((key & kDiagBlock) || (bi + 1) * kG > i_lim || (cb + 1) * kG > j_lim) {
+                        // pairs that are none lie below every edge
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) {
+                            const int i = bi * kG + li + 8 * (v >> 2), j = cb * kG + lj + 8 * (v & 3);
+                            if (i >= i_lim || j >= j_lim || ((key & kDiagBlock) && i >= j)) c[v] = -1.0;
+                        }
+                    }
+                    if (key & kTableBlock) {
+#pragma unroll
+                        for (int q = 0; q < 16; q += kLook) {
+                            u32x2 e[kLook];
+                            float x[kLook];
+                            uint32_t at[kLook];
+                            float least = INFINITY;
+#pragma unroll
+                            for (int v = 0; v < kLook; ++v) {
+                                x[v] = static_cast<float>(c[q + v]);
+                                e[v] = cell_of<GT, true>(tbl, x[v]);
+                            }
+#pragma unroll
+                            for (int v = 0; v < kLook; ++v) {
+                                const float d = __uint_as_float(e[v].x) - x[v];
+                                at[v] = row_offset(tbl, e[v], d);
+                                add_offset(at[v] + column, c[q + v] >= 0.0 ? 1u : 0u);
+                                // x and the edge are rounded to binary32: within 2^-22 x the chord itself decides
+                                least = fminf(least, fmaf(-0x1p-22f, x[v], fabsf(d)));
+                            }
+                            if (__builtin_amdgcn_ballot_w64(least <= 0x1p-120f) != 0) {
+#pragma unroll
+                                for (int v = 0; v < kLook; ++v) {
+                                    const float d = __uint_as_float(e[v].x) - x[v];
+                                    if (fmaf(-0x1p-22f, x[v], fabsf(d)) <= 0x1p-120f && c[q + v] >= 0.0) {
+                                        const uint32_t row = (e[v].y + (c[q + v] >= e_lds[e[v].y] ? 1u : 0u)) << tbl.row_shift;
+                                        if (row != at[v]) {
+                                            add_offset(row + column, 1u);
+                                            add_offset(at[v] + column, 0xFFFFFFFFu);
+                                        }
+                                    }
+                                }
+                            }
+                        }
+                        continue;
+                    }
+                    for (uint32_t r = 0; r < m; ++r) {
+                        const double e = edge(k0 + r);
+                        uint32_t pairs = 0;
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) pairs += static_cast<uint32_t>(__builtin_popcountll(__builtin_amdgcn_ballot_w64(c[v] >= e)));
+                        add_above(k0 + r, pairs);
+                    }
+                }
+                continue;
+            }
             // the column's j-points as the product reads them
             u32x4 B[2];
 #pragma unroll
@@ -941,7 +1046,7 @@ __global__ void __launch_bounds__(kThreads) k_block_bounds(const ViewDesc *__res
 #pragma unroll
     for (int r = 0; r < kPer; ++r) {
         const double ex = p[r].x - cx, ey = p[r].y - cy, ez = p[r].z - cz;
-        if (ok[r]) {
+        if (ok[r] && vw.g32s) {
             const float x = static_cast<float>(ex), y = static_cast<float>(ey), z = static_cast<float>(ez);
             vw.g32s[b + r * kThreads + tid] = make_float4(-2.0f * x, -2.0f * y, -2.0f * z, fmaf(z, z, fmaf(y, y, x * x)));
         }
@@ -981,7 +1086,7 @@ void lds_layout(int32_t max_edges, int32_t max_cells, int32_t cols, int32_t *col
     auto bytes = [&](int32_t c, int32_t cells) { return static_cast<uint32_t>(8 * (max_edges + cells) + 4 * ((max_edges + 1) * c + max_edges)); };
     static const uint32_t fixed = [] {
         hipFuncAttributes a;
-        return hipFuncGetAttributes(&a, reinterpret_cast<const void *>(k_count_blocks<false>)) == hipSuccess
+        return hipFuncGetAttributes(&a, reinterpret_cast<const void *>(k_count_blocks<false, false>)) == hipSuccess
                    ? static_cast<uint32_t>(a.sharedSizeBytes) : 36u * 1024u;
     }();
     const uint32_t room = 40u * 1024u - std::min(fixed, 40u * 1024u);
@@ -995,12 +1100,13 @@ void lds_layout(int32_t max_edges, int32_t max_cells, int32_t cols, int32_t *col
 
 // (global_table: the sets' chord tables do not fit into LDS at four workgroups a
 // CU; three workgroups with them took 115 ms where this takes 103)
-hipError_t occupancy(bool global_table, uint32_t lds_bytes, int *per_cu) {
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        per_cu, global_table ? k_count_blocks<true> : k_count_blocks<false>, kThreads, lds_bytes);
+hipError_t occupancy(bool fp64, bool global_table, uint32_t lds_bytes, int *per_cu) {
+    const auto k = fp64 ? (global_table ? k_count_blocks<true, true> : k_count_blocks<false, true>)
+                        : (global_table ? k_count_blocks<true, false> : k_count_blocks<false, false>);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k, kThreads, lds_bytes);
 }
 
-hipError_t launch_count(bool global_table, const SegDesc *segs, const TableDesc *tabs, const uint64_t *items, const uint64_t *tiles,
+hipError_t launch_count(bool fp64, bool global_table, const SegDesc *segs, const TableDesc *tabs, const uint64_t *items, const uint64_t *tiles,
                         const unsigned long long *n_items, unsigned long long *queue, unsigned long long *rechecked,
                         unsigned long long *stats, unsigned long long *counts, const unsigned long long *copies,
                         int64_t count_words, int32_t max_edges, int32_t max_cells, int32_t cols, uint32_t lds_bytes, int chunk, uint64_t flush_cap, int grid, hipStream_t st) {
@@ -1023,8 +1129,9 @@ hipError_t launch_count(bool global_table, const SegDesc *segs, const TableDesc 
     p.max_cells = max_cells;
     p.cols = cols;
     p.chunk = chunk;
-    if (global_table) k_count_blocks<true><<<dim3(grid), dim3(kThreads), lds_bytes, st>>>(p);
-    else k_count_blocks<false><<<dim3(grid), dim3(kThreads), lds_bytes, st>>>(p);
+    const auto k = fp64 ? (global_table ? k_count_blocks<true, true> : k_count_blocks<false, true>)
+                        : (global_table ? k_count_blocks<true, false> : k_count_blocks<false, false>);
+    k<<<dim3(grid), dim3(kThreads), lds_bytes, st>>>(p);
     return hipGetLastError();
 }
 
