@@ -86,8 +86,8 @@ int pc_debug_set_compact_table(int32_t mode);
  * launches (except pc_autotune's own candidates) run the vector kernel on
  * tiles of that many points whatever the tuner chose; 0 restores the default
  * (the block kernel on pairs of 512-point tiles where it serves the launch --
- * PC_MIXED with neither PC_NO_PRUNE nor PC_MATRIX_CORES -- the vector kernel on
- * 256-point tiles elsewhere, or the tuned size with PC_TUNED).  Counts do not depend on it.
+ * without PC_NO_PRUNE and PC_MATRIX_CORES -- the vector kernel on 256-point tiles
+ * elsewhere, or the tuned size with PC_TUNED).  Counts do not depend on it.
  * PC_ERR_INVALID for other values.
  */
 int pc_debug_set_tile(int32_t tile);
@@ -121,8 +121,8 @@ int pc_debug_last_launch(double *kernel_ms, uint64_t *items, int32_t *grid, uint
  * those items).  few_items counts the work units (items, or open sub-blocks
  * of split items) with at most 3 edges inside their chord interval (binned by
  * comparing with those edges alone), gram_items those whose vector-path
- * chords are formed in tile-centred Gram form.  The block kernel (the mixed
- * mode's pruned launches) looks at every left item in 32 x 32 blocks, all from
+ * chords are formed in tile-centred Gram form.  The block kernel (pruned
+ * launches without PC_MATRIX_CORES) looks at every left item in 32 x 32 blocks, all from
  * tile-centred coordinates: there split_items and gram_items count the items
  * with blocks left, few_items those of them with a block of at most 3 edges, and
  * mfma_items stays 0 (it counts PC_MATRIX_CORES items).  Any pointer may be NULL.

@@ -1,6 +1,6 @@
-// pc_kernels.hip -- the vector kernels of exact angular pair counting: binary64
-// mode, launches without pruning or with PC_MATRIX_CORES, and 128-point tiles.
-// (The mixed mode's default launch is the block kernel, pc_blocks.hip.)
+// pc_kernels.hip -- the vector kernels of exact angular pair counting: launches
+// without pruning or with PC_MATRIX_CORES, and 128-point tiles.  (Pruned launches
+// are the block kernel's, pc_blocks.hip.)
 //
 // Work decomposition (paper Sec. 2.1 splits the n x n pair matrix into
 // submatrices, one launch each; here one persistent launch covers every

@@ -2,8 +2,8 @@
 //
 // The counting launch has parameters that change its speed but not its counts:
 // the tile size (the size of the paper's submatrices, Sec. 2.1: 128 or 256
-// points, 256 standing for the default launch, which in the mixed mode is the
-// block kernel on pairs of 512-point tiles; smaller tiles bound sparse catalogues more tightly, so more tile
+// points, 256 standing for the default launch, the block kernel on pairs of
+// 512-point tiles; smaller tiles bound sparse catalogues more tightly, so more tile
 // pairs are binned whole or against fewer edges, at more work items), the
 // mixed kernel's histogram lane columns (LDS per wave, hence waves per CU,
 // and lanes sharing a counter word), how many work items a wave takes from the
