@@ -868,6 +868,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         d.a64s = ordered ? reinterpret_cast<double4 *>(W + vw.o_a64s) : const_cast<double4 *>(d.src);
         d.a32s = need_a32 ? reinterpret_cast<float4 *>(W + vw.o_a32s) : nullptr;
         d.g32s = need_g32 ? reinterpret_cast<float4 *>(W + vw.o_g32s) : nullptr;
+        d.slots = reinterpret_cast<uint32_t *>(d.g32s);  // done with when the bounds step writes there
         d.bounds = reinterpret_cast<double4 *>(W + vw.o_bounds);
         d.groups = blocks ? reinterpret_cast<float4 *>(W + vw.o_groups) : nullptr;
         d.n = n;
@@ -1113,8 +1114,15 @@ int upload_catalog(const pc_catalog *c, hipStream_t st, uint64_t *handle) {
     const size_t og = ar.take(sizeof(float4) * static_cast<size_t>(t512 * kGroups));
     const size_t ob = ar.take(sizeof(double4) * static_cast<size_t>(n_tiles(static_cast<int64_t>(n), kResidentTile.tile) *
                                                                      (1 + kResidentTile.subs)));
-    const size_t oerr = ar.take(sizeof(int) * 4 + sizeof(uint32_t) * kExtWords);  // flag, then the extent
-    const size_t odesc = ar.take(sizeof(SrcDesc) + 2 * sizeof(ViewDesc));
+    struct alignas(16) Desc {
+        SrcDesc s;
+        ViewDesc v, v512;          // v512: the bounds of the block kernel's tiles
+        uint32_t ext[kExtWords];   // zeroed with the rest: the extent,
+        int err[4];                // the validity flag
+    };
+    static_assert(sizeof(Desc) % 16 == 0 && sizeof(Desc) <= kPutBytes, "goes to the device as arguments");
+    const size_t odesc = ar.take(sizeof(Desc));
+    const size_t oext = odesc + offsetof(Desc, ext), oerr = odesc + offsetof(Desc, err);
     // scratch of the conversion and the ordering lies in copies that are
     // written after it is done with: counters and keys in the two Gram forms,
     // the caller's host arrays in the ordered binary32 copy
@@ -1131,13 +1139,11 @@ int upload_catalog(const pc_catalog *c, hipStream_t st, uint64_t *handle) {
     r->g512 = reinterpret_cast<float4 *>(W + og512);
     r->b512 = reinterpret_cast<double4 *>(W + ob512);
     r->groups = reinterpret_cast<float4 *>(W + og);
-    r->ext = reinterpret_cast<uint32_t *>(W + oerr) + 4;
-    PC_HIP(launch_zero(W + oerr, sizeof(int) * 4 + sizeof(uint32_t) * kExtWords, st), "zero");
-    if (c->n > 0) {
-        struct {
-            SrcDesc s;
-            ViewDesc v, v512;  // v512: the bounds of the block kernel's tiles
-        } d = {};
+    r->ext = reinterpret_cast<uint32_t *>(W + oext);
+    Desc d = {};
+    if (c->n <= 0) {
+        PC_HIP(launch_zero(W + odesc, sizeof(d), st), "zero");
+    } else {
         d.s.ra = c->ra_deg;
         d.s.dec = c->dec_deg;
         if (!c->on_device) {
@@ -1154,6 +1160,7 @@ int upload_catalog(const pc_catalog *c, hipStream_t st, uint64_t *handle) {
         d.v.ext = r->ext;
         d.v.keys = reinterpret_cast<uint32_t *>(W + okeys);
         d.v.hist = reinterpret_cast<uint32_t *>(W + ohist);
+        d.v.slots = d.v.keys + c->n;
         d.v.a64s = r->a64s;
         d.v.a32s = r->a32s;
         d.v.g32s = r->g32s;
@@ -1166,10 +1173,9 @@ int upload_catalog(const pc_catalog *c, hipStream_t st, uint64_t *handle) {
         d.v512.bounds = r->b512;
         d.v512.groups = r->groups;
         d.v512.tiles = t512;
-        PC_HIP(hipMemcpyAsync(W + odesc, &d, sizeof(d), hipMemcpyHostToDevice, st), "H2D descriptors");
         const SrcDesc *ds = reinterpret_cast<const SrcDesc *>(W + odesc);
-        const ViewDesc *dv = reinterpret_cast<const ViewDesc *>(W + odesc + sizeof(SrcDesc));
-        PC_HIP(launch_zero(W + ohist, sizeof(uint32_t) * buckets, st), "zero");
+        const ViewDesc *dv = reinterpret_cast<const ViewDesc *>(W + odesc + offsetof(Desc, v));
+        PC_HIP(launch_zero_put(W + ohist, sizeof(uint32_t) * buckets, W + odesc, &d, sizeof(d), st), "zero");
         PC_HIP(launch_convert(ds, 1, convert_blocks(c->n), st), "convert");
         PC_HIP(launch_order(dv, 1, order_blocks(c->n), reinterpret_cast<uint32_t *>(W + ohist), buckets,
                             reinterpret_cast<uint32_t *>(W + osums), st),

@@ -223,6 +223,7 @@ struct ViewDesc {
     const uint32_t *ext;    // extent of its source
     uint32_t *keys;         // n words
     uint32_t *hist;         // `buckets` zeroed counters, hist0 words into the launch's counters
+    uint32_t *slots;        // a point's place among its cell's, or null
     double4 *a64s;          // ordered copies: binary64,
     float4 *a32s, *g32s;    // binary32 (or null), Gram form centred on the tile (or null)
     double4 *bounds;        // of its tiles, then of their sub-blocks
