@@ -77,7 +77,7 @@ def code_fingerprint(paths) -> str:
 
 
 # the sources whose code a traffic record was taken on, per kernel
-K_COUNT_SOURCES = ("pc_kernels.hip", "pc_internal.hpp", "pc_math.h")
+K_COUNT_SOURCES = ("pc_blocks.hip", "pc_internal.hpp")
 K_AP_MAP_SOURCES = ("pc_aperture.hip",)
 
 

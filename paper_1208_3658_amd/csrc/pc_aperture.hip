@@ -50,7 +50,11 @@ constexpr int kApPerCu = 64;           // and per CU wanted (see block_parts)
 constexpr int kApGroup = 4;            // galaxies whose weights one scalar load fetches
 constexpr int kQCells = 1024;          // filter table cells over x in [0, 1], and one at x = 1
 constexpr int kApFlush = 64;           // galaxies summed in binary32 before the binary64 add
-constexpr int kApTested = 0, kApInside = 1, kApFlag = 2, kApMeta = 3;  // pairs tested, inside; a galaxy is not finite
+// a galaxy is not finite; pairs tested, inside: each in cache lines of its own,
+// as every workgroup reads the first and adds to the others (in one line the
+// reads waited for the adds: 2.17 ms instead of 0.87 for 2048 x 2048 points of 1
+// arcmin)
+constexpr int kApFlag = 0, kApTested = 32, kApInside = 64, kApMeta = 65, kApMetaWords = 96;
 constexpr uint32_t kNoCell = 0xFFFFFFFFu;
 constexpr int64_t kMaxCells = int64_t(1) << 22;
 constexpr double kMaxExtent = 1e15;     // lattice extent limit (binary32 offsets stay finite)
@@ -81,7 +85,7 @@ struct ApParams {
     Lattice lat;
     double x0, y0, gdx, gdy;
     int32_t nx, ny, tiles_x, n_tiles, per_xcd;  // tiles: blocks of 8P x 8P points
-    int32_t parts;    // workgroups per block
+    int32_t parts;    // workgroups per block; 0: a block per wave, four blocks per workgroup
     double r2;        // theta^2 (binary64), the cut
     double reach;     // theta with a relative margin for the cell search
     float k_x;        // x = r k_x = r / theta, clamped to [0, 1]; table position s = kQCells x
@@ -225,7 +229,8 @@ __device__ __forceinline__ float q_table(float s, uint32_t tab) {
     return fmaf(fmaf(fmaf(c.w, t, c.z), t, c.y), t, c.x);
 }
 
-// A workgroup of four waves owns a block of (8P) x (8P) grid points: lane (lx,
+// A workgroup of four waves owns a block of (8P) x (8P) grid points (or four
+// blocks, one per wave, see block_parts): lane (lx,
 // ly) = (lane % 8, lane / 8) of every wave holds the P x P points (lx + 8a, ly +
 // 8b), so every galaxy read is used for P^2 independent pairs per lane.  The
 // galaxies near the block come in runs of at most 64 that share a row of cells;
@@ -306,7 +311,7 @@ k_ap_map(const ApParams p) {
     using lds_f4 = __attribute__((address_space(3))) const f32x4;
     using WeightU = const __attribute__((address_space(4))) f32x4;  // wave-uniform: scalar loads
     __shared__ float4 qtab[kQCells + 1];
-    __shared__ uint2 rows[kApRows];
+    __shared__ uint2 all_rows[kApWaves][kApRows];
     const int tid = static_cast<int>(threadIdx.x);
     const int lane = tid & 63;
     const int wave = static_cast<int>(__builtin_amdgcn_readfirstlane(tid >> 6));
@@ -316,8 +321,13 @@ k_ap_map(const ApParams p) {
     // catalogue that is refused (the outputs stay as they are)
     if (tile >= p.n_tiles || p.meta[kApFlag] != 0) return;
     for (int k = tid; k <= kQCells; k += 64 * kApWaves) qtab[k] = p.qtab[k];
+    __syncthreads();
+    const bool shared_block = p.parts > 0;
+    uint2 *const rows = all_rows[wave];
     const int tx = tile % p.tiles_x, ty = tile / p.tiles_x;
-    const int ix0 = tx * BS, iy0 = ty * BS;
+    const int ix0 = (shared_block ? tx : 2 * tx + (wave & 1)) * BS, iy0 = (shared_block ? ty : 2 * ty + (wave >> 1)) * BS;
+    // a block of the group past the grid's edge has no points
+    if (ix0 >= p.nx || iy0 >= p.ny) return;
     const int ix1 = min(ix0 + BS - 1, p.nx - 1), iy1 = min(iy0 + BS - 1, p.ny - 1);
     // the block's reference point: its centre (any binary64 value serves)
     const double xb = p.x0 + (static_cast<double>(ix0) + 0.5 * (BS - 1)) * p.gdx;
@@ -367,13 +377,15 @@ k_ap_map(const ApParams p) {
     const int cy0 = cell_index(gyl - p.reach - L.s * 1e-9, L.oy, L.inv_s, L.ncy);
     const int cy1 = cell_index(gyh + p.reach + L.s * 1e-9, L.oy, L.inv_s, L.ncy);
     // the wave's turn among the runs of the block
-    const uint32_t turns = static_cast<uint32_t>(p.parts) * kApWaves;
-    uint32_t skip = blockIdx.y * kApWaves + static_cast<uint32_t>(wave);
+    const uint32_t turns = shared_block ? static_cast<uint32_t>(p.parts) * kApWaves : 1u;
+    uint32_t skip = shared_block ? blockIdx.y * kApWaves + static_cast<uint32_t>(wave) : 0u;
     for (int cyb = cy0; cyb <= cy1; cyb += kApRows) {
         const int n_rows = min(cy1 - cyb + 1, kApRows);
-        __syncthreads();
-        if (tid < n_rows) rows[tid] = ap_row(p, cyb + tid, gxl, gxh, gyl, gyh);
-        __syncthreads();
+        // the wave's own copy: LDS operations of a wave are done in order
+        __builtin_amdgcn_wave_barrier();
+        if (lane < n_rows) rows[lane] = ap_row(p, cyb + lane, gxl, gxh, gyl, gyh);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
         for (int ri = 0; ri < n_rows; ++ri) {
             const uint32_t g_begin = __builtin_amdgcn_readfirstlane(rows[ri].x);
             const uint32_t g_end = __builtin_amdgcn_readfirstlane(rows[ri].y);
@@ -590,20 +602,22 @@ k_ap_map(const ApParams p) {
     static_assert((kApWaves - 1) * kPts * (sizeof(double2) + sizeof(uint32_t)) <= sizeof(qtab), "space for the sums");
     double2 *const sum = reinterpret_cast<double2 *>(qtab);
     uint32_t *const num = reinterpret_cast<uint32_t *>(sum + (kApWaves - 1) * kPts);
-    __syncthreads();
-    if (wave > 0) {
+    if (shared_block) __syncthreads();
+    if (shared_block && wave > 0) {
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             sum[(wave - 1) * kPts + k * 64 + lane] = make_double2(S1[k], S2[k]);
             num[(wave - 1) * kPts + k * 64 + lane] = cnt[k];
         }
     }
-    __syncthreads();
-    if (wave > 0) return;
+    if (shared_block) {
+        __syncthreads();
+        if (wave > 0) return;
+    }
     uint32_t in_lane = 0, lanes = 0;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        for (int w = 0; w < kApWaves - 1; ++w) {
+        for (int w = 0; shared_block && w < kApWaves - 1; ++w) {
             const double2 v = sum[w * kPts + k * 64 + lane];
             S1[k] += v.x;
             S2[k] += v.y;
@@ -628,7 +642,7 @@ k_ap_map(const ApParams p) {
         const uint32_t pts = wave_sum_u32(lanes);
         if (lane == 0) atomicAdd(p.meta + kApTested, static_cast<unsigned long long>(tested) * pts);
     }
-    if (p.parts == 1) {
+    if (p.parts <= 1) {
         const uint32_t in_block = wave_sum_u32(in_lane);
         if (lane == 0) atomicAdd(p.meta + kApInside, static_cast<unsigned long long>(in_block));
     }
@@ -822,16 +836,33 @@ int points_per_lane(const pc_grid *g, double theta, int cus) {
     return 16.0 * std::max(g->dx, g->dy) <= 0.25 * theta && blocks16 >= 16.0 * cus ? 2 : 1;
 }
 
-// Workgroups per block: a grid of few blocks leaves CUs idle, or one or two
-// workgroups on each, which latency then bounds.  kApPerCu workgroups per CU
-// (nine times what fits at once) also let large and small blocks even out; more
-// than kApMaxParts of a block cost more in the final sum than they gain.
-// Map kernel and sum with at most 1 / 4 / 8 / 16 / 32 parts: 301 / 105 / 77 / 77 /
-// 80 us at 120 blocks, 1.77 / 1.73 / 1.70 / 1.69 / 1.71 ms at 4096; from 16384 blocks
-// on there is one part (191 ms at 16384 blocks of 16 x 16 points).
-int block_parts(int32_t n_tiles, int cus) {
+// Workgroups per block, or 0: a wave per block.  g: galaxies a block sees, about
+// (the grid's area taken for the field's).  A workgroup costs some microseconds
+// before its first galaxy, so a block gets several only to fill the chip (four
+// per CU), or where each still has 400 galaxies and the CUs, by g / 100 workgroups
+// each, have room; and a large grid of small apertures (g below 3000, 32 blocks a
+// CU) leaves each block to one wave.  Map kernel with 0 / 1 / 2 / 4 / 8 / 16, us:
+//   144 blocks, g  6107:    977   279   169   114    86    86   -> 8
+//   144 blocks, g   442:    119    49    38    32    34    44   -> 4
+//   625 blocks, g  2018:    312   149   118   105   110   136   -> 4
+//  1444 blocks, g   343:    106    66    79   100   144   225   -> 1
+//  1444 blocks, g  2468:    418   273   247   231   250   316   -> 4
+//  4096 blocks, g  1306:    374   317   340   398   509   765   -> 1
+//  4096 blocks, g  9959:   2154  1742  1662  1650  1740  1947   -> 4
+// 16384 blocks, g   344:    330   355   486   689  1018  1588   -> 0
+// 16384 blocks, g  8583:   5496  5058  5112  5300  5648  6394   -> 1
+// 65536 blocks, g  2196:   5168  5563  6116  6868  8392 11555   -> 0
+// 65536 blocks, g  8678:  17380 16511 16729 16994 17634 18931   -> 1
+int block_parts(const pc_grid *g, double theta, int64_t n, int32_t side, int32_t n_blocks, int cus) {
+    const double w = side * g->dx, h = side * g->dy;
+    const double seen = std::min(static_cast<double>(n), static_cast<double>(n) * (3.14 * theta * theta + 2.0 * theta * (w + h) + w * h) /
+                                                             (g->dx * g->nx * (g->dy * g->ny)));
+    const double blocks = n_blocks, per_cu = std::min(seen / 100.0, static_cast<double>(kApPerCu));
+    if (blocks >= 32.0 * cus && seen < 3000.0) return 0;
     int parts = 1;
-    while (parts < kApMaxParts && static_cast<int64_t>(n_tiles) * parts < int64_t(kApPerCu) * cus) parts *= 2;
+    while (parts < kApMaxParts && (blocks * 2 * parts <= 4.0 * cus ||
+                                   (blocks * 2 * parts <= per_cu * cus && seen >= 400.0 * 2 * parts)))
+        parts *= 2;
     return parts;
 }
 
@@ -939,8 +970,9 @@ extern "C" int pc_aperture_mass(const pc_shear_catalog *cat, const pc_grid *grid
     const int P = points_per_lane(grid, theta_max, di->cus);
     const int32_t side = 8 * P;
     const int32_t tiles_x = (grid->nx + side - 1) / side;
-    const int32_t n_tiles = tiles_x * ((grid->ny + side - 1) / side);
-    const int parts = block_parts(n_tiles, di->cus);
+    const int32_t n_blocks = tiles_x * ((grid->ny + side - 1) / side);
+    const int parts = block_parts(grid, theta_max, n, side, n_blocks, di->cus);
+    const int32_t n_tiles = parts > 0 ? n_blocks : ((grid->nx + 2 * side - 1) / (2 * side)) * ((grid->ny + 2 * side - 1) / (2 * side));
 
     // work space
     const bool host_in = !cat->on_device, host_out = !out_on_device;
@@ -952,8 +984,8 @@ extern "C" int pc_aperture_mass(const pc_shear_catalog *cat, const pc_grid *grid
     const size_t o_pos = take(&size, sizeof(double2) * nn);
     const size_t o_wgt = take(&size, sizeof(ApWeight) * (nn + 2 * kApGroup));
     // the counters of pairs and the cells' starts: cleared by one launch
-    const size_t o_meta = take(&size, sizeof(unsigned long long) * (kApMeta + 1) + sizeof(uint32_t) * static_cast<size_t>(n_cells + 1));
-    const size_t o_start = o_meta + sizeof(unsigned long long) * (kApMeta + 1);
+    const size_t o_meta = take(&size, sizeof(unsigned long long) * kApMetaWords + sizeof(uint32_t) * static_cast<size_t>(n_cells + 1));
+    const size_t o_start = o_meta + sizeof(unsigned long long) * kApMetaWords;
     const size_t o_slots = take(&size, sizeof(uint32_t) * nn);
     const size_t o_sums = take(&size, sizeof(uint32_t) * scan_sums_words(n_cells + 1));
     const size_t o_part_s = take(&size, parts > 1 ? sizeof(double2) * static_cast<size_t>(parts) * static_cast<size_t>(m) : 0);
@@ -991,7 +1023,7 @@ extern "C" int pc_aperture_mass(const pc_shear_catalog *cat, const pc_grid *grid
     if (rc) return rc;
 
     // order the galaxies by cell
-    AP_HIP(launch_zero_u32(reinterpret_cast<uint32_t *>(meta), 2 * (kApMeta + 1) + n_cells + 1, st), "zero cell counts");
+    AP_HIP(launch_zero_u32(reinterpret_cast<uint32_t *>(meta), 2 * kApMetaWords + n_cells + 1, st), "zero cell counts");
     if (n > 0) {
         const dim3 grid_n(static_cast<uint32_t>((n + 255) / 256));
         k_ap_keys<<<grid_n, dim3(256), 0, st>>>(X, Y, E1, E2, n, L, keys, slots, start, meta);
@@ -1021,7 +1053,7 @@ extern "C" int pc_aperture_mass(const pc_shear_catalog *cat, const pc_grid *grid
     p.gdy = grid->dy;
     p.nx = grid->nx;
     p.ny = grid->ny;
-    p.tiles_x = tiles_x;
+    p.tiles_x = parts > 0 ? tiles_x : (grid->nx + 2 * side - 1) / (2 * side);
     p.n_tiles = n_tiles;
     p.per_xcd = (p.n_tiles + 7) / 8;
     p.parts = parts;
@@ -1053,7 +1085,7 @@ extern "C" int pc_aperture_mass(const pc_shear_catalog *cat, const pc_grid *grid
     // f2 needs no raise when every value it can take in the binary32 step is
     // positive and normal (see k_ap_map)
     const bool raise = !(p.f2_in >= FLT_MIN);
-    const dim3 grid_dim(static_cast<uint32_t>(8 * p.per_xcd), static_cast<uint32_t>(parts)), block_dim(64 * kApWaves);
+    const dim3 grid_dim(static_cast<uint32_t>(8 * p.per_xcd), static_cast<uint32_t>(std::max(parts, 1))), block_dim(64 * kApWaves);
     if (P == 2 && !raise)
         k_ap_map<2, false><<<grid_dim, block_dim, 0, st>>>(p);
     else if (P == 2)
