@@ -155,16 +155,17 @@ __global__ void __launch_bounds__(256) k_ap_scatter(const uint32_t *__restrict__
 
 // That order is arbitrary; place each galaxy at its rank by catalogue index
 // inside the cell, so the summation order of the map kernel, and with it every
-// output bit, is reproducible.
+// output bit, is reproducible.  A thread per place, not per galaxy: the threads of
+// a cell then read the same members (1M galaxies, 9 a cell: 83 us, per galaxy 73; but
+// 140 a cell: 110, per galaxy 586).
 __global__ void __launch_bounds__(256) k_ap_place(const double *__restrict__ X, const double *__restrict__ Y,
                                                   const double *__restrict__ E1, const double *__restrict__ E2,
                                                   const uint32_t *__restrict__ keys, const uint32_t *__restrict__ idx,
-                                                  const uint32_t *__restrict__ start, int64_t n,
+                                                  const uint32_t *__restrict__ start, int64_t n_cells, int64_t n,
                                                   double2 *__restrict__ pos, ApWeight *__restrict__ wgt) {
     const int64_t j = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (j >= n) return;
-    const uint32_t i = static_cast<uint32_t>(j), key = keys[i];
-    if (key == kNoCell) return;
+    if (j >= n || j >= static_cast<int64_t>(start[n_cells])) return;
+    const uint32_t i = idx[j], key = keys[i];
     const uint32_t lo = start[key], hi = start[key + 1];
     uint32_t rank = 0;
     for (uint32_t q = lo; q < hi; ++q) rank += idx[q] < i ? 1u : 0u;
@@ -1031,7 +1032,7 @@ extern "C" int pc_aperture_mass(const pc_shear_catalog *cat, const pc_grid *grid
         AP_HIP(launch_exclusive_scan(start, n_cells + 1, sums, st), "cell scan");
         k_ap_scatter<<<grid_n, dim3(256), 0, st>>>(keys, slots, start, n, idx);
         AP_HIP(hipGetLastError(), "k_ap_scatter");
-        k_ap_place<<<grid_n, dim3(256), 0, st>>>(X, Y, E1, E2, keys, idx, start, n, pos, wgt);
+        k_ap_place<<<grid_n, dim3(256), 0, st>>>(X, Y, E1, E2, keys, idx, start, n_cells, n, pos, wgt);
         AP_HIP(hipGetLastError(), "k_ap_place");
     }
 
