@@ -42,11 +42,11 @@
 // What bounds it: vector instructions and matrix products, which a SIMD does
 // not overlap: together some 85% of the cycles, the rest waits for LDS and at
 // the tile pair's barriers.  A block of one edge takes 34 vector instructions
-// and four products (about 47 cycles of a CU), of two 57, through the table 151,
+// and four products (about 47 cycles of a CU), of two 57, through the table 115 or 135,
 // by differences 97 per half; the item's and the columns' shares are 15 to 27 per
 // block.  Counting kernel, this one against the vector kernel of 256-point tiles
-// on the same ordering: 22.5 / 42.7 ms on the 1M workload, 127 / 212 ms for 1M x 1M
-// points in 254 bins, 13.8 / 21.0 ms for 64 mocks x 300,000 randoms, 1.63 / 2.2 ms
+// on the same ordering: 21.9 / 42.7 ms on the 1M workload, 103 / 212 ms for 1M x 1M
+// points in 254 bins, 13.0 / 21.0 ms for 64 mocks x 300,000 randoms, 1.51 / 2.2 ms
 // for 300,000 x 400,000 resident points in 24 even bins, 0.10 / 0.29 ms for 10,000
 // + 10,000 points, 0.024 / 0.134 ms for 1003 points.
 //
@@ -75,9 +75,13 @@
 // (tile-centred Gram).
 //
 // Blocks of three edges and more (near tiles, sparse catalogues) look each chord
-// up in a table instead: c' = RN(RN(h) - d) is within E_t = E + 4 u (D + R)^2 of the
-// chord, its cell holds at most one edge, and a chord within E_t of that edge
-// goes to binary64.  The table needs E_t below an eighth of a cell (see
+// up in a table instead.  There the product starts at RN(D^2) and takes the
+// j-points negated, so that it is the chord itself: |D|^2 joins M (13 u D^2) and is
+// rounded (u D^2), the table's edge is (2 u (D + R)^2), so the chord is within E_t =
+// E + 14 u D^2 + 2 u (D + R)^2 (measured: at most 0.18 E_t, 3.7 u (D + R)^2 and 0.24 to
+// 0.76 in the mean square, where the cell table of the vector kernel has the
+// differences' 28 and 0.5 to 2.2).  Its cell holds at most one edge, and a chord within
+// E_t of that edge goes to binary64.  The table needs E_t below an eighth of a cell (see
 // build_lutb); blocks that reach below that (near ones: E grows with the tiles'
 // size, not with the chord) form their chords from differences, (D - b') + a'
 // per coordinate, whose error follows the chord: the difference vector is off
@@ -587,7 +591,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
             at[48] = slots_si(i < i_lim ? s : kNever);
         }
         // ---- classification of the wave's 64 blocks
-        const float E_t = (E + 0x1p-22f * (Dl + R) * (Dl + R)) * (1.0f + 0x1p-16f);
+        const float E_t = (E + 0x1p-23f * (7.0f * Dl * Dl + (Dl + R) * (Dl + R))) * (1.0f + 0x1p-16f);
         if (classifies) {
             const float vx = fx + (si.x - sj.x), vy = fy + (si.y - sj.y), vz = fz + (si.z - sj.z);
             const float d = __builtin_amdgcn_sqrtf(fmaf(vx, vx, fmaf(vy, vy, vz * vz)));
@@ -854,6 +858,9 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
                     }
                 }
             }
+            // far blocks of the table last
+            uint32_t look = ballot32((desc & (kTableBlock | kNearBlock)) == kTableBlock) & open;
+            open &= ~look;
             // blocks of more edges, and those on the diagonal
             while (open) {
                 const int bi = __builtin_ctz(open);
@@ -861,86 +868,49 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
                 const uint32_t key = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(desc), bi));
                 const uint32_t k0 = key & 0xFFFFu, m = (key >> 16) & 0xFFFu;
                 BlockD D;
-                if (key & kTableBlock) {
-                    if (key & kNearBlock) {
-                        const float S = Dl + R, A = 0x1p-20f * S, A2 = 2.0f * A * A, B2 = 0x1p-83f * (S * S) * (S * S);
-                        const float q = A * pow2(28u - tbl.shift);
-                        const float floor_c = fmaxf(q * q, 0x1p-42f * S * S * pow2(28u - tbl.shift)) * (1.0f + 0x1p-10f);
-                        const float A2n = -A2;
-                        float px[2], py[2], pz[2];
-                        int32_t below[2];  // i-points (of the tile) that the lane's j-points pair with
+                if (key & kNearBlock) {
+                    const float S = Dl + R, A = 0x1p-20f * S, A2 = 2.0f * A * A, B2 = 0x1p-83f * (S * S) * (S * S);
+                    const float q = A * pow2(28u - tbl.shift);
+                    const float floor_c = fmaxf(q * q, 0x1p-42f * S * S * pow2(28u - tbl.shift)) * (1.0f + 0x1p-10f);
+                    const float A2n = -A2;
+                    float px[2], py[2], pz[2];
+                    int32_t below[2];  // i-points (of the tile) that the lane's j-points pair with
 #pragma unroll
-                        for (int c = 0; c < 2; ++c) {
-                            const int j = cb * kG + 16 * c + (lane & 15);
-                            const float4 g = jg[min(j, j_lim - 1)];
-                            px[c] = fmaf(0.5f, g.x, fx);
-                            py[c] = fmaf(0.5f, g.y, fy);
-                            pz[c] = fmaf(0.5f, g.z, fz);
-                            below[c] = j >= j_lim ? 0 : (key & kDiagBlock) ? min(j, i_lim) : i_lim;
-                        }
-#pragma unroll 1
-                        for (int r = 0; r < 8; r += 4) {
-                            float4 g[4];
-                            const int i0 = bi * kG + 4 * r + 4 * grp;
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) g[v] = (ld_uniform(&sp->ig) + ibeg)[min(i0 + v, i_lim - 1)];
-                            float x[8], d[8];
-                            u32x2 e[8];
-                            uint32_t at[8], hits = 0;
-#pragma unroll
-                            for (int v = 0; v < 8; ++v) {
-                                const float4 &a = g[v & 3];
-                                const float dx = fmaf(-0.5f, a.x, px[v >> 2]), dy = fmaf(-0.5f, a.y, py[v >> 2]),
-                                            dz = fmaf(-0.5f, a.z, pz[v >> 2]);
-                                x[v] = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-                                e[v] = cell_of<GT, true>(tbl, x[v]);
-                            }
-#pragma unroll
-                            for (int v = 0; v < 8; ++v) {
-                                d[v] = __uint_as_float(e[v].x) - x[v];
-                                at[v] = row_offset(tbl, e[v], d[v]);
-                                const bool ok = i0 + (v & 3) < below[v >> 2];
-                                add_offset(at[v] + column, ok ? 1u : 0u);
-                                if (ok && (fmaf(d[v], d[v], A2n * x[v]) <= B2 || x[v] <= floor_c)) hits |= 1u << v;
-                            }
-                            send_rows(hits, at, bi, 2 * r);
-                        }
-                        continue;
+                    for (int c = 0; c < 2; ++c) {
+                        const int j = cb * kG + 16 * c + (lane & 15);
+                        const float4 g = jg[min(j, j_lim - 1)];
+                        px[c] = fmaf(0.5f, g.x, fx);
+                        py[c] = fmaf(0.5f, g.y, fy);
+                        pz[c] = fmaf(0.5f, g.z, fz);
+                        below[c] = j >= j_lim ? 0 : (key & kDiagBlock) ? min(j, i_lim) : i_lim;
                     }
-                    const float H0 = threshold(k0);
-                    const float top = uni_f(static_cast<float>(static_cast<double>(H0) + D2));  // c = top - d
-                    block_products(As, bi, B, H0, D);
-                    auto look_up = [&](auto clamp) {
+#pragma unroll 1
+                    for (int r = 0; r < 8; r += 4) {
+                        float4 g[4];
+                        const int i0 = bi * kG + 4 * r + 4 * grp;
 #pragma unroll
-                        for (int q = 0; q < 16; q += kLook) {
-                            float c[kLook];
-                            u32x2 e[kLook];
-                            uint32_t at[kLook];
-                            float least = INFINITY;
+                        for (int v = 0; v < 4; ++v) g[v] = (ld_uniform(&sp->ig) + ibeg)[min(i0 + v, i_lim - 1)];
+                        float x[8], d[8];
+                        u32x2 e[8];
+                        uint32_t at[8], hits = 0;
 #pragma unroll
-                            for (int v = 0; v < kLook; ++v) {
-                                c[v] = top - D.d[(q + v) >> 2][v & 3];
-                                e[v] = cell_of<GT, decltype(clamp)::value>(tbl, c[v]);
-                            }
-#pragma unroll
-                            for (int v = 0; v < kLook; ++v) {
-                                c[v] = __uint_as_float(e[v].x) - c[v];
-                                at[v] = row_offset(tbl, e[v], c[v]);
-                                add_offset(at[v] + column, 1u);
-                                least = fminf(least, fabsf(c[v]));
-                            }
-                            if (__builtin_expect(__builtin_amdgcn_ballot_w64(least <= E_t) != 0, 0)) {
-                                uint32_t hits = 0;
-#pragma unroll
-                                for (int v = 0; v < kLook; ++v) hits |= fabsf(c[v]) <= E_t ? 1u << v : 0u;
-                                send_rows(hits, at, bi, q);
-                            }
+                        for (int v = 0; v < 8; ++v) {
+                            const float4 &a = g[v & 3];
+                            const float dx = fmaf(-0.5f, a.x, px[v >> 2]), dy = fmaf(-0.5f, a.y, py[v >> 2]),
+                                        dz = fmaf(-0.5f, a.z, pz[v >> 2]);
+                            x[v] = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+                            e[v] = cell_of<GT, true>(tbl, x[v]);
                         }
-                    };
-                    // (without the clamp 131 instructions a block instead of 151: 1.61 / 1.66 ms
-                    // for 300,000 x 400,000 points, 13.5 / 13.8 ms for 64 mocks)
-                    if (key & kInRange) look_up(std::false_type());
-                    else look_up(std::true_type());
+#pragma unroll
+                        for (int v = 0; v < 8; ++v) {
+                            d[v] = __uint_as_float(e[v].x) - x[v];
+                            at[v] = row_offset(tbl, e[v], d[v]);
+                            const bool ok = i0 + (v & 3) < below[v >> 2];
+                            add_offset(at[v] + column, ok ? 1u : 0u);
+                            if (ok && (fmaf(d[v], d[v], A2n * x[v]) <= B2 || x[v] <= floor_c)) hits |= 1u << v;
+                        }
+                        send_rows(hits, at, bi, 2 * r);
+                    }
                     continue;
                 }
                 const float H0 = threshold(k0);
@@ -976,6 +946,52 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
                         block_tally<kSelHi, true>(D, d1, nq, mn);
                     }
                 }
+            }
+            // The product of the negated j-points is the chord less |D|^2: a
+            // subtraction per pair less than from d, 15.2 / 14.6 ms for 64 mocks,
+            // 1.70 / 1.64 ms for 300,000 x 400,000 points.
+            if (look) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) B[c] ^= 0x80008000u;
+                const float D2f = uni_f(static_cast<float>(D2));
+                do {
+                    const int bi = __builtin_ctz(look);
+                    look &= look - 1u;
+                    const uint32_t key = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(desc), bi));
+                    BlockD D;
+                    block_products(As, bi, B, D2f, D);
+                    auto look_up = [&](auto clamp) {
+#pragma unroll
+                        for (int q = 0; q < 16; q += kLook) {
+                            float c[kLook];
+                            u32x2 e[kLook];
+                            uint32_t at[kLook];
+                            float least = INFINITY;
+#pragma unroll
+                            for (int v = 0; v < kLook; ++v) {
+                                c[v] = D.d[(q + v) >> 2][v & 3];
+                                e[v] = cell_of<GT, decltype(clamp)::value>(tbl, c[v]);
+                            }
+#pragma unroll
+                            for (int v = 0; v < kLook; ++v) {
+                                c[v] = __uint_as_float(e[v].x) - c[v];
+                                at[v] = row_offset(tbl, e[v], c[v]);
+                                add_offset(at[v] + column, 1u);
+                                least = fminf(least, fabsf(c[v]));
+                            }
+                            if (__builtin_expect(__builtin_amdgcn_ballot_w64(least <= E_t) != 0, 0)) {
+                                uint32_t hits = 0;
+#pragma unroll
+                                for (int v = 0; v < kLook; ++v) hits |= fabsf(c[v]) <= E_t ? 1u << v : 0u;
+                                send_rows(hits, at, bi, q);
+                            }
+                        }
+                    };
+                    // (without the clamp 115 instructions a block instead of 135: 1.61 / 1.66 ms
+                    // for 300,000 x 400,000 points, 13.5 / 13.8 ms for 64 mocks)
+                    if (key & kInRange) look_up(std::false_type());
+                    else look_up(std::true_type());
+                } while (look);
             }
         }
         flush_run();
