@@ -744,9 +744,10 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     const size_t zero_bytes = (o_region - o_res + sizeof(uint32_t) * static_cast<size_t>(hist_words) + 15) & ~size_t(15);
     const size_t o_sums = ar.take(sizeof(uint32_t) * std::max<size_t>(scan_sums_words(hist_words), 4));
     // descriptors, sent with one copy: sources | views | segments | tables
+    // (written in whole 16-byte words, see launch_zero_put)
     const size_t b_srcs = sizeof(SrcDesc) * srcs.size(), b_views = sizeof(ViewDesc) * views.size(),
                  b_segs = sizeof(SegDesc) * segs.size(), b_tabs = sizeof(TableDesc) * tabs.size();
-    const size_t o_desc = ar.take(b_srcs + b_views + b_segs + b_tabs);
+    const size_t o_desc = ar.take((b_srcs + b_views + b_segs + b_tabs + 15) & ~size_t(15));
     std::vector<size_t> o_blob(blobs.size());
     for (size_t k = 0; k < blobs.size(); ++k) o_blob[k] = ar.take(blobs[k].bytes.size());
     if (plan_only) {
