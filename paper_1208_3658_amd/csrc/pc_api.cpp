@@ -53,7 +53,7 @@ namespace t256 { PC_TILE_STEPS }
 // the block kernel (pc_blocks.hip)
 namespace blk {
 hipError_t launch_bounds(const ViewDesc *views, int n_views, int64_t tiles, hipStream_t st);
-void lds_layout(int32_t max_edges, int32_t max_cells, int32_t cols, int32_t *cols_out, int32_t *cells_out,
+void lds_layout(bool fp64, bool few_pairs, int32_t max_edges, int32_t max_cells, int32_t cols, int32_t *cols_out, int32_t *cells_out,
                 uint32_t *lds_bytes);
 hipError_t occupancy(bool fp64, bool global_table, uint32_t lds_bytes, int *per_cu);
 hipError_t launch_count(bool fp64, bool global_table, const SegDesc *segs, const TableDesc *tabs, const uint64_t *items, const uint64_t *tiles,
@@ -849,7 +849,9 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
             all = all && !t->host.lutb.empty();
         }
         const bool any = max_cells > 0;
-        blk::lds_layout(max_edges, max_cells, lt.cols ? std::min(lt.cols, 16) : 16, &bcols, &max_cells, &blocks_lds);
+        double pairs = 0.0;
+        for (const SegDesc &sd : segs) pairs += static_cast<double>(sd.ni) * static_cast<double>(sd.nj) * (sd.tri ? 0.5 : 1.0);
+        blk::lds_layout(fp64, pairs <= kUnorderedPairs, max_edges, max_cells, lt.cols ? std::min(lt.cols, 16) : 16, &bcols, &max_cells, &blocks_lds);
         // Few pairs are counted in the caller's order: unordered groups prune
         // nothing and put every block through the chord table (hence only with
         // one), but the four ordering launches cost more than that.  Whole
@@ -858,10 +860,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         // 156 / 144 for 8192 x 8192 in bins of all scales, but 131 / 136 where the
         // bins end at 2 degrees and the order lets most pairs go.
         global_table = any && max_cells == 0;
-        ordered = !all || max_cells == 0;
-        double pairs = 0.0;
-        for (const SegDesc &sd : segs) pairs += static_cast<double>(sd.ni) * static_cast<double>(sd.nj) * (sd.tri ? 0.5 : 1.0);
-        ordered = ordered || pairs > kUnorderedPairs;
+        ordered = !all || max_cells == 0 || pairs > kUnorderedPairs;
     }
     std::vector<ViewDesc> vds;
     int64_t ord_blocks = 0, all_tiles = 0;

@@ -102,6 +102,7 @@
 // for 100,000 + 100,000 points in 30 bins, the vector kernel of 256-point tiles
 // 3.26.
 #include <algorithm>
+#include <array>
 #include <type_traits>
 
 #include "pc_internal.hpp"
@@ -133,13 +134,17 @@ constexpr uint32_t kNearBlock = 1u << 29;   // with kTableBlock: chords from dif
 // 3 / 4 / 5 / 6: 1.63 / 1.68 / 1.67 / 1.77 ms for 300,000 x 400,000 points, 13.8 / 14.0 /
 // 14.6 / 15.1 ms for 64 mocks, 22.5 / 22.6 / 22.7 / 23.0 ms on the 1M workload.
 constexpr uint32_t kTableEdges = 3;
-// The same with the table in global memory: large edge sets, whose histogram has
-// one or two lane columns for 64 lanes' adds.  1M x 1M points in 254 bins with the
-// line at 4 / 5 / 6 / 8 / 10: 115.2 / 105.3 / 103.0 / 102.8 / 103.9 ms, without the table
-// 127 ms (tiles next to each other have tens of edges a block).
-constexpr uint32_t kTableEdgesG = 8;
+// The same with the table in global memory, by the histogram's lane columns: the
+// fewer there are, the more of 64 lanes' adds meet in one word.  Whole calls with the
+// line at 4 / 5 / 6 / 8 / 12, ms: eight columns (125 log bins, 300,000 x 300,000 points)
+// 9.58 / 9.68 / 9.88 / 10.3 / 10.9; four (150 and 200) 11.8 / 11.3 / 11.4 / 11.9 / 12.6 and
+// 15.3 / 14.2 / 14.3 / 14.9 / 16.1; two (254) 28.6 / 21.0 / 18.7 / 18.4 / 19.8, and 1M x 1M
+// points 115.2 / - / 103.0 / 102.8 / 105; one (300 bins, 100,000 x 100,000 points)
+// - / 10.0 / - / 4.70 / 4.15.
+constexpr uint32_t table_edges_global(int32_t cols) { return cols >= 4 ? 5u : cols == 2 ? 8u : 12u; }
 // The same in binary64, where an edge costs a pair a comparison: 100,000 + 100,000
-// points in 30 bins with the line at 3 / 4 / 5 / 8 / 12: 2.31 / 2.34 / 2.32 / 2.42 / 2.47 ms.
+// points in 30 bins with the line at 3 / 4 / 5 / 8 / 12: 2.31 / 2.34 / 2.32 / 2.42 / 2.47 ms;
+// 50,000 x 50,000 points in 254 bins - / 1.09 / 1.08 / 1.26 / - ms.
 constexpr uint32_t kTableEdges64 = 5;
 constexpr uint32_t kOnes = 0x3F803F80u;     // two bf16 ones
 
@@ -158,6 +163,7 @@ struct BParams {
     uint32_t flush_every;                   // items between flushes, so that no 32-bit word can wrap
     int32_t max_edges, max_cells;           // of the launch's tables: LDS layout (max_cells 0: no table)
     int32_t cols;                           // lane columns of the histogram (power of two)
+    uint32_t table_edges;                   // edges from which a block goes through the table
     int32_t chunk;                          // work units taken from the queue at a time, at most
 };
 
@@ -613,7 +619,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
             if (part_bits == 4 && cbj != static_cast<int>(part)) np = 0u;
             const uint32_t m = np ? b - a : 0u;
             const bool near = !F64 && has_table && lo * lo < E_t * pow2(27u - tbl.shift);
-            const bool by_table = m && (near || (F64 ? m >= kTableEdges64 && has_table : m >= (GT ? kTableEdgesG : kTableEdges) && has_table && np == kG * kG && !on_diag));
+            const bool by_table = m && (near || m >= p.table_edges && has_table && (F64 || np == kG * kG && !on_diag));
             const bool in_range = lo * lo * (1.0f - 0x1p-18f) - E_t > tbl.lo && hi * hi * (1.0f + 0x1p-18f) + E_t < tbl.hi;
             blk[cbj * kN + cbi] = m ? a | (m << 16) | (on_diag ? kDiagBlock : 0u) | (by_table ? kTableBlock : 0u) | (near ? kNearBlock : 0u) | (by_table && in_range ? kInRange : 0u) : 0u;
             if (np && !by_table) add_row(h, K0 + a, np);
@@ -1108,21 +1114,32 @@ hipError_t launch_bounds(const ViewDesc *views, int n_views, int64_t tiles, hipS
 
 // ------------------------------------------------------------------ launch
 
-// The launch's LDS layout: the histogram's lane columns (at most `cols`, and
-// fewer for large edge sets) and whether the chord tables come along, so that
-// four workgroups fit a CU where that is possible (40 KB each; the largest edge
-// set, 1024 edges, takes 52 KB, under the 64 KB any kernel may have).
-void lds_layout(int32_t max_edges, int32_t max_cells, int32_t cols, int32_t *cols_out, int32_t *cells_out,
+// The launch's LDS layout: the histogram's lane columns (at most `cols`) and
+// whether the chord tables come along, so that four workgroups fit a CU where that
+// is possible (40 KB each; the largest edge set, 1024 edges, takes 52 KB, under the
+// 64 KB any kernel may have).  Beside a mixed launch's i-tile the tables come along
+// where they leave eight columns: with fewer, the adds that meet in one word cost
+// more than look-ups from the cache.  Whole calls of 100,000 x 100,000 points, table
+// in LDS / in global memory: 1.45 / 1.48 ms for 80 log bins (eight columns beside the
+// table), 2.37 / 1.68 for 100 (four), 5.1 / 1.92 for 125 (two), 11.5 / 2.31 for 150 (one).
+// Small calls take any column there is: the table in LDS spares them the ordering
+// (few_pairs, see run_batch).
+constexpr int32_t kLdsCols = 8;
+void lds_layout(bool fp64, bool few_pairs, int32_t max_edges, int32_t max_cells, int32_t cols, int32_t *cols_out, int32_t *cells_out,
                 uint32_t *lds_bytes) {
     auto bytes = [&](int32_t c, int32_t cells) { return static_cast<uint32_t>(8 * (max_edges + cells) + 4 * ((max_edges + 1) * c + max_edges)); };
-    static const uint32_t fixed = [] {
+    static const std::array<uint32_t, 2> fixed = [] {
         hipFuncAttributes a;
-        return hipFuncGetAttributes(&a, reinterpret_cast<const void *>(k_count_blocks<false, false>)) == hipSuccess
-                   ? static_cast<uint32_t>(a.sharedSizeBytes) : 36u * 1024u;
+        std::array<uint32_t, 2> f = {36u * 1024u, 36u * 1024u};
+        if (hipFuncGetAttributes(&a, reinterpret_cast<const void *>(k_count_blocks<false, false>)) == hipSuccess)
+            f[0] = static_cast<uint32_t>(a.sharedSizeBytes);
+        if (hipFuncGetAttributes(&a, reinterpret_cast<const void *>(k_count_blocks<false, true>)) == hipSuccess)
+            f[1] = static_cast<uint32_t>(a.sharedSizeBytes);
+        return f;
     }();
-    const uint32_t room = 40u * 1024u - std::min(fixed, 40u * 1024u);
+    const uint32_t room = 40u * 1024u - std::min(fixed[fp64], 40u * 1024u);
     int32_t c = 1;
-    if (bytes(c, max_cells) > room) max_cells = 0;
+    if (bytes(fp64 || few_pairs ? 1 : std::min(cols, kLdsCols), max_cells) > room) max_cells = 0;
     while (c < cols && bytes(2 * c, max_cells) <= room) c *= 2;
     *cols_out = c;
     *cells_out = max_cells;
@@ -1159,6 +1176,7 @@ hipError_t launch_count(bool fp64, bool global_table, const SegDesc *segs, const
     p.max_edges = max_edges;
     p.max_cells = max_cells;
     p.cols = cols;
+    p.table_edges = fp64 ? kTableEdges64 : global_table ? table_edges_global(cols) : kTableEdges;
     p.chunk = chunk;
     const auto k = fp64 ? (global_table ? k_count_blocks<true, true> : k_count_blocks<false, true>)
                         : (global_table ? k_count_blocks<true, false> : k_count_blocks<false, false>);
