@@ -55,6 +55,18 @@ int pc_debug_guard_band_gram(const double *theta_edges_deg, int32_t n_edges, flo
 int pc_debug_fused_band(const double *theta_edges_deg, int32_t n_edges, int32_t gram, float *h, float *w);
 
 /*
+ * pc_debug_chord_table -- the block kernel's chord table of an edge set (host
+ * only; Sec. 2.1 binning).
+ *   info   host int64[3], written: cells (0: the set has no table), the shift
+ *          from a binary32 chord's bits to its cell, the first cell's number.
+ *   cells  host uint32[2 * cells] or NULL, written when max_cells suffices: per
+ *          cell the bits of its edge (+inf: none) and the row below it.
+ * PC_ERR_INVALID for a NULL info or an invalid edge set.
+ */
+int pc_debug_chord_table(const double *theta_edges_deg, int32_t n_edges, int64_t *info, uint32_t *cells,
+                         int64_t max_cells);
+
+/*
  * pc_debug_set_timing -- on != 0: the calling thread's later counting calls
  * record HIP events around the counting kernel on the call's stream.
  */

@@ -88,6 +88,7 @@ _SIGNATURES = {
     "pc_autotune": ([_vp, _i32, _i32, ctypes.c_char_p, _vp, ctypes.c_char_p, _i32], ctypes.c_int),
     "pc_autotune_load": ([ctypes.c_char_p], ctypes.c_int),
     "pc_debug_lut32": ([_vp, _i32, _vp, _vp, _i64], ctypes.c_int),
+    "pc_debug_chord_table": ([_vp, _i32, _vp, _vp, _i64], ctypes.c_int),
     "pc_debug_set_timing": ([_i32], ctypes.c_int),
     "pc_debug_set_flush_every": ([_u64], ctypes.c_int),
     "pc_debug_set_compact_table": ([_i32], ctypes.c_int),
@@ -424,6 +425,18 @@ def pc_debug_lut32(theta_edges):
     _check(f(tp, t.size, info.ctypes.data, ent.ctypes.data, int(info[0])))
     keys = ["n_cells", "shift", "clamp_lo", "clamp_hi", "row_bytes", "cols", "multi", "_"]
     return dict(zip(keys, (int(v) for v in info))), ent
+
+
+def pc_debug_chord_table(theta_edges):
+    """The block kernel's chord table: (shift, first cell, edges float32, rows
+    uint32); empty arrays when the set has none."""
+    t, tp = _edges(theta_edges)
+    f = lib().pc_debug_chord_table
+    info = np.zeros(3, dtype=np.int64)
+    _check(f(tp, t.size, info.ctypes.data, None, 0))
+    cells = np.zeros((int(info[0]), 2), dtype=np.uint32)
+    _check(f(tp, t.size, info.ctypes.data, cells.ctypes.data, int(info[0])))
+    return int(info[1]), int(info[2]), cells[:, 0].copy().view(np.float32), cells[:, 1].copy()
 
 
 def pc_debug_set_timing(on: bool):

@@ -1413,6 +1413,21 @@ extern "C" int pc_debug_lut32(const double *theta_edges_deg, int32_t n_edges, in
     return PC_OK;
 }
 
+extern "C" int pc_debug_chord_table(const double *theta_edges_deg, int32_t n_edges, int64_t *info, uint32_t *cells,
+                                    int64_t max_cells) {
+    clear_error();
+    if (!theta_edges_deg || !info) return fail(PC_ERR_INVALID, "NULL argument");
+    HostTable t;
+    std::string err;
+    if (!build_table(theta_edges_deg, n_edges, t, err)) return fail(PC_ERR_INVALID, err);
+    info[0] = static_cast<int64_t>(t.lutb.size());
+    info[1] = t.b_shift;
+    info[2] = t.b_key0;
+    if (cells && static_cast<int64_t>(t.lutb.size()) <= max_cells && !t.lutb.empty())
+        memcpy(cells, t.lutb.data(), sizeof(LutEntryB) * t.lutb.size());
+    return PC_OK;
+}
+
 extern "C" int pc_debug_fused_band(const double *theta_edges_deg, int32_t n_edges, int32_t gram, float *h,
                                    float *w) {
     clear_error();

@@ -140,12 +140,13 @@ constexpr uint32_t kTableEdges = 3;
 // 9.58 / 9.68 / 9.88 / 10.3 / 10.9; four (150 and 200) 11.8 / 11.3 / 11.4 / 11.9 / 12.6 and
 // 15.3 / 14.2 / 14.3 / 14.9 / 16.1; two (254) 28.6 / 21.0 / 18.7 / 18.4 / 19.8, and 1M x 1M
 // points 115.2 / - / 103.0 / 102.8 / 105; one (300 bins, 100,000 x 100,000 points)
-// - / 10.0 / - / 4.70 / 4.15.
+// - / 10.0 / - / 4.70 / 4.15, in 500 bins - / - / - / 7.69 / 5.70 (without a table 19.2).
 constexpr uint32_t table_edges_global(int32_t cols) { return cols >= 4 ? 5u : cols == 2 ? 8u : 12u; }
 // The same in binary64, where an edge costs a pair a comparison: 100,000 + 100,000
 // points in 30 bins with the line at 3 / 4 / 5 / 8 / 12: 2.31 / 2.34 / 2.32 / 2.42 / 2.47 ms;
-// 50,000 x 50,000 points in 254 bins - / 1.09 / 1.08 / 1.26 / - ms.
-constexpr uint32_t kTableEdges64 = 5;
+// 50,000 x 50,000 points in 254 bins (eight columns) - / 1.09 / 1.08 / 1.26 / - ms, in
+// 400 (four) - / 1.57 / 1.46 / 1.32 / 1.54, in 500 (two) - / 2.01 / 1.93 / 1.83 / 1.59.
+constexpr uint32_t table_edges64(int32_t cols) { return cols >= 8 ? 5u : cols == 4 ? 8u : 12u; }
 constexpr uint32_t kOnes = 0x3F803F80u;     // two bf16 ones
 
 struct BParams {
@@ -1116,8 +1117,10 @@ hipError_t launch_bounds(const ViewDesc *views, int n_views, int64_t tiles, hipS
 
 // The launch's LDS layout: the histogram's lane columns (at most `cols`) and
 // whether the chord tables come along, so that four workgroups fit a CU where that
-// is possible (40 KB each; the largest edge set, 1024 edges, takes 52 KB, under the
-// 64 KB any kernel may have).  Beside a mixed launch's i-tile the tables come along
+// is possible, else three (40 or 53 KB each; the largest edge set, 1024 edges, takes
+// 52 KB, under the 64 KB any kernel may have).  500 log bins, which leave no room for
+// a column at four, take 15.6 ms for 200,000 x 200,000 points with three workgroups'
+// four columns, 18.8 with one.  Beside a mixed launch's i-tile the tables come along
 // where they leave eight columns: with fewer, the adds that meet in one word cost
 // more than look-ups from the cache.  Whole calls of 100,000 x 100,000 points, table
 // in LDS / in global memory: 1.45 / 1.48 ms for 80 log bins (eight columns beside the
@@ -1137,7 +1140,12 @@ void lds_layout(bool fp64, bool few_pairs, int32_t max_edges, int32_t max_cells,
             f[1] = static_cast<uint32_t>(a.sharedSizeBytes);
         return f;
     }();
-    const uint32_t room = 40u * 1024u - std::min(fixed[fp64], 40u * 1024u);
+    auto room_of = [&](uint32_t workgroups) {
+        const uint32_t each = 160u * 1024u / workgroups;
+        return each - std::min(fixed[fp64], each);
+    };
+    uint32_t room = room_of(4);
+    if (bytes(1, 0) > room) room = room_of(3);
     int32_t c = 1;
     if (bytes(fp64 || few_pairs ? 1 : std::min(cols, kLdsCols), max_cells) > room) max_cells = 0;
     while (c < cols && bytes(2 * c, max_cells) <= room) c *= 2;
@@ -1176,7 +1184,7 @@ hipError_t launch_count(bool fp64, bool global_table, const SegDesc *segs, const
     p.max_edges = max_edges;
     p.max_cells = max_cells;
     p.cols = cols;
-    p.table_edges = fp64 ? kTableEdges64 : global_table ? table_edges_global(cols) : kTableEdges;
+    p.table_edges = fp64 ? table_edges64(cols) : global_table ? table_edges_global(cols) : kTableEdges;
     p.chunk = chunk;
     const auto k = fp64 ? (global_table ? k_count_blocks<true, true> : k_count_blocks<false, true>)
                         : (global_table ? k_count_blocks<true, false> : k_count_blocks<false, false>);

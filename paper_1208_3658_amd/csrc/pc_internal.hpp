@@ -57,6 +57,10 @@ constexpr int kQueueStride = 16;
 constexpr int kQueueBase = kPruneStatBase + kPruneStripes * kPruneStripeWords;
 constexpr int kJPad = 16;               // readable points past the end of an ordered binary32 copy
 constexpr int kMaxLutCells = 1024;        // per table, 16 bytes each
+// Cells of the block kernel's chord table, 8 bytes each: with as many, every set
+// of even bins from 0 has one (1023 bins: 22.5k).  Larger tables are read from
+// global memory.
+constexpr int kMaxChordCells = 32768;
 constexpr uint32_t kLdsTarget = 16 * 1024;  // per-wave histogram bytes aimed for at most
 
 // Histogram layout in LDS: n_edges + 3 rows (under/overflow bins, one

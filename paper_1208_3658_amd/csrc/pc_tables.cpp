@@ -319,7 +319,7 @@ void build_lut32(const std::vector<float> &lo, const std::vector<float> &hi, uin
 // chord known to within E_t of its exact value, E_t <= q(c) / 2 (so E_t <= q(mn):
 // c < 2 mn), is then placed by its cell's edge alone unless it is within E_t of
 // that edge: any other edge is farther than E_t from it.  The coarsest S that leaves no cell with two edges,
-// within kMaxLutCells cells; none: no table.  One cell more at each end takes
+// within kMaxChordCells cells; none: no table.  One cell more at each end takes
 // the chords outside.
 void build_lutb(HostTable &t) {
     t.lutb.clear();
@@ -329,7 +329,7 @@ void build_lutb(HostTable &t) {
     if (first == n || (first > 0 && t.e64[first - 1] > 0.0)) return;
     for (int s = 22; s >= 12; --s) {
         const uint32_t c0 = (f2u(static_cast<float>(t.e64[first])) >> s) - 1, c1 = (f2u(static_cast<float>(t.e64[n - 1])) >> s) + 1;
-        if (c1 - c0 + 1 > static_cast<uint32_t>(kMaxLutCells)) return;
+        if (c1 - c0 + 1 > static_cast<uint32_t>(kMaxChordCells)) return;
         std::vector<LutEntryB> cells;
         bool ok = true;
         int below = first, above = first;  // edges under the cell's reach, edges not past it

@@ -20,7 +20,7 @@ def dev(c):
 
 
 @pytest.mark.parametrize("mode", [pc.PC_MIXED, pc.PC_FP64_PLAIN])
-@pytest.mark.parametrize("bins", [80, 90, 100, 125, 150, 200, 254, 400])
+@pytest.mark.parametrize("bins", [80, 90, 100, 125, 150, 200, 254, 400, 500, 700, 1000])
 def test_counts_match_the_oracle(bins, mode):
     rng = np.random.default_rng(bins)
     patch = synth.centred_patch(12.0)
