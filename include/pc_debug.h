@@ -67,6 +67,14 @@ int pc_debug_chord_table(const double *theta_edges_deg, int32_t n_edges, int64_t
                          int64_t max_cells);
 
 /*
+ * pc_debug_static_plan -- the bytes that a pc_count_batch_static call with these
+ * arguments would use of a fixed area of `bytes` bytes (more than `bytes`: it
+ * would be refused), planned on the host; no device is touched.
+ * PC_ERR_INVALID for a NULL need, bytes = 0 or arguments that call refuses.
+ */
+int pc_debug_static_plan(const pc_job *jobs, int32_t n_jobs, int32_t mode, uint64_t bytes, uint64_t *need);
+
+/*
  * pc_debug_set_timing -- on != 0: the calling thread's later counting calls
  * record HIP events around the counting kernel on the call's stream.
  */

@@ -88,6 +88,7 @@ _SIGNATURES = {
     "pc_autotune": ([_vp, _i32, _i32, ctypes.c_char_p, _vp, ctypes.c_char_p, _i32], ctypes.c_int),
     "pc_autotune_load": ([ctypes.c_char_p], ctypes.c_int),
     "pc_debug_lut32": ([_vp, _i32, _vp, _vp, _i64], ctypes.c_int),
+    "pc_debug_static_plan": ([ctypes.POINTER(pc_job), _i32, _i32, _u64, ctypes.POINTER(_u64)], ctypes.c_int),
     "pc_debug_chord_table": ([_vp, _i32, _vp, _vp, _i64], ctypes.c_int),
     "pc_debug_set_timing": ([_i32], ctypes.c_int),
     "pc_debug_set_flush_every": ([_u64], ctypes.c_int),
@@ -313,6 +314,21 @@ def pc_count_batch_static(jobs, mode: int = PC_MIXED, stream=None):
     arr, outs = _job_array(jobs, keep)
     _check(lib().pc_count_batch_static(arr, len(jobs), int(mode), _stream(stream)))
     return outs
+
+
+def pc_debug_static_plan(sizes, theta_edges, mode: int = PC_MIXED, nbytes: int = PC_STATIC_SCRATCH_BYTES) -> int:
+    """Bytes of a fixed area of `nbytes` that pc_count_batch_static would use
+    for the pairs of each of len(sizes) device catalogues of so many points
+    (host only, nothing is read)."""
+    t, tp = _edges(theta_edges)
+    cats = [pc_catalog(1 + q, 1, int(n), 1, 0) for q, n in enumerate(sizes)]
+    out = np.zeros(t.size + 1, dtype=np.uint64)
+    arr = (pc_job * len(cats))()
+    for q, c in enumerate(cats):
+        arr[q] = pc_job(ctypes.pointer(c), None, tp, t.size, 1, 0, -1, out.ctypes.data)
+    need = _u64(0)
+    _check(lib().pc_debug_static_plan(arr, len(cats), int(mode), int(nbytes), ctypes.byref(need)))
+    return need.value
 
 
 PC_BINS_EVEN, PC_BINS_LN, PC_BINS_LOG10 = 0, 1, 2

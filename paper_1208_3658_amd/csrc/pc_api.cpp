@@ -189,26 +189,28 @@ DevTable::~DevTable() {
     if (d_mem) (void)hipFree(d_mem);
 }
 
-void table_blob(const HostTable &h, TableBlob *out) {
-    // one device block: e64 | band | band_g | fband | fband_g | lut32 | lutc | lut64
+void table_blob(const HostTable &h, TableBlob *out, TableParts parts) {
+    // one device block: e64 | band | band_g | fband | fband_g | lut32 | lutc | lut64 | lutb
+    const bool vec = parts == kAllTables || parts == kMixedTables, vec64 = parts == kAllTables || parts == kFp64Table,
+               blk = parts == kAllTables || parts == kBlockTable;
     const size_t b_e = sizeof(double) * h.e64.size();
-    const size_t b_b = 2 * sizeof(float) * h.e64.size();
+    const size_t b_b = vec ? 2 * sizeof(float) * h.e64.size() : 0;
     out->o_band = (b_e + 255) & ~size_t(255);
     out->o_band_g = (out->o_band + b_b + 255) & ~size_t(255);
     out->o_fband = (out->o_band_g + b_b + 255) & ~size_t(255);
     out->o_fband_g = (out->o_fband + b_b + 255) & ~size_t(255);
     out->o_lut32 = (out->o_fband_g + b_b + 255) & ~size_t(255);
-    const size_t b_l32 = sizeof(LutEntry32) * h.lut32.entries.size();
+    const size_t b_l32 = vec ? sizeof(LutEntry32) * h.lut32.entries.size() : 0;
     out->o_lutc = (out->o_lut32 + b_l32 + 255) & ~size_t(255);
-    const size_t b_lc = sizeof(LutEntryC) * h.lut32.compact.size();
+    const size_t b_lc = vec ? sizeof(LutEntryC) * h.lut32.compact.size() : 0;
     out->o_lut64 = (out->o_lutc + b_lc + 255) & ~size_t(255);
-    const size_t b_l64 = sizeof(LutEntry64) * h.lut64.size();
+    const size_t b_l64 = vec64 ? sizeof(LutEntry64) * h.lut64.size() : 0;
     out->o_lutb = (out->o_lut64 + b_l64 + 255) & ~size_t(255);
-    const size_t b_lb = sizeof(LutEntryB) * h.lutb.size();
+    const size_t b_lb = blk ? sizeof(LutEntryB) * h.lutb.size() : 0;
     std::vector<unsigned char> &blob = out->bytes;
     blob.assign(out->o_lutb + b_lb + 256, 0);
     memcpy(blob.data(), h.e64.data(), b_e);
-    for (size_t k = 0; k < h.e64.size(); ++k) {
+    for (size_t k = 0; vec && k < h.e64.size(); ++k) {
         const float bb[4] = {h.lo[k], h.hi[k], h.lo_g[k], h.hi_g[k]};
         memcpy(blob.data() + out->o_band + 8 * k, bb, 8);
         memcpy(blob.data() + out->o_band_g + 8 * k, bb + 2, 8);
@@ -379,7 +381,9 @@ struct Workspace {
 struct Arena {
     size_t size = 0;
     size_t take(size_t bytes) {
-        const size_t o = (size_t(size) + 255) & ~size_t(255);
+        // a cache line; small pieces, of which a batch of small views has many, half
+        const size_t align = bytes >= 1024 ? 128 : 64;
+        const size_t o = (size + align - 1) & ~(align - 1);
         size = o + bytes;
         return o;
     }
@@ -415,6 +419,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     const LaunchTune *tune = opts.tune;
     const bool plan_only = opts.plan_bytes != nullptr;
     const bool ext = !plan_only && opts.ws != nullptr;  // caller's workspace: allocate nothing
+    const bool fixed = opts.ws_bytes > 0;               // run, or planned, for a workspace of that size
     if (jobs.empty()) return fail(PC_ERR_INVALID, "no jobs");
     const int mode = mode_flags & ~(PC_NO_PRUNE | PC_MATRIX_CORES | PC_TUNED);
     const bool prune = (mode_flags & PC_NO_PRUNE) == 0;
@@ -483,7 +488,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         const pc_catalog *c = nullptr;
         std::shared_ptr<Resident> res;
         int64_t n = 0;
-        size_t o_a64 = 0, o_ext = 0;
+        size_t o_a64 = 0;
         size_t at_ra = 0, at_dec = 0;  // host arrays: place in the call's host data, in doubles
     };
     std::vector<Source> srcs;
@@ -533,7 +538,9 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         int src = -1;
         int64_t b = 0, e = 0;
         bool resident_full = false;
-        size_t o_a64s = 0, o_a32s = 0, o_g32s = 0, o_bounds = 0, o_groups = 0, o_keys = 0;
+        size_t o_a64s = 0, o_a32s = 0, o_g32s = 0, o_bounds = 0, o_groups = 0;
+        // the ordering's scratch (see plan_order): keys in the region, first counter
+        size_t o_keys = 0;
         int64_t hist0 = 0;
         uint32_t buckets = 0;
     };
@@ -557,11 +564,10 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
             v.resident_full = true;
         } else if (n > 0) {
             v.o_a64s = ar.take(sizeof(double4) * static_cast<size_t>(n));
-            // binary32 copies padded: the kernel reads a step of j-points ahead
+            // binary32 copies padded: the vector kernels read a step of j-points ahead
             if (need_a32) v.o_a32s = ar.take(sizeof(float4) * static_cast<size_t>(n + kJPad));
-            if (need_g32) v.o_g32s = ar.take(sizeof(float4) * static_cast<size_t>(n + kJPad));
+            if (need_g32) v.o_g32s = ar.take(sizeof(float4) * static_cast<size_t>(blocks ? n : n + kJPad));
             v.o_bounds = ar.take(sizeof(double4) * static_cast<size_t>(n_tiles(n, tile) * (1 + T.subs)));
-            if (blocks && !fp64) v.o_keys = ar.take(sizeof(uint32_t) * static_cast<size_t>(n));
             if (blocks) v.o_groups = ar.take(sizeof(float4) * static_cast<size_t>(n_tiles(n, tile) * kGroups));
         }
         const int id = static_cast<int>(views.size());
@@ -603,12 +609,12 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
             auto it = local_tab.find(key);
             if (it == local_tab.end()) {
                 auto t = std::make_shared<DevTable>();
-                if (ext) {
+                if (fixed) {
                     std::string err;
                     if (!build_table(j.theta, j.n_edges, t->host, err, fp64 ? 0 : lt.cols))
                         return fail(PC_ERR_INVALID, err);
                     blobs.emplace_back();
-                    table_blob(t->host, &blobs.back());
+                    table_blob(t->host, &blobs.back(), blocks ? kBlockTable : fp64 ? kFp64Table : kMixedTables);
                 }
                 it = local_tab.emplace(std::move(key), static_cast<int>(tabs.size())).first;
                 tabs.push_back(t);
@@ -661,8 +667,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     // and the ordering counters follow the results: zeroed by one launch
     const size_t count_words = res_words - kMetaWords;
     const size_t o_pcopies = ar.take(sizeof(unsigned long long) * kPruneStripes * count_words);
-    for (Source &sc : srcs)
-        if (!sc.res) sc.o_ext = ar.take(sizeof(uint32_t) * kExtWords);
+    const size_t o_ext = ar.take(sizeof(uint32_t) * kExtWords * srcs.size());
 
     // ---- segments
     std::vector<SegDesc> segs;
@@ -718,38 +723,90 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     // (mixed mode); their descriptions sit beside the survivors
     // (block kernel: the survivors' tiles do)
     const bool split = prune && (blocks || (PC_SPLIT && !fp64));
-    // the ordering's counters (and keys, where the ordered copies take more
-    // room) are done with when the prune pass writes the survivors: one region
-    // holds the one, then the other
-    int64_t hist_words = 0;
-    size_t order_bytes = 0;
-    for (View &v : views) {
-        if (v.resident_full || v.e <= v.b) continue;
-        v.hist0 = hist_words;
-        v.buckets = order_buckets(v.e - v.b, prune ? 4 : 2);
-        hist_words += v.buckets;
-    }
-    order_bytes = sizeof(uint32_t) * static_cast<size_t>(hist_words);
-    for (View &v : views) {
-        if (v.resident_full || v.e <= v.b || (blocks && !fp64)) continue;
-        v.o_keys = order_bytes;  // from the region's start
-        order_bytes += sizeof(uint32_t) * static_cast<size_t>((v.e - v.b + 63) & ~int64_t(63));
-    }
     // (mixed mode: 16 bytes per pair of 256-point tiles also where the block
     // kernel's larger tiles leave a quarter of them)
     const uint64_t slots = std::max<uint64_t>(prune ? (blocks && fp64 ? items : std::max(items, limit_items)) : 1, 1);
-    const size_t surv_bytes = sizeof(uint64_t) * slots;
-    const size_t o_region = ar.take(std::max(order_bytes, surv_bytes * (split ? 2 : 1)));
-    const size_t o_surv = o_region, o_sub = o_region + surv_bytes;
-    const size_t zero_bytes = (o_region - o_res + sizeof(uint32_t) * static_cast<size_t>(hist_words) + 15) & ~size_t(15);
-    const size_t o_sums = ar.take(sizeof(uint32_t) * std::max<size_t>(scan_sums_words(hist_words), 4));
+    const size_t surv_bytes = sizeof(uint64_t) * slots, surv_region = surv_bytes * (split ? 2 : 1);
+    // The ordering's counters, and the keys where no ordered copy has room for
+    // them until it is written, are done with when the prune pass writes the
+    // survivors: one region holds the one, then the other.  Views are ordered
+    // together in rounds of as many as fit `cap` bytes (a view by itself may
+    // take more, but where `limited`, a workspace that would not hold it,
+    // it gets fewer counters and a coarser order).
+    struct OrderRound {
+        size_t first = 0, count = 0;  // of the views to order
+        int64_t words = 0, blocks = 0;
+    };
+    std::vector<OrderRound> rounds;
+    constexpr size_t kOrderBytes = size_t(64) << 20;
+    auto plan_order = [&](size_t cap, bool limited) -> size_t {
+        rounds.clear();
+        size_t most = 0, used = 0, place = 0;
+        for (View &v : views) {
+            if (v.resident_full || v.e <= v.b) continue;
+            const size_t keys = need_g32 ? 0 : sizeof(uint32_t) * static_cast<size_t>((v.e - v.b + 3) & ~int64_t(3));
+            v.buckets = order_buckets(v.e - v.b, prune ? 4 : 2);
+            if (limited && keys + sizeof(uint32_t) * v.buckets > cap)
+                v.buckets = std::max<uint32_t>(kMinBuckets, cap > keys ? static_cast<uint32_t>((cap - keys) / sizeof(uint32_t)) & ~3u : 0u);
+            const size_t need = keys + sizeof(uint32_t) * v.buckets;
+            if (rounds.empty() || used + need > cap) {
+                rounds.push_back(OrderRound());
+                rounds.back().first = place;
+                used = 0;
+            }
+            OrderRound &r = rounds.back();
+            v.hist0 = r.words;
+            v.o_keys = used - sizeof(uint32_t) * static_cast<size_t>(r.words);  // behind the round's counters
+            r.words += v.buckets;
+            ++r.count;
+            ++place;
+            used += need;
+            most = std::max(most, used);
+        }
+        return most;
+    };
     // descriptors, sent with one copy: sources | views | segments | tables
     // (written in whole 16-byte words, see launch_zero_put)
-    const size_t b_srcs = sizeof(SrcDesc) * srcs.size(), b_views = sizeof(ViewDesc) * views.size(),
+    size_t to_convert = 0, to_order = 0;
+    for (const Source &sc : srcs) to_convert += !sc.res && sc.n > 0 ? 1 : 0;
+    for (const View &v : views) to_order += !v.resident_full && v.e > v.b ? 1 : 0;
+    const size_t b_srcs = sizeof(SrcDesc) * to_convert, b_views = sizeof(ViewDesc) * to_order,
                  b_segs = sizeof(SegDesc) * segs.size(), b_tabs = sizeof(TableDesc) * tabs.size();
-    const size_t o_desc = ar.take((b_srcs + b_views + b_segs + b_tabs + 15) & ~size_t(15));
+    const size_t before_region = ar.size;
+    size_t o_region = 0, o_sums = 0, o_desc = 0, order_bytes = 0;
+    int64_t hist_words = 0;  // the largest round's
     std::vector<size_t> o_blob(blobs.size());
-    for (size_t k = 0; k < blobs.size(); ++k) o_blob[k] = ar.take(blobs[k].bytes.size());
+    auto place_rest = [&](size_t cap, bool limited) {
+        ar.size = before_region;
+        order_bytes = plan_order(cap, limited);
+        hist_words = 0;
+        for (const OrderRound &r : rounds) hist_words = std::max(hist_words, r.words);
+        o_region = ar.take(std::max(order_bytes, surv_region));
+        o_sums = ar.take(sizeof(uint32_t) * std::max<size_t>(scan_sums_words(hist_words), 4));
+        o_desc = ar.take((b_srcs + b_views + b_segs + b_tabs + 15) & ~size_t(15));
+        for (size_t k = 0; k < blobs.size(); ++k) o_blob[k] = ar.take(blobs[k].bytes.size());
+    };
+    place_rest(std::max(kOrderBytes, surv_region), false);
+    if (fixed && ar.size > opts.ws_bytes) {
+        // a workspace that does not hold this: more rounds, and if they do not
+        // help no chord tables (they are the larger ones of dense edge sets)
+        auto fit = [&] {
+            const size_t others = ar.size - std::max(order_bytes, surv_region);
+            place_rest(std::max(surv_region, opts.ws_bytes > others ? (opts.ws_bytes - others) & ~size_t(127) : 0), true);
+            return ar.size <= opts.ws_bytes;
+        };
+        if (!fit() && blocks) {
+            for (size_t k = 0; k < blobs.size(); ++k) {
+                tabs[k]->host.lutb.clear();
+                table_blob(tabs[k]->host, &blobs[k], kBlockTable);
+            }
+            place_rest(std::max(kOrderBytes, surv_region), false);
+            if (ar.size > opts.ws_bytes) fit();
+        }
+    }
+    const size_t o_surv = o_region, o_sub = o_region + surv_bytes;
+    const int64_t first_words = rounds.empty() ? 0 : rounds[0].words;
+    const size_t zero_bytes = (o_region - o_res + sizeof(uint32_t) * static_cast<size_t>(first_words) + 15) & ~size_t(15);
     if (plan_only) {
         *opts.plan_bytes = ar.size;
         return PC_OK;
@@ -799,7 +856,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         }
         const pc_catalog *c = srcs[k].c;
         src_a64[k] = reinterpret_cast<const double4 *>(W + srcs[k].o_a64);
-        src_ext[k] = reinterpret_cast<const uint32_t *>(W + srcs[k].o_ext);
+        src_ext[k] = reinterpret_cast<const uint32_t *>(W + o_ext) + k * kExtWords;
         if (c->n <= 0) continue;
         SrcDesc d;
         d.ra = c->ra_deg;
@@ -818,7 +875,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         }
         d.a64 = reinterpret_cast<double4 *>(W + srcs[k].o_a64);
         d.err = reinterpret_cast<int *>(W + o_err) + k;
-        d.ext = reinterpret_cast<uint32_t *>(W + srcs[k].o_ext);
+        d.ext = reinterpret_cast<uint32_t *>(W + o_ext) + k * kExtWords;
         d.n = c->n;
         d.blk0 = conv_blocks;
         conv_blocks += convert_blocks(c->n);
@@ -863,8 +920,9 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         ordered = !all || max_cells == 0 || pairs > kUnorderedPairs;
     }
     std::vector<ViewDesc> vds;
-    int64_t ord_blocks = 0, all_tiles = 0;
-    uint32_t points = 0;
+    int64_t all_tiles = 0;
+    uint32_t points = 0;  // of the round's views so far
+    size_t round = 0;
     for (size_t v = 0; v < views.size(); ++v) {
         const View &vw = views[v];
         if (vw.resident_full) {
@@ -882,23 +940,29 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         ViewDesc d;
         d.src = src_a64[vw.src] + vw.b;
         d.ext = src_ext[vw.src];
-        d.keys = reinterpret_cast<uint32_t *>(W + (blocks && !fp64 ? 0 : o_region) + vw.o_keys);
+        if (vds.size() == rounds[round].first + rounds[round].count) {
+            ++round;
+            points = 0;
+        }
         d.hist = reinterpret_cast<uint32_t *>(W + o_region) + vw.hist0;
         // (read only where the order is the caller's)
         d.a64s = ordered ? reinterpret_cast<double4 *>(W + vw.o_a64s) : const_cast<double4 *>(d.src);
         d.a32s = need_a32 ? reinterpret_cast<float4 *>(W + vw.o_a32s) : nullptr;
         d.g32s = need_g32 ? reinterpret_cast<float4 *>(W + vw.o_g32s) : nullptr;
-        d.slots = reinterpret_cast<uint32_t *>(d.g32s);  // done with when the bounds step writes there
+        // (done with when the bounds step writes the Gram form)
+        d.slots = reinterpret_cast<uint32_t *>(d.g32s);
+        d.keys = need_g32 ? d.slots + n
+                          : reinterpret_cast<uint32_t *>(W + o_region + sizeof(uint32_t) * static_cast<size_t>(rounds[round].words) + vw.o_keys);
         d.bounds = reinterpret_cast<double4 *>(W + vw.o_bounds);
         d.groups = blocks ? reinterpret_cast<float4 *>(W + vw.o_groups) : nullptr;
         d.n = n;
         d.hist0 = vw.hist0;
-        d.blk0 = ord_blocks;
+        d.blk0 = rounds[round].blocks;
         d.tile0 = all_tiles;
         d.tiles = n_tiles(n, tile);
         d.buckets = vw.buckets;
         d.points0 = points;
-        ord_blocks += order_blocks(n);
+        rounds[round].blocks += order_blocks(n);
         all_tiles += d.tiles;
         points += static_cast<uint32_t>(n);
         vds.push_back(d);
@@ -996,11 +1060,14 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     const SrcDesc *d_srcs = reinterpret_cast<const SrcDesc *>(W + o_desc);
     const ViewDesc *d_views = reinterpret_cast<const ViewDesc *>(W + o_desc + b_srcs);
     PC_HIP(launch_convert(d_srcs, static_cast<int>(sds.size()), conv_blocks, st), "convert");
-    if (ordered)
-        PC_HIP(launch_order(d_views, static_cast<int>(vds.size()), ord_blocks,
-                            reinterpret_cast<uint32_t *>(W + o_region), hist_words,
+    for (const OrderRound &r : rounds) {
+        if (!ordered) break;
+        uint32_t *const hist = reinterpret_cast<uint32_t *>(W + o_region);
+        if (r.first > 0) PC_HIP(launch_zero(hist, sizeof(uint32_t) * static_cast<size_t>(r.words), st), "zero counters");
+        PC_HIP(launch_order(d_views + r.first, static_cast<int>(r.count), r.blocks, hist, r.words,
                             reinterpret_cast<uint32_t *>(W + o_sums), st),
                "order");
+    }
     PC_HIP(T.launch_bounds(d_views, static_cast<int>(vds.size()), all_tiles, st), "bounds");
     unsigned long long *meta = reinterpret_cast<unsigned long long *>(W + o_meta);
 
@@ -1411,6 +1478,19 @@ extern "C" int pc_debug_lut32(const double *theta_edges_deg, int32_t n_edges, in
     if (entries && static_cast<int64_t>(L.entries.size()) <= max_cells)
         memcpy(entries, L.entries.data(), sizeof(LutEntry32) * L.entries.size());
     return PC_OK;
+}
+
+extern "C" int pc_debug_static_plan(const pc_job *jobs, int32_t n_jobs, int32_t mode, uint64_t bytes,
+                                    uint64_t *need) {
+    clear_error();
+    if (!need || bytes == 0) return fail(PC_ERR_INVALID, "need is NULL or bytes is 0");
+    std::vector<BatchJob> v;
+    const int rc = jobs_from_abi(jobs, n_jobs, &v);
+    if (rc) return rc;
+    BatchOpts o;
+    o.plan_bytes = need;
+    o.ws_bytes = bytes;
+    return run_batch_opts(v, mode, nullptr, nullptr, o);
 }
 
 extern "C" int pc_debug_chord_table(const double *theta_edges_deg, int32_t n_edges, int64_t *info, uint32_t *cells,

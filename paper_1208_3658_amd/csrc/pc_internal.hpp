@@ -47,6 +47,9 @@ constexpr int kPruneStripes = 16;
 // order (see run_batch)
 constexpr double kUnorderedPairs = 16777216.0;
 
+// ordering counters of a view, at least
+constexpr uint32_t kMinBuckets = 8;
+
 // descriptors up to this size go to the device as a kernel's arguments
 constexpr size_t kPutBytes = 2048;
 constexpr int kPruneStripeWords = 16;

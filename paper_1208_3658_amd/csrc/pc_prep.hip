@@ -409,9 +409,9 @@ __global__ void __launch_bounds__(256) k_zero_put(uint4 *p, int64_t n4, uint4 *d
 }
 
 // Ordering counters of a view of n points (a multiple of 4; at least one per
-// face).
+// face of the cube).
 uint32_t order_buckets(int64_t n, int per_point) {
-    const int64_t m = std::min<int64_t>(std::max<int64_t>(per_point * n, 256), int64_t(1) << 26);
+    const int64_t m = std::min<int64_t>(std::max<int64_t>(per_point * n, kMinBuckets), int64_t(1) << 26);
     return static_cast<uint32_t>((m + 3) & ~int64_t(3));
 }
 

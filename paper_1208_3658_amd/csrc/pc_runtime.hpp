@@ -51,12 +51,14 @@ struct DevTable {
 int get_table(const double *theta, int32_t n_edges, std::shared_ptr<DevTable> *out, int cols = 0);
 
 // A table's device image: e64 | band | band_g | fband | fband_g | lut32 |
-// lutc | lut64 at the offsets below (256-byte aligned), built on the host.
+// lutc | lut64 | lutb at the offsets below (256-byte aligned), built on the host;
+// of one launch the parts that its kernel reads.
+enum TableParts { kAllTables, kBlockTable, kMixedTables, kFp64Table };
 struct TableBlob {
     std::vector<unsigned char> bytes;
     size_t o_band = 0, o_band_g = 0, o_fband = 0, o_fband_g = 0, o_lut32 = 0, o_lutc = 0, o_lut64 = 0, o_lutb = 0;
 };
-void table_blob(const HostTable &h, TableBlob *out);
+void table_blob(const HostTable &h, TableBlob *out, TableParts parts = kAllTables);
 // points t's device pointers into a copy of the blob at `base` (t does not own it)
 void table_place(DevTable *t, const TableBlob &b, unsigned char *base);
 
@@ -142,7 +144,8 @@ int run_batch(const std::vector<BatchJob> &jobs, int mode, hipStream_t st, Batch
 //    the batch needs more than ws_bytes (nothing is launched then).
 //  * plan_bytes: only plan -- write the workspace bytes the batch needs
 //    (tables excluded; they are cached per device) and return, with no device
-//    call.  Catalogue arguments are validated as for a real run.
+//    call.  Catalogue arguments are validated as for a real run.  With ws_bytes
+//    the plan is the one for a workspace of that size, tables included.
 //  * trusted_inputs: the host catalogues were already checked point by point
 //    (finite RA, |Dec| <= 90); only their shape is checked here.
 //  * plan_sizes (planning only): resident-catalogue handles that need not
