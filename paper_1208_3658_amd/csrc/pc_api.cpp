@@ -539,7 +539,8 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         int64_t b = 0, e = 0;
         bool resident_full = false;
         size_t o_a64s = 0, o_a32s = 0, o_g32s = 0, o_bounds = 0, o_groups = 0;
-        // the ordering's scratch (see plan_order): keys in the region, first counter
+        // the ordering's scratch (see plan_order): keys, of their own or from the
+        // region's counters on, first counter
         size_t o_keys = 0;
         int64_t hist0 = 0;
         uint32_t buckets = 0;
@@ -549,6 +550,10 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     // which ordered forms the launch's kernels read: plain binary32 (vector
     // paths), tile-centred Gram form (pruned mixed launches)
     const bool need_a32 = !fp64 && !blocks, need_g32 = prune && !fp64;
+    // the ordering's keys: in the Gram form's place where a workspace is tight
+    // (beside the points' places, both done with when the form is written), of
+    // their own otherwise, or in the ordering's region where there is no Gram form
+    const bool own_keys = need_g32 && blocks && !fixed;
     auto add_view = [&](int src, int64_t b, int64_t e) -> int {
         auto key = std::make_tuple(src, b, e);
         auto it = view_of.find(key);
@@ -567,6 +572,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
             // binary32 copies padded: the vector kernels read a step of j-points ahead
             if (need_a32) v.o_a32s = ar.take(sizeof(float4) * static_cast<size_t>(n + kJPad));
             if (need_g32) v.o_g32s = ar.take(sizeof(float4) * static_cast<size_t>(blocks ? n : n + kJPad));
+            if (own_keys) v.o_keys = ar.take(sizeof(uint32_t) * static_cast<size_t>(n));
             v.o_bounds = ar.take(sizeof(double4) * static_cast<size_t>(n_tiles(n, tile) * (1 + T.subs)));
             if (blocks) v.o_groups = ar.take(sizeof(float4) * static_cast<size_t>(n_tiles(n, tile) * kGroups));
         }
@@ -756,7 +762,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
             }
             OrderRound &r = rounds.back();
             v.hist0 = r.words;
-            v.o_keys = used - sizeof(uint32_t) * static_cast<size_t>(r.words);  // behind the round's counters
+            if (!need_g32) v.o_keys = used - sizeof(uint32_t) * static_cast<size_t>(r.words);  // behind the round's counters
             r.words += v.buckets;
             ++r.count;
             ++place;
@@ -951,8 +957,9 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         d.g32s = need_g32 ? reinterpret_cast<float4 *>(W + vw.o_g32s) : nullptr;
         // (done with when the bounds step writes the Gram form)
         d.slots = reinterpret_cast<uint32_t *>(d.g32s);
-        d.keys = need_g32 ? d.slots + n
-                          : reinterpret_cast<uint32_t *>(W + o_region + sizeof(uint32_t) * static_cast<size_t>(rounds[round].words) + vw.o_keys);
+        d.keys = own_keys   ? reinterpret_cast<uint32_t *>(W + vw.o_keys)
+                 : need_g32 ? d.slots + n
+                            : reinterpret_cast<uint32_t *>(W + o_region + sizeof(uint32_t) * static_cast<size_t>(rounds[round].words) + vw.o_keys);
         d.bounds = reinterpret_cast<double4 *>(W + vw.o_bounds);
         d.groups = blocks ? reinterpret_cast<float4 *>(W + vw.o_groups) : nullptr;
         d.n = n;
