@@ -75,6 +75,12 @@ int pc_debug_chord_table(const double *theta_edges_deg, int32_t n_edges, int64_t
 int pc_debug_static_plan(const pc_job *jobs, int32_t n_jobs, int32_t mode, uint64_t bytes, uint64_t *need);
 
 /*
+ * pc_debug_last_workspace -- the calling thread's last counting launch: bytes of
+ * device workspace it allocated, or used of the fixed area.  PC_ERR_INVALID for NULL.
+ */
+int pc_debug_last_workspace(uint64_t *bytes);
+
+/*
  * pc_debug_set_timing -- on != 0: the calling thread's later counting calls
  * record HIP events around the counting kernel on the call's stream.
  */

@@ -89,6 +89,7 @@ _SIGNATURES = {
     "pc_autotune_load": ([ctypes.c_char_p], ctypes.c_int),
     "pc_debug_lut32": ([_vp, _i32, _vp, _vp, _i64], ctypes.c_int),
     "pc_debug_static_plan": ([ctypes.POINTER(pc_job), _i32, _i32, _u64, ctypes.POINTER(_u64)], ctypes.c_int),
+    "pc_debug_last_workspace": ([ctypes.POINTER(_u64)], ctypes.c_int),
     "pc_debug_chord_table": ([_vp, _i32, _vp, _vp, _i64], ctypes.c_int),
     "pc_debug_set_timing": ([_i32], ctypes.c_int),
     "pc_debug_set_flush_every": ([_u64], ctypes.c_int),
@@ -441,6 +442,12 @@ def pc_debug_lut32(theta_edges):
     _check(f(tp, t.size, info.ctypes.data, ent.ctypes.data, int(info[0])))
     keys = ["n_cells", "shift", "clamp_lo", "clamp_hi", "row_bytes", "cols", "multi", "_"]
     return dict(zip(keys, (int(v) for v in info))), ent
+
+
+def pc_debug_last_workspace() -> int:
+    v = _u64(0)
+    _check(lib().pc_debug_last_workspace(ctypes.byref(v)))
+    return v.value
 
 
 def pc_debug_chord_table(theta_edges):

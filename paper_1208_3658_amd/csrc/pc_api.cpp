@@ -729,9 +729,13 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     // (mixed mode); their descriptions sit beside the survivors
     // (block kernel: the survivors' tiles do)
     const bool split = prune && (blocks || (PC_SPLIT && !fp64));
-    // (mixed mode: 16 bytes per pair of 256-point tiles also where the block
-    // kernel's larger tiles leave a quarter of them)
-    const uint64_t slots = std::max<uint64_t>(prune ? (blocks && fp64 ? items : std::max(items, limit_items)) : 1, 1);
+    // The survivors.  A mixed plan, and a fixed workspace, count 16 bytes per pair of
+    // 256-point tiles, what the vector kernels need, so that admission and the
+    // fixed area's limit are the same whichever kernel runs; the block kernel
+    // writes 16 per pair of 512-point tiles, and an ordinary call allocates only
+    // those (4M x 8M points: 2.0 GB instead of 7.8).
+    const bool as_vector = !blocks || (!fp64 && (plan_only || fixed));
+    const uint64_t slots = std::max<uint64_t>(!prune ? 1 : as_vector ? std::max(items, limit_items) : items, 1);
     const size_t surv_bytes = sizeof(uint64_t) * slots, surv_region = surv_bytes * (split ? 2 : 1);
     // The ordering's counters, and the keys where no ordered copy has room for
     // them until it is written, are done with when the prune pass writes the
@@ -1484,6 +1488,13 @@ extern "C" int pc_debug_lut32(const double *theta_edges_deg, int32_t n_edges, in
     info[7] = 0;
     if (entries && static_cast<int64_t>(L.entries.size()) <= max_cells)
         memcpy(entries, L.entries.data(), sizeof(LutEntry32) * L.entries.size());
+    return PC_OK;
+}
+
+extern "C" int pc_debug_last_workspace(uint64_t *bytes) {
+    clear_error();
+    if (!bytes) return fail(PC_ERR_INVALID, "bytes is NULL");
+    *bytes = t_last.workspace_bytes;
     return PC_OK;
 }
 

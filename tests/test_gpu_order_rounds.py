@@ -36,3 +36,13 @@ def test_many_views(count, n, mode, static):
         assert g.tolist() == w.tolist(), k
     for k in (0, count // 2, count - 1):
         assert got[k].tolist() == oracle.count(cats[k], E).tolist(), k
+
+
+def test_an_ordinary_call_allocates_the_survivors_it_can_write():
+    """300,000 x 300,000 points: 32 bytes a point converted, 53 ordered, 16 for the
+    ordering's counters, whose place the survivors of 586 x 586 pairs of 512-point
+    tiles take (16 bytes each, 5.5 MB; 22 MB for pairs of 256-point tiles)."""
+    cats, devs = catalogues(2, 300_000)
+    got = pc.pc_count(devs[0], E, B=devs[1], auto=False)
+    assert pc.pc_debug_last_workspace() < 102 * 600_000
+    assert got.tolist() == pc.pc_count_ex(devs[0], E, B=devs[1], auto=False, mode=pc.PC_FP64_PLAIN).tolist()
