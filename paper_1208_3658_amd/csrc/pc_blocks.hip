@@ -416,6 +416,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
     __shared__ Pending pend;
     __shared__ uint64_t sh_next[2];
     __shared__ unsigned long long sh_stat[6]; // pairs by edges (1, 2, 3, more), items with open, with few-edge blocks
+    __shared__ uint32_t sh_item;              // the item has open blocks (1), blocks of a few edges (2)
     const int tid0 = static_cast<int>(threadIdx.x);
     const int wave = static_cast<int>(uni(threadIdx.x / kWave));
 
@@ -454,7 +455,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
         for (int s = 0; s < kPruneStripes; ++s) v += p.copies[s * p.count_words + w];
         if (v) atomicAdd(p.counts + w, v);
     }
-    if (tid0 == 0) pend.n = 0u;
+    if (tid0 == 0) pend.n = sh_item = 0u;
 
     for (;; ++wi) {
         // opaque per item: addresses made from it are recomputed rather than
@@ -495,7 +496,8 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
         const uint32_t part = static_cast<uint32_t>(wi) & ((1u << part_bits) - 1u);
         const int first_col = part_bits == 0 ? wave : part_bits == 2 ? static_cast<int>(part) * kWaves + wave : static_cast<int>(part);
         const uint32_t rows = part_bits == 4 ? 0xFu << (4 * wave) : kColMask;
-        // the wave that classifies the unit's blocks (all do their own where a unit is a whole survivor)
+        // the wave that classifies the unit's blocks (all do their own where a unit is a whole survivor; in a
+        // survivor's first unit the others look at the rest, for its statistics)
         const bool classifies = part_bits == 0 || wave == static_cast<int>(part_bits == 2 ? part : part >> 2);
         const uint64_t w0 = ld_uniform(p.items + (wi >> part_bits)), w1 = ld_uniform(p.tiles + (wi >> part_bits));
         const uint32_t seg = static_cast<uint32_t>(w0);
@@ -599,7 +601,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
         }
         // ---- classification of the wave's 64 blocks
         const float E_t = (E + 0x1p-23f * (7.0f * Dl * Dl + (Dl + R) * (Dl + R))) * (1.0f + 0x1p-16f);
-        if (classifies) {
+        if (classifies || part == 0) {
             const float vx = fx + (si.x - sj.x), vy = fy + (si.y - sj.y), vz = fz + (si.z - sj.z);
             const float d = __builtin_amdgcn_sqrtf(fmaf(vx, vx, fmaf(vy, vy, vz * vz)));
             // outward: 12 u (D + R) covers the roundings above
@@ -617,14 +619,18 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
             uint32_t np = static_cast<uint32_t>(ni * nj);
             const bool on_diag = diag && cbi == cbj;
             if (diag && cbi >= cbj) np = on_diag ? static_cast<uint32_t>(ni * (ni - 1) / 2) : 0u;
-            if (part_bits == 4 && cbj != static_cast<int>(part)) np = 0u;
+            if (part == 0) {
+                const uint32_t m = np ? b - a : 0u;
+                const uint64_t any = __builtin_amdgcn_ballot_w64(m != 0u), few = __builtin_amdgcn_ballot_w64(m - 1u < 3u);
+                if (lane == 0 && any) atomicOr(&sh_item, few ? 3u : 1u);
+            }
+            if (!classifies || (part_bits == 4 && cbj != static_cast<int>(part))) np = 0u;
             const uint32_t m = np ? b - a : 0u;
             const bool near = !F64 && has_table && lo * lo < E_t * pow2(27u - tbl.shift);
             const bool by_table = m && (near || m >= p.table_edges && has_table && (F64 || np == kG * kG && !on_diag));
             const bool in_range = lo * lo * (1.0f - 0x1p-18f) - E_t > tbl.lo && hi * hi * (1.0f + 0x1p-18f) + E_t < tbl.hi;
             blk[cbj * kN + cbi] = m ? a | (m << 16) | (on_diag ? kDiagBlock : 0u) | (by_table ? kTableBlock : 0u) | (near ? kNearBlock : 0u) | (by_table && in_range ? kInRange : 0u) : 0u;
             if (np && !by_table) add_row(h, K0 + a, np);
-            const uint64_t any = __builtin_amdgcn_ballot_w64(m != 0u);
             const bool full = !diag && i_lim == kT && j_lim == kT && part_bits != 4;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -636,11 +642,13 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
                 }
                 if (lane == 0 && v) atomicAdd(sh_stat + k, static_cast<unsigned long long>(v));
             }
-            const uint64_t few = __builtin_amdgcn_ballot_w64(m - 1u < 3u);
-            if (tid == 0 && part == 0 && any) atomicAdd(sh_stat + 4, 1ull);
-            if (tid == 0 && part == 0 && few) atomicAdd(sh_stat + 5, 1ull);
         }
         __syncthreads();
+        if (tid == 0 && sh_item) {
+            sh_stat[4] += 1ull;
+            sh_stat[5] += sh_item >> 1;
+            sh_item = 0u;
+        }
 
         // ---- the wave's columns of blocks; lane k holds the threshold of edge K0 + k
         const float h_lane = static_cast<float>(e_lds[min(K0 + static_cast<uint32_t>(lane), static_cast<uint32_t>(h.n_edges - 1))] + h_off);
@@ -1011,7 +1019,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
     if ((tid0 & (kWave - 1)) == 0 && seen) atomicAdd(p.rechecked, static_cast<unsigned long long>(seen));
     __syncthreads();
     const unsigned long long pairs = sh_stat[0] + sh_stat[1] + sh_stat[2] + sh_stat[3];
-    if (tid0 == 0 && pairs) {
+    if (tid0 == 0 && (pairs | sh_stat[4])) {
         unsigned long long *st = p.stats + (blockIdx.x % kPruneStripes) * kPruneStripeWords;
         atomicAdd(st + 1, pairs);
         atomicAdd(st + 10, pairs);
