@@ -75,6 +75,17 @@ int pc_debug_chord_table(const double *theta_edges_deg, int32_t n_edges, int64_t
 int pc_debug_static_plan(const pc_job *jobs, int32_t n_jobs, int32_t mode, uint64_t bytes, uint64_t *need);
 
 /*
+ * pc_debug_set_order -- whether the calling thread's later block kernel launches
+ * put their catalogues into spatial order: 0 as they choose (calls of few pairs
+ * do not), 1 always, -1 only where an edge set's chord table does not fit into
+ * LDS.  Counts do not depend on it.  PC_ERR_INVALID for other values.
+ * pc_debug_last_ordered -- whether the calling thread's last counting launch did
+ * (0 also where all its catalogues are resident).  PC_ERR_INVALID for NULL.
+ */
+int pc_debug_set_order(int32_t mode);
+int pc_debug_last_ordered(int32_t *ordered);
+
+/*
  * pc_debug_last_workspace -- the calling thread's last counting launch: bytes of
  * device workspace it allocated, or used of the fixed area.  PC_ERR_INVALID for NULL.
  */

@@ -90,6 +90,8 @@ _SIGNATURES = {
     "pc_debug_lut32": ([_vp, _i32, _vp, _vp, _i64], ctypes.c_int),
     "pc_debug_static_plan": ([ctypes.POINTER(pc_job), _i32, _i32, _u64, ctypes.POINTER(_u64)], ctypes.c_int),
     "pc_debug_last_workspace": ([ctypes.POINTER(_u64)], ctypes.c_int),
+    "pc_debug_set_order": ([_i32], ctypes.c_int),
+    "pc_debug_last_ordered": ([ctypes.POINTER(_i32)], ctypes.c_int),
     "pc_debug_chord_table": ([_vp, _i32, _vp, _vp, _i64], ctypes.c_int),
     "pc_debug_set_timing": ([_i32], ctypes.c_int),
     "pc_debug_set_flush_every": ([_u64], ctypes.c_int),
@@ -442,6 +444,18 @@ def pc_debug_lut32(theta_edges):
     _check(f(tp, t.size, info.ctypes.data, ent.ctypes.data, int(info[0])))
     keys = ["n_cells", "shift", "clamp_lo", "clamp_hi", "row_bytes", "cols", "multi", "_"]
     return dict(zip(keys, (int(v) for v in info))), ent
+
+
+def pc_debug_set_order(mode: int):
+    """1: block kernel launches always order their catalogues, -1: only where a
+    chord table does not fit into LDS, 0: as they choose."""
+    _check(lib().pc_debug_set_order(int(mode)))
+
+
+def pc_debug_last_ordered() -> bool:
+    v = _i32(0)
+    _check(lib().pc_debug_last_ordered(ctypes.byref(v)))
+    return bool(v.value)
 
 
 def pc_debug_last_workspace() -> int:

@@ -405,6 +405,9 @@ static thread_local uint64_t t_flush_cap = 0;
 static thread_local int t_compact_mode = 0;
 // per-thread tile size for launches without explicit parameters (testing; 0: as chosen)
 static thread_local int t_force_tile = 0;
+// spatial ordering of the block kernel's launches: 0 as chosen, 1 always, -1
+// only where a chord table does not fit into LDS (testing)
+static thread_local int t_order = 0;
 static thread_local BatchStats t_last;
 
 int run_batch(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_t st, BatchStats *stats,
@@ -918,7 +921,8 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         const bool any = max_cells > 0;
         double pairs = 0.0;
         for (const SegDesc &sd : segs) pairs += static_cast<double>(sd.ni) * static_cast<double>(sd.nj) * (sd.tri ? 0.5 : 1.0);
-        blk::lds_layout(fp64, pairs <= kUnorderedPairs, max_edges, max_cells, lt.cols ? std::min(lt.cols, 16) : 16, &bcols, &max_cells, &blocks_lds);
+        const bool few_pairs = t_order ? t_order < 0 : pairs <= kUnorderedPairs;
+        blk::lds_layout(fp64, few_pairs, max_edges, max_cells, lt.cols ? std::min(lt.cols, 16) : 16, &bcols, &max_cells, &blocks_lds);
         // Few pairs are counted in the caller's order: unordered groups prune
         // nothing and put every block through the chord table (hence only with
         // one), but the four ordering launches cost more than that.  Whole
@@ -927,7 +931,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         // 156 / 144 for 8192 x 8192 in bins of all scales, but 131 / 136 where the
         // bins end at 2 degrees and the order lets most pairs go.
         global_table = any && max_cells == 0;
-        ordered = !all || max_cells == 0 || pairs > kUnorderedPairs;
+        ordered = !all || max_cells == 0 || !few_pairs;
     }
     std::vector<ViewDesc> vds;
     int64_t all_tiles = 0;
@@ -1181,6 +1185,7 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     }
     t_last.pairs_mfma = prune ? ps[11] : 0;
     t_last.workspace_bytes = ar.size;
+    t_last.ordered = ordered && !vds.empty();
     if (t_timing && !ext && items > 0) {
         float ms = 0.0f;
         PC_HIP(hipEventElapsedTime(&ms, t_ev0, t_ev1), "hipEventElapsedTime");
@@ -1560,6 +1565,20 @@ extern "C" int pc_debug_set_tile(int32_t tile) {
     clear_error();
     if (tile != 0 && tile != 128 && tile != 256) return fail(PC_ERR_INVALID, "tile must be 0, 128 or 256");
     t_force_tile = tile;
+    return PC_OK;
+}
+
+extern "C" int pc_debug_set_order(int32_t mode) {
+    clear_error();
+    if (mode < -1 || mode > 1) return fail(PC_ERR_INVALID, "mode must be -1, 0 or 1");
+    t_order = mode;
+    return PC_OK;
+}
+
+extern "C" int pc_debug_last_ordered(int32_t *ordered) {
+    clear_error();
+    if (!ordered) return fail(PC_ERR_INVALID, "ordered is NULL");
+    *ordered = t_last.ordered ? 1 : 0;
     return PC_OK;
 }
 

@@ -116,6 +116,7 @@ struct BatchStats {
     uint64_t pairs_gram = 0;      // of the few-edge pairs, chords in tile-centred Gram form
     uint64_t pairs_mfma = 0;      // pairs on the matrix cores
     uint64_t workspace_bytes = 0; // device workspace of the launch
+    bool ordered = false;         // the launch put catalogues into spatial order
 };
 
 // Launch parameters a tuner may choose (all give the same counts):
