@@ -758,9 +758,11 @@ const float4 *filter_table() {
     return tab;
 }
 
-// The same in the current device's memory, uploaded once.
+// The same in the current device's memory, uploaded once, on the stream of the
+// call that comes first (the legacy stream may not be used while another thread
+// captures a graph) and waited for, so that every stream may read it.
 __device__ float4 g_filter[kQCells + 1];
-int device_filter(int device, const float4 **out) {
+int device_filter(int device, hipStream_t st, const float4 **out) {
     static std::mutex lock;
     static std::vector<const float4 *> ready;
     std::lock_guard<std::mutex> hold(lock);
@@ -768,7 +770,8 @@ int device_filter(int device, const float4 **out) {
     if (!ready[device]) {
         void *d = nullptr;
         AP_HIP(hipGetSymbolAddress(&d, HIP_SYMBOL(g_filter)), "filter table's address");
-        AP_HIP(hipMemcpy(d, filter_table(), sizeof(float4) * (kQCells + 1), hipMemcpyHostToDevice), "H2D filter table");
+        AP_HIP(hipMemcpyAsync(d, filter_table(), sizeof(float4) * (kQCells + 1), hipMemcpyHostToDevice, st), "H2D filter table");
+        AP_HIP(hipStreamSynchronize(st), "hipStreamSynchronize");
         ready[device] = static_cast<const float4 *>(d);
     }
     *out = ready[device];
@@ -1020,7 +1023,7 @@ extern "C" int pc_aperture_mass(const pc_shear_catalog *cat, const pc_grid *grid
     uint32_t *sums = reinterpret_cast<uint32_t *>(base + o_sums);
     unsigned long long *meta = reinterpret_cast<unsigned long long *>(base + o_meta);
     const float4 *qtab = nullptr;
-    rc = device_filter(di->device, &qtab);
+    rc = device_filter(di->device, st, &qtab);
     if (rc) return rc;
 
     // order the galaxies by cell
