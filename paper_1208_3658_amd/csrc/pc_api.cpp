@@ -430,12 +430,17 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     const bool fp64 = mode == PC_FP64_PLAIN;
     // launch parameters: explicit, tuned for this shape (PC_TUNED), or defaults
     LaunchTune lt;
+    bool vector_tuned = false;
     if (tune) {
         lt = *tune;
     } else if (mode_flags & PC_TUNED) {
         TuneEntry te;
-        if (tune_lookup(tune_key_of(jobs), &te) == PC_OK) lt = te.tune;
-        else lt.matrix_cores = (mode_flags & PC_MATRIX_CORES) != 0;
+        if (tune_lookup(tune_key_of(jobs), &te) == PC_OK) {
+            lt = te.tune;
+            vector_tuned = !te.blocks;
+        } else {
+            lt.matrix_cores = (mode_flags & PC_MATRIX_CORES) != 0;
+        }
     } else {
         lt.matrix_cores = (mode_flags & PC_MATRIX_CORES) != 0;
     }
@@ -451,6 +456,13 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     // kernels stay for 128-point tiles, for visiting every pair, for
     // PC_MATRIX_CORES and for binary64.
     const bool blocks = prune && !mc && lt.tile != 128 && !lt.vector;
+    // columns and chunk that were chosen for the vector kernel say nothing about
+    // this one (four columns, a choice for large edge sets there, take 3.15 ms for
+    // 300,000 x 400,000 points in 24 bins, its own sixteen 1.59)
+    if (blocks && vector_tuned) {
+        lt.cols = LaunchTune().cols;
+        lt.chunk = LaunchTune().chunk;
+    }
     const TileOps &T = blocks ? kTileBlocks : lt.tile == 128 ? kTile128 : kTile256;
     const int tile = T.tile;
     // host-side validation first, so bad arguments are reported as such

@@ -173,6 +173,7 @@ struct TuneKey {
 };
 struct TuneEntry {
     LaunchTune tune;
+    bool blocks = false;     // cols and chunk were timed on the block kernel
     double kernel_ms = 0.0;  // counting kernel (HIP events)
     double launch_ms = 0.0;  // the whole launch (host clock)
 };

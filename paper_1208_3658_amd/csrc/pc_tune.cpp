@@ -88,9 +88,9 @@ std::string entry_json(const TuneKey &k, const TuneEntry &e) {
     char buf[512];
     snprintf(buf, sizeof(buf),
              "{\"device\": \"%s\", \"edges_class\": %d, \"pairs_class\": %d, \"tile\": %d, \"cols\": %d, "
-             "\"chunk\": %d, \"matrix_cores\": %d, \"kernel_ms\": %.4f, \"launch_ms\": %.4f}",
+             "\"chunk\": %d, \"matrix_cores\": %d, \"kernel\": \"%s\", \"kernel_ms\": %.4f, \"launch_ms\": %.4f}",
              k.device.c_str(), k.edges_class, k.pairs_class, e.tune.tile, e.tune.cols, e.tune.chunk,
-             e.tune.matrix_cores ? 1 : 0, e.kernel_ms, e.launch_ms);
+             e.tune.matrix_cores ? 1 : 0, e.blocks ? "blocks" : "vector", e.kernel_ms, e.launch_ms);
     return buf;
 }
 
@@ -157,6 +157,8 @@ int parse_file(const char *path, std::map<TuneKey, TuneEntry> *out) {
         ok = ok && field(line, "matrix_cores", &v) && to_int(v, &mc);
         if (ok && field(line, "kernel_ms", &v)) e.kernel_ms = atof(v.c_str());
         if (ok && field(line, "launch_ms", &v)) e.launch_ms = atof(v.c_str());
+        // (entries without it were timed on the vector kernel)
+        if (ok && field(line, "kernel", &v)) e.blocks = v == "blocks";
         // entries written before the tile size was tuned mean 256-point tiles
         if (ok && field(line, "tile", &v)) ok = to_int(v, &e.tune.tile) && (e.tune.tile == 128 || e.tune.tile == 256);
         const bool cols_ok = e.tune.cols == 0 || (e.tune.cols >= 4 && e.tune.cols <= 64 &&
@@ -315,6 +317,7 @@ extern "C" int pc_autotune(const pc_job *jobs, int32_t n_jobs, int32_t mode, con
     }
     TuneEntry e;
     e.tune = cands[static_cast<size_t>(best)];
+    e.blocks = prune && e.tune.tile != 128 && !e.tune.matrix_cores;
     e.kernel_ms = best_ms;
     e.launch_ms = best_lms;
     const TuneKey key = tune_key_of(v);
