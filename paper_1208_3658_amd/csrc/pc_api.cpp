@@ -53,7 +53,7 @@ namespace t256 { PC_TILE_STEPS }
 // the block kernel (pc_blocks.hip)
 namespace blk {
 hipError_t launch_bounds(const ViewDesc *views, int n_views, int64_t tiles, hipStream_t st);
-void lds_layout(bool fp64, bool few_pairs, int32_t max_edges, int32_t max_cells, int32_t cols, int32_t *cols_out, int32_t *cells_out,
+void lds_layout(bool fp64, bool few_pairs, double edges_met, int32_t max_edges, int32_t max_cells, int32_t cols, int32_t *cols_out, int32_t *cells_out,
                 uint32_t *lds_bytes);
 hipError_t occupancy(bool fp64, bool global_table, uint32_t lds_bytes, int *per_cu);
 hipError_t launch_count(bool fp64, bool global_table, const SegDesc *segs, const TableDesc *tabs, const uint64_t *items, const uint64_t *tiles,
@@ -931,10 +931,20 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
             all = all && !t->host.lutb.empty();
         }
         const bool any = max_cells > 0;
-        double pairs = 0.0;
-        for (const SegDesc &sd : segs) pairs += static_cast<double>(sd.ni) * static_cast<double>(sd.nj) * (sd.tri ? 0.5 : 1.0);
+        // The pairs, and over them the mean of the edges that a block meets: its
+        // size, of 32 points, over the last bin's width, if the catalogues fill a
+        // field about as wide as the last edge (their extent is not on the host).
+        double pairs = 0.0, edges_met = 0.0;
+        for (const SegDesc &sd : segs) {
+            const double ni = static_cast<double>(sd.ni), nj = static_cast<double>(sd.nj), p = ni * nj * (sd.tri ? 0.5 : 1.0);
+            const std::vector<double> &e = tabs[static_cast<size_t>(sd.tab)]->host.e64;
+            const double last = std::sqrt(e[e.size() - 1]);
+            pairs += p;
+            edges_met += p * std::sqrt(kGroup / std::sqrt(ni * nj)) * last / (last - std::sqrt(e[e.size() - 2]));
+        }
+        edges_met /= std::max(pairs, 1.0);
         const bool few_pairs = t_order ? t_order < 0 : pairs <= kUnorderedPairs;
-        blk::lds_layout(fp64, few_pairs, max_edges, max_cells, lt.cols ? std::min(lt.cols, 16) : 16, &bcols, &max_cells, &blocks_lds);
+        blk::lds_layout(fp64, few_pairs, edges_met, max_edges, max_cells, lt.cols ? std::min(lt.cols, 16) : 16, &bcols, &max_cells, &blocks_lds);
         // Few pairs are counted in the caller's order: unordered groups prune
         // nothing and put every block through the chord table (hence only with
         // one), but the four ordering launches cost more than that.  Whole

@@ -132,8 +132,10 @@ constexpr uint32_t kNearBlock = 1u << 29;   // with kTableBlock: chords from dif
 // the same half add and minimum per pair, the table nine instructions and two
 // LDS accesses per pair whatever their number.  Counting kernel with the line at
 // 3 / 4 / 5 / 6: 1.63 / 1.68 / 1.67 / 1.77 ms for 300,000 x 400,000 points, 13.8 / 14.0 /
-// 14.6 / 15.1 ms for 64 mocks, 22.5 / 22.6 / 22.7 / 23.0 ms on the 1M workload.
-constexpr uint32_t kTableEdges = 3;
+// 14.6 / 15.1 ms for 64 mocks, 22.5 / 22.6 / 22.7 / 23.0 ms on the 1M workload.  With
+// eight lane columns the line lies at 4: 18.9 / 17.2 / 17.7 ms at 3 / 4 / 5 for 300,000 x
+// 300,000 points in 254 bins.
+constexpr uint32_t table_edges(int32_t cols) { return cols >= 16 ? 3u : 4u; }
 // The same with the table in global memory, by the histogram's lane columns: the
 // fewer there are, the more of 64 lanes' adds meet in one word.  Whole calls with the
 // line at 4 / 5 / 6 / 8 / 12, ms: eight columns (125 log bins, 300,000 x 300,000 points)
@@ -1124,20 +1126,28 @@ hipError_t launch_bounds(const ViewDesc *views, int n_views, int64_t tiles, hipS
 // ------------------------------------------------------------------ launch
 
 // The launch's LDS layout: the histogram's lane columns (at most `cols`) and
-// whether the chord tables come along, so that four workgroups fit a CU where that
-// is possible, else three (40 or 53 KB each; the largest edge set, 1024 edges, takes
-// 52 KB, under the 64 KB any kernel may have).  500 log bins, which leave no room for
-// a column at four, take 15.6 ms for 200,000 x 200,000 points with three workgroups'
-// four columns, 18.8 with one.  Beside a mixed launch's i-tile the tables come along
-// where they leave eight columns: with fewer, the adds that meet in one word cost
-// more than look-ups from the cache.  Whole calls of 100,000 x 100,000 points, table
-// in LDS / in global memory: 1.45 / 1.48 ms for 80 log bins (eight columns beside the
-// table), 2.37 / 1.68 for 100 (four), 5.1 / 1.92 for 125 (two), 11.5 / 2.31 for 150 (one).
+// whether the chord tables come along.
+// Four workgroups share a CU where that is possible, else three (40 or 53 KB each;
+// the largest edge set, 1024 edges, takes 52 KB, under the 64 KB any kernel may
+// have): 500 log bins, which leave no room for a column at four, take 15.6 ms for
+// 200,000 x 200,000 points with three workgroups' four columns, 18.8 with one.
+// Beside a mixed launch's i-tile the tables come along where they leave eight
+// columns: with fewer, the adds that meet in one word cost more than look-ups from
+// the cache.  Whole calls of 100,000 x 100,000 points, table in LDS / in global memory:
+// 1.45 / 1.48 ms for 80 log bins (eight columns beside the table), 2.37 / 1.68 for 100
+// (four), 5.1 / 1.92 for 125 (two), 11.5 / 2.31 for 150 (one).
+// Where most blocks go through the table three workgroups with it are better than
+// four without.  edges_met tells (see run_batch): four without / three with, ms, at
+// 0.13 (254 bins, 1M x 1M) 103 / 110, 0.14 (100, 300,000 x 300,000) 8.13 / 8.65, 0.17 (125)
+// 9.68 / 9.96, 0.20 (150) 11.3 / 11.1, 0.27 (200) 14.2 / 13.2, 0.34 (254) 18.4 / 17.2, 0.65
+// (200 over 1.5 decades, 250,000 x 125,000) 8.98 / 6.62; even bins: 0.46 (45) 8.03 / 7.13,
+// 1.03 (100) 10.7 / 7.47.
 // Small calls take any column there is: the table in LDS spares them the ordering
 // (few_pairs, see run_batch).
 constexpr int32_t kLdsCols = 8;
-void lds_layout(bool fp64, bool few_pairs, int32_t max_edges, int32_t max_cells, int32_t cols, int32_t *cols_out, int32_t *cells_out,
-                uint32_t *lds_bytes) {
+constexpr double kEdgesMet = 0.2;
+void lds_layout(bool fp64, bool few_pairs, double edges_met, int32_t max_edges, int32_t max_cells, int32_t cols,
+                int32_t *cols_out, int32_t *cells_out, uint32_t *lds_bytes) {
     auto bytes = [&](int32_t c, int32_t cells) { return static_cast<uint32_t>(8 * (max_edges + cells) + 4 * ((max_edges + 1) * c + max_edges)); };
     static const std::array<uint32_t, 2> fixed = [] {
         hipFuncAttributes a;
@@ -1155,15 +1165,18 @@ void lds_layout(bool fp64, bool few_pairs, int32_t max_edges, int32_t max_cells,
     uint32_t room = room_of(4);
     if (bytes(1, 0) > room) room = room_of(3);
     int32_t c = 1;
-    if (bytes(fp64 || few_pairs ? 1 : std::min(cols, kLdsCols), max_cells) > room) max_cells = 0;
+    const int32_t least = fp64 || few_pairs ? 1 : std::min(cols, kLdsCols);
+    if (max_cells > 0 && bytes(least, max_cells) > room) {
+        if (!fp64 && !few_pairs && edges_met >= kEdgesMet && bytes(least, max_cells) <= room_of(3)) room = room_of(3);
+        else max_cells = 0;
+    }
     while (c < cols && bytes(2 * c, max_cells) <= room) c *= 2;
     *cols_out = c;
     *cells_out = max_cells;
     *lds_bytes = bytes(c, max_cells);
 }
 
-// (global_table: the sets' chord tables do not fit into LDS at four workgroups a
-// CU; three workgroups with them took 115 ms where this takes 103)
+// (global_table: the sets' chord tables are not in LDS)
 hipError_t occupancy(bool fp64, bool global_table, uint32_t lds_bytes, int *per_cu) {
     const auto k = fp64 ? (global_table ? k_count_blocks<true, true> : k_count_blocks<false, true>)
                         : (global_table ? k_count_blocks<true, false> : k_count_blocks<false, false>);
@@ -1192,7 +1205,7 @@ hipError_t launch_count(bool fp64, bool global_table, const SegDesc *segs, const
     p.max_edges = max_edges;
     p.max_cells = max_cells;
     p.cols = cols;
-    p.table_edges = fp64 ? table_edges64(cols) : global_table ? table_edges_global(cols) : kTableEdges;
+    p.table_edges = fp64 ? table_edges64(cols) : global_table ? table_edges_global(cols) : table_edges(cols);
     p.chunk = chunk;
     const auto k = fp64 ? (global_table ? k_count_blocks<true, true> : k_count_blocks<false, true>)
                         : (global_table ? k_count_blocks<true, false> : k_count_blocks<false, false>);
