@@ -144,11 +144,12 @@ constexpr uint32_t table_edges(int32_t cols) { return cols >= 16 ? 3u : 4u; }
 // points 115.2 / - / 103.0 / 102.8 / 105; one (300 bins, 100,000 x 100,000 points)
 // - / 10.0 / - / 4.70 / 4.15, in 500 bins - / - / - / 7.69 / 5.70 (without a table 19.2).
 constexpr uint32_t table_edges_global(int32_t cols) { return cols >= 4 ? 5u : cols == 2 ? 8u : 12u; }
-// The same in binary64, where an edge costs a pair a comparison: 100,000 + 100,000
-// points in 30 bins with the line at 3 / 4 / 5 / 8 / 12: 2.31 / 2.34 / 2.32 / 2.42 / 2.47 ms;
-// 50,000 x 50,000 points in 254 bins (eight columns) - / 1.09 / 1.08 / 1.26 / - ms, in
-// 400 (four) - / 1.57 / 1.46 / 1.32 / 1.54, in 500 (two) - / 2.01 / 1.93 / 1.83 / 1.59.
-constexpr uint32_t table_edges64(int32_t cols) { return cols >= 8 ? 5u : cols == 4 ? 8u : 12u; }
+// The same in binary64, where an edge costs a pair a comparison: whole calls with the
+// line at 3 / 4 / 5 / 8 / 12, ms: 125,000 + 250,000 points in 40 even bins (sixteen
+// columns) 7.77 / 7.69 / 8.60 / - / -, 100,000 in 30 log bins 0.667 / 0.680 / 0.693 / - / -;
+// 50,000 x 50,000 points in 254 bins (eight columns) - / 1.09 / 1.08 / 1.26 / -, in 400
+// (four) - / 1.57 / 1.46 / 1.32 / 1.54, in 500 (two) - / 2.01 / 1.93 / 1.83 / 1.59.
+constexpr uint32_t table_edges64(int32_t cols) { return cols >= 16 ? 3u : cols == 8 ? 5u : cols == 4 ? 8u : 12u; }
 constexpr uint32_t kOnes = 0x3F803F80u;     // two bf16 ones
 
 struct BParams {
@@ -723,12 +724,15 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
                             }
                         }
                     }
+                    uint32_t none = 0;  // the lane's pairs that are none: below every edge
                     if ((key & kDiagBlock) || (bi + 1) * kG > i_lim || (cb + 1) * kG > j_lim) {
-                        // pairs that are none lie below every edge
 #pragma unroll
                         for (int v = 0; v < 16; ++v) {
                             const int i = bi * kG + li + 8 * (v >> 2), j = cb * kG + lj + 8 * (v & 3);
-                            if (i >= i_lim || j >= j_lim || ((key & kDiagBlock) && i >= j)) c[v] = -1.0;
+                            if (i >= i_lim || j >= j_lim || ((key & kDiagBlock) && i >= j)) {
+                                c[v] = -1.0;
+                                ++none;
+                            }
                         }
                     }
                     if (key & kTableBlock) {
@@ -747,7 +751,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
                             for (int v = 0; v < kLook; ++v) {
                                 const float d = __uint_as_float(e[v].x) - x[v];
                                 at[v] = row_offset(tbl, e[v], d);
-                                add_offset(at[v] + column, c[q + v] >= 0.0 ? 1u : 0u);
+                                add_offset(at[v] + column, 1u);
                                 // x and the edge are rounded to binary32: within 2^-22 x the chord itself decides
                                 least = fminf(least, fmaf(-0x1p-22f, x[v], fabsf(d)));
                             }
@@ -755,7 +759,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
 #pragma unroll
                                 for (int v = 0; v < kLook; ++v) {
                                     const float d = __uint_as_float(e[v].x) - x[v];
-                                    if (fmaf(-0x1p-22f, x[v], fabsf(d)) <= 0x1p-120f && c[q + v] >= 0.0) {
+                                    if (fmaf(-0x1p-22f, x[v], fabsf(d)) <= 0x1p-120f) {
                                         const uint32_t row = (e[v].y + (c[q + v] >= e_lds[e[v].y] ? 1u : 0u)) << tbl.row_shift;
                                         if (row != at[v]) {
                                             add_offset(row + column, 1u);
@@ -764,6 +768,10 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
                                     }
                                 }
                             }
+                        }
+                        if (none) {
+                            const u32x2 e = cell_of<GT, true>(tbl, -1.0f);
+                            add_offset(row_offset(tbl, e, __uint_as_float(e.x) + 1.0f) + column, 0u - none);
                         }
                         continue;
                     }
