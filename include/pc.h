@@ -262,9 +262,10 @@ const char *pc_version(void);
 /* ------------------------------------------------------------ residency */
 
 /*
- * pc_catalog_upload -- convert a catalogue once (RA/Dec -> binary64 and
- * binary32 unit vectors in caller order and in a spatially ordered copy with
- * its tile bounds, about 112 bytes per point) and keep it resident on the
+ * pc_catalog_upload -- convert a catalogue once (RA/Dec -> binary64 unit
+ * vectors in caller order, and a spatially ordered copy in binary64, binary32
+ * and tile-centred form for both tile sizes, with its tile bounds, about 113
+ * bytes per point) and keep it resident on the
  * current device.  *handle receives a nonzero id.  Paper Sec. 2.1: positions
  * are copied to GPU global memory once and reused for every submatrix.
  */

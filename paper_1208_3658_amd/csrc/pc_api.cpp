@@ -452,9 +452,9 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     // the matrix-core path needs the prune pass's marks; binary32 only
     if (lt.tile != 0 && lt.tile != 128 && lt.tile != 256) return fail(PC_ERR_INVALID, "tile must be 128 or 256 points");
     const bool mc = lt.matrix_cores && prune && !fp64 && lt.tile != 128;
-    // the block kernel runs the mixed mode's pruned launches.  The vector
-    // kernels stay for 128-point tiles, for visiting every pair, for
-    // PC_MATRIX_CORES and for binary64.
+    // the block kernel runs the pruned launches, mixed and binary64.  The vector
+    // kernels stay for 128-point tiles, for visiting every pair and for
+    // PC_MATRIX_CORES.
     const bool blocks = prune && !mc && lt.tile != 128 && !lt.vector;
     // columns and chunk that were chosen for the vector kernel say nothing about
     // this one (four columns, a choice for large edge sets there, take 3.15 ms for
@@ -830,8 +830,6 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         }
     }
     const size_t o_surv = o_region, o_sub = o_region + surv_bytes;
-    const int64_t first_words = rounds.empty() ? 0 : rounds[0].words;
-    const size_t zero_bytes = (o_region - o_res + sizeof(uint32_t) * static_cast<size_t>(first_words) + 15) & ~size_t(15);
     if (plan_only) {
         *opts.plan_bytes = ar.size;
         return PC_OK;
@@ -951,7 +949,9 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
         // calls, ordered / caller's order: 100 / 79 us for the pairs of 1003
         // points, 111 / 95 of 4096, 123 / 110 of 6000; 122 / 108 for 4096 x 4096,
         // 156 / 144 for 8192 x 8192 in bins of all scales, but 131 / 136 where the
-        // bins end at 2 degrees and the order lets most pairs go.
+        // bins end at 2 degrees and the order lets most pairs go.  In binary64 110 / 79
+        // for 1003 points, 115 / 90 for 4096, 127 / 101 for 4096 x 4096, 158 / 140 for 8192
+        // x 8192, 129 / 137 with bins to 2 degrees: the same line.
         global_table = any && max_cells == 0;
         ordered = !all || max_cells == 0 || !few_pairs;
     }
@@ -1088,6 +1088,9 @@ int run_batch_opts(const std::vector<BatchJob> &jobs, int mode_flags, hipStream_
     put(b_srcs, vds.data(), sizeof(ViewDesc) * vds.size());
     put(b_srcs + b_views, segs.data(), b_segs);
     put(b_srcs + b_views + b_segs, tds.data(), b_tabs);
+    // (the counters of the ordering's first round too, where there is one)
+    const int64_t first_words = ordered && !rounds.empty() ? rounds[0].words : 0;
+    const size_t zero_bytes = (o_region - o_res + sizeof(uint32_t) * static_cast<size_t>(first_words) + 15) & ~size_t(15);
     if (desc.size() <= kPutBytes) {
         PC_HIP(launch_zero_put(W + o_res, zero_bytes, W + o_desc, desc.data(), desc.size(), st), "zero results");
     } else {

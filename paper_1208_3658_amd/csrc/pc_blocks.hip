@@ -14,8 +14,8 @@
 //     other, with the column's 32 j-points in registers;
 //   * an open block is four v_mfma_f32_16x16x32_bf16, each giving
 //     d = h - c for 256 pairs (c the squared chord, h the threshold of the
-//     block's first edge); the sign of d is the count, and d within a proven
-//     width of 0 sends the pair to binary64.
+//     block's first edge); the sign of d is the count, and d within a bounded
+//     width of 0 (see below) sends the pair to binary64.
 //
 // Chords.  With o_I, o_J the tiles' sphere centres, D = o_I - o_J, and the
 // points centred on their own tile (a' = RN32(a - o_I), b' = RN32(b - o_J)),
@@ -66,9 +66,11 @@
 //   * a higher edge of the block, d_t = RN(d + RN(h_t - h)): <= u (8 D R + 2 R^2)
 // in all below u (80 D R + 45 R^2).  E = u R (88 D + 50 R) + 2^-48 (D + R)^2 +
 // 2^-110 lies 10% above that; its second term covers the binary64 steps and the
-// binary64 chord itself (5 v c), the third underflow.  With h = e + E: d < 0
-// proves the binary64 chord at or above e, d > W = 2E proves it below, and 0 <=
-// d <= W is recomputed in binary64 in the reference's order.  Measured against
+// binary64 chord itself (5 v c), the third underflow.  All of it is proven but the
+// product's term, which allows three times the largest error measured of a sum
+// whose order is not documented.  Given that, with h = e + E, d < 0 shows the
+// binary64 chord at or above e, d > W = 2E shows it below, and 0 <= d <= W is
+// recomputed in binary64 in the reference's order.  Measured against
 // binary64 over tile pairs of catalogues of 1003 to 1M points: at most 0.05 E;
 // 2.7 u (D + R)^2 at most and 0.05 to 0.17 in the mean square, where the vector
 // kernel's forms have 28 and 0.5 to 2.2 (differences), 2.8 and 0.23 to 0.76

@@ -1026,7 +1026,12 @@ hipError_t launch_prune(const SegDesc *segs, int32_t n_segs, const TableDesc *ta
                         int32_t split_ok, bool blocks, hipStream_t st) {
     if (total_rows <= 0) return hipSuccess;
     if (total_rows > 0x7FFFFFFF) return hipErrorInvalidValue;
+#if PC_R == 4
     const auto k = blocks ? k_prune<true> : k_prune<false>;
+#else
+    if (blocks) return hipErrorInvalidValue;  // the block kernel's pass is in the 256-point build
+    const auto k = k_prune<false>;
+#endif
     k<<<dim3(static_cast<uint32_t>(total_rows)), dim3(kPruneThreads), 0, st>>>(segs, n_segs, tabs, survivors, sub, meta,
                                                                                 mfma_ok, split_ok);
     return hipGetLastError();
