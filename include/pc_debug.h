@@ -178,8 +178,11 @@ int pc_debug_last_pruning(uint64_t *survivors, uint64_t *pairs_computed, uint64_
  *                   binary64 kernel and of launches with PC_NO_PRUNE) or, in the
  *                   block kernel, in blocks of more than 3 edges.
  *   gram_pairs      of the few-edge pairs, those whose chords the vector path
- *                   forms in tile-centred Gram form (NULL allowed).
- *   mfma_pairs      pairs whose chords came from the matrix cores (NULL allowed).
+ *                   forms in tile-centred Gram form (0 in the block kernel; NULL
+ *                   allowed).
+ *   mfma_pairs      pairs whose chords came from the matrix cores: of the mixed
+ *                   block kernel all but those of near blocks, which are formed
+ *                   from differences (NULL allowed).
  * Sec. 2.1 (binning) is the operation; these figures let a reader count the
  * comparisons a pair needs on its path.
  */

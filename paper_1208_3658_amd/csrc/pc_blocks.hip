@@ -420,7 +420,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
     __shared__ uint32_t blk[kThreads];        // open blocks: k0 - K0 | m << 16 | flags; 0: nothing to do
     __shared__ Pending pend;
     __shared__ uint64_t sh_next[2];
-    __shared__ unsigned long long sh_stat[6]; // pairs by edges (1, 2, 3, more), items with open, with few-edge blocks
+    __shared__ unsigned long long sh_stat[7]; // pairs by edges (1, 2, 3, more), of near blocks; items with open, with few-edge blocks
     __shared__ uint32_t sh_item;              // the item has open blocks (1), blocks of a few edges (2)
     const int tid0 = static_cast<int>(threadIdx.x);
     const int wave = static_cast<int>(uni(threadIdx.x / kWave));
@@ -452,7 +452,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
     // fixed work once (no difference either way at 38,861).
     const uint64_t total = ld_uniform(p.n_items);
     const uint32_t part_bits = total >= 4ull * gridDim.x ? 0u : total * 2u >= gridDim.x ? 2u : 4u;
-    if (tid0 < 6) sh_stat[tid0] = 0ull;
+    if (tid0 < 7) sh_stat[tid0] = 0ull;
     for (int64_t w = static_cast<int64_t>(blockIdx.x) * kThreads + tid0; w < p.count_words;
          w += static_cast<int64_t>(gridDim.x) * kThreads) {
         unsigned long long v = 0;
@@ -638,8 +638,8 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
             if (np && !by_table) add_row(h, K0 + a, np);
             const bool full = !diag && i_lim == kT && j_lim == kT && part_bits != 4;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint64_t s = __builtin_amdgcn_ballot_w64(k < 3 ? m == static_cast<uint32_t>(k + 1) : m > 3u);
+            for (int k = 0; k < (F64 ? 4 : 5); ++k) {
+                const uint64_t s = __builtin_amdgcn_ballot_w64(k < 3 ? m == static_cast<uint32_t>(k + 1) : k == 3 ? m > 3u : near && m != 0u);
                 uint32_t v = static_cast<uint32_t>(__builtin_popcountll(s)) * (kG * kG);
                 if (!full) {
                     v = (s >> lane) & 1u ? np : 0u;
@@ -650,8 +650,8 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
         }
         __syncthreads();
         if (tid == 0 && sh_item) {
-            sh_stat[4] += 1ull;
-            sh_stat[5] += sh_item >> 1;
+            sh_stat[5] += 1ull;
+            sh_stat[6] += sh_item >> 1;
             sh_item = 0u;
         }
 
@@ -1031,15 +1031,15 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
     if ((tid0 & (kWave - 1)) == 0 && seen) atomicAdd(p.rechecked, static_cast<unsigned long long>(seen));
     __syncthreads();
     const unsigned long long pairs = sh_stat[0] + sh_stat[1] + sh_stat[2] + sh_stat[3];
-    if (tid0 == 0 && (pairs | sh_stat[4])) {
+    if (tid0 == 0 && (pairs | sh_stat[5])) {
         unsigned long long *st = p.stats + (blockIdx.x % kPruneStripes) * kPruneStripeWords;
         atomicAdd(st + 1, pairs);
-        atomicAdd(st + 10, pairs);
+        if (!F64) atomicAdd(st + 11, pairs - sh_stat[4]);
         atomicAdd(st + 6, sh_stat[3]);
         for (int k = 0; k < 3; ++k) atomicAdd(st + 7 + k, sh_stat[k]);
-        atomicAdd(st + 3, sh_stat[5]);
-        atomicAdd(st + 4, sh_stat[4]);
-        atomicAdd(st + 5, sh_stat[4]);
+        atomicAdd(st + 3, sh_stat[6]);
+        atomicAdd(st + 4, sh_stat[5]);
+        atomicAdd(st + 5, sh_stat[5]);
     }
 }
 

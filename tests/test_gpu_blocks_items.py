@@ -24,3 +24,22 @@ def test_items_with_open_blocks(jobs):
     assert (p["survivors"], p["split_items"], p["few_items"], p["gram_items"]) == (jobs,) * 4, p
     want = oracle.count(A, e, B=B, auto=False).tolist()
     assert all(g.tolist() == want for g in got)
+
+
+def test_pairs_of_the_matrix_cores():
+    """Chords of tiles far apart come from the product, some of a tile with itself
+    from differences, those of binary64 launches from neither."""
+    rng = np.random.default_rng(9)
+    A = 10.0 + rng.random(700), rng.random(700)
+    B = 60.0 + rng.random(900), rng.random(900)
+    a, b = (tuple(torch.from_numpy(x).cuda() for x in c) for c in (A, B))
+    e = np.array([0.01, 0.1, 49.8, 50.0, 50.2])
+    pc.pc_count(a, e, B=b, auto=False)
+    p, n = pc.pc_debug_last_paths(), pc.pc_debug_last_pruning()["pairs_computed"]
+    assert n > 0 and p["mfma"] == n and p["gram"] == 0
+    pc.pc_count(a, e)
+    p, n = pc.pc_debug_last_paths(), pc.pc_debug_last_pruning()["pairs_computed"]
+    assert 0 <= p["mfma"] < n and p["gram"] == 0
+    pc.pc_count_ex(a, e, mode=pc.PC_FP64_PLAIN)
+    p = pc.pc_debug_last_paths()
+    assert p["mfma"] == 0 and p["gram"] == 0
