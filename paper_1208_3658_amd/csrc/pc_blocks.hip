@@ -638,8 +638,8 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
             if (np && !by_table) add_row(h, K0 + a, np);
             const bool full = !diag && i_lim == kT && j_lim == kT && part_bits != 4;
 #pragma unroll
-            for (int k = 0; k < (F64 ? 4 : 5); ++k) {
-                const uint64_t s = __builtin_amdgcn_ballot_w64(k < 3 ? m == static_cast<uint32_t>(k + 1) : k == 3 ? m > 3u : near && m != 0u);
+            for (int k = 0; k < 4; ++k) {
+                const uint64_t s = __builtin_amdgcn_ballot_w64(k < 3 ? m == static_cast<uint32_t>(k + 1) : m > 3u);
                 uint32_t v = static_cast<uint32_t>(__builtin_popcountll(s)) * (kG * kG);
                 if (!full) {
                     v = (s >> lane) & 1u ? np : 0u;
@@ -647,6 +647,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
                 }
                 if (lane == 0 && v) atomicAdd(sh_stat + k, static_cast<unsigned long long>(v));
             }
+            if (near && m) atomicAdd(sh_stat + 4, static_cast<unsigned long long>(np));
         }
         __syncthreads();
         if (tid == 0 && sh_item) {
