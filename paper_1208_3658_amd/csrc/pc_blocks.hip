@@ -146,12 +146,14 @@ constexpr uint32_t table_edges(int32_t cols) { return cols >= 16 ? 3u : 4u; }
 // points 115.2 / - / 103.0 / 102.8 / 105; one (300 bins, 100,000 x 100,000 points)
 // - / 10.0 / - / 4.70 / 4.15, in 500 bins - / - / - / 7.69 / 5.70 (without a table 19.2).
 constexpr uint32_t table_edges_global(int32_t cols) { return cols >= 4 ? 5u : cols == 2 ? 8u : 12u; }
-// The same in binary64, where an edge costs a pair a comparison: whole calls with the
-// line at 3 / 4 / 5 / 8 / 12, ms: 125,000 + 250,000 points in 40 even bins (sixteen
-// columns) 7.77 / 7.69 / 8.60 / - / -, 100,000 in 30 log bins 0.667 / 0.680 / 0.693 / - / -;
-// 50,000 x 50,000 points in 254 bins (eight columns) - / 1.09 / 1.08 / 1.26 / -, in 400
-// (four) - / 1.57 / 1.46 / 1.32 / 1.54, in 500 (two) - / 2.01 / 1.93 / 1.83 / 1.59.
-constexpr uint32_t table_edges64(int32_t cols) { return cols >= 16 ? 3u : cols == 8 ? 5u : cols == 4 ? 8u : 12u; }
+// The same in binary64, where an edge costs a pair a comparison: counting kernel with
+// the line at 3 / 4 / 5 / 6 / 8, ms: 1M x 1M points in 40 log bins (sixteen columns)
+// 32.6 / 32.7 / 32.9 / 33.0 / 33.1, 100,000 x 100,000 in 30 1.12 / 1.15 / 1.16 / 1.18 / 1.21,
+// 200,000 x 200,000 in 40 even bins to half the field's width 9.53 / 9.47 / 10.5 / 10.7 /
+// 10.7; 1M x 1M in 254 log bins (eight columns) 118 / 120 / 124 / 128 / 134.  Whole calls
+// of 50,000 x 50,000 at 4 / 5 / 8 / 12 in 400 bins (four) 1.57 / 1.46 / 1.32 / 1.54, in 500
+// (two) 2.01 / 1.93 / 1.83 / 1.59.
+constexpr uint32_t table_edges64(int32_t cols) { return cols >= 8 ? 3u : cols == 4 ? 8u : 12u; }
 constexpr uint32_t kOnes = 0x3F803F80u;     // two bf16 ones
 
 struct BParams {
@@ -421,7 +423,8 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
     __shared__ Pending pend;
     __shared__ uint64_t sh_next[2];
     __shared__ unsigned long long sh_stat[7]; // pairs by edges (1, 2, 3, more), of near blocks; items with open, with few-edge blocks
-    __shared__ uint32_t sh_item;              // the item has open blocks (1), blocks of a few edges (2)
+    // a bit per item, of 32 items and the 32 before: it has open blocks, blocks of a few edges
+    __shared__ uint32_t sh_open[2], sh_few[2];
     const int tid0 = static_cast<int>(threadIdx.x);
     const int wave = static_cast<int>(uni(threadIdx.x / kWave));
 
@@ -460,7 +463,12 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
         for (int s = 0; s < kPruneStripes; ++s) v += p.copies[s * p.count_words + w];
         if (v) atomicAdd(p.counts + w, v);
     }
-    if (tid0 == 0) pend.n = sh_item = 0u;
+    if (tid0 == 0) pend.n = sh_open[0] = sh_open[1] = sh_few[0] = sh_few[1] = 0u;
+    auto add_items = [&](uint32_t r) {        // thread 0
+        sh_stat[5] += __popc(sh_open[r]);
+        sh_stat[6] += __popc(sh_few[r]);
+        sh_open[r] = sh_few[r] = 0u;
+    };
 
     for (;; ++wi) {
         // opaque per item: addresses made from it are recomputed rather than
@@ -556,6 +564,10 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
         }
         if (switched) {
             if (cur_job >= 0) flush_hist(h, cur_counts);
+            if (tid == 0) {
+                add_items(0u);
+                add_items(1u);
+            }
             if (tab != cur_tab) {
                 const TableDesc *td = p.tabs + tab;
                 h.n_edges = ld_uniform(&td->n_edges);
@@ -583,6 +595,8 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
             __syncthreads();  // the table and the cleared histogram
         }
         ++since_flush;
+        const uint32_t ring = (since_flush >> 5) & 1u, item_bit = 1u << (since_flush & 31u);
+        if (tid == 0 && (since_flush & 31u) == 0u) add_items(ring ^ 1u);
 
         // ---- the i-tile, in the product's form
 #pragma unroll
@@ -606,7 +620,9 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
         }
         // ---- classification of the wave's 64 blocks
         const float E_t = (E + 0x1p-23f * (7.0f * Dl * Dl + (Dl + R) * (Dl + R))) * (1.0f + 0x1p-16f);
-        if (classifies || part == 0) {
+        // (opaque: with the condition itself the binary64 instance took 3.5% longer, 32.5 / 31.4 ms for
+        // 1M x 1M points in 40 bins)
+        if (uni(classifies || part == 0)) {
             const float vx = fx + (si.x - sj.x), vy = fy + (si.y - sj.y), vz = fz + (si.z - sj.z);
             const float d = __builtin_amdgcn_sqrtf(fmaf(vx, vx, fmaf(vy, vy, vz * vz)));
             // outward: 12 u (D + R) covers the roundings above
@@ -627,7 +643,8 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
             if (part == 0) {
                 const uint32_t m = np ? b - a : 0u;
                 const uint64_t any = __builtin_amdgcn_ballot_w64(m != 0u), few = __builtin_amdgcn_ballot_w64(m - 1u < 3u);
-                if (lane == 0 && any) atomicOr(&sh_item, few ? 3u : 1u);
+                if (lane == 0 && any) atomicOr(sh_open + ring, item_bit);
+                if (lane == 0 && few) atomicOr(sh_few + ring, item_bit);
             }
             if (!classifies || (part_bits == 4 && cbj != static_cast<int>(part))) np = 0u;
             const uint32_t m = np ? b - a : 0u;
@@ -650,11 +667,6 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
             if (near && m) atomicAdd(sh_stat + 4, static_cast<unsigned long long>(np));
         }
         __syncthreads();
-        if (tid == 0 && sh_item) {
-            sh_stat[5] += 1ull;
-            sh_stat[6] += sh_item >> 1;
-            sh_item = 0u;
-        }
 
         // ---- the wave's columns of blocks; lane k holds the threshold of edge K0 + k
         const float h_lane = static_cast<float>(e_lds[min(K0 + static_cast<uint32_t>(lane), static_cast<uint32_t>(h.n_edges - 1))] + h_off);
@@ -1028,6 +1040,10 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
     __syncthreads();
     if (tid0 < static_cast<int>(min(pend.n, kQueued))) recheck(h, pend.a[tid0], pend.b[tid0], pend.edge[tid0], e_lds);
     if (cur_job >= 0) flush_hist(h, cur_counts);
+    if (tid0 == 0) {
+        add_items(0u);
+        add_items(1u);
+    }
     for (int o = 32; o > 0; o >>= 1) seen += __shfl_xor(seen, o, kWave);
     if ((tid0 & (kWave - 1)) == 0 && seen) atomicAdd(p.rechecked, static_cast<unsigned long long>(seen));
     __syncthreads();
