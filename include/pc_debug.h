@@ -1,5 +1,5 @@
 /*
- * pc_debug.h -- verification hooks of libpc.so (host only, no device needed).
+ * pc_debug.h -- verification hooks of libpc.so (host only unless stated).
  *
  * They expose the host-built tables that the mixed-precision kernel uses to
  * place a binary32 squared chord into a bin, so that the table logic can be
@@ -65,6 +65,15 @@ int pc_debug_fused_band(const double *theta_edges_deg, int32_t n_edges, int32_t 
  */
 int pc_debug_chord_table(const double *theta_edges_deg, int32_t n_edges, int64_t *info, uint32_t *cells,
                          int64_t max_cells);
+
+/*
+ * pc_debug_products -- n products of the block kernel's matrix instruction, for
+ * the test of the rounding that its error bound rests on: out[q] = c[q] + the sum
+ * over k < 32 of a[32 q + k] b[32 q + k], slots in order, a and b bfloat16 as their
+ * 16 bits.  Host arrays, n at most 2^20; needs the device.  PC_ERR_INVALID for
+ * another n or NULL arrays.
+ */
+int pc_debug_products(int32_t n, const uint16_t *a, const uint16_t *b, const float *c, float *out);
 
 /*
  * pc_debug_static_plan -- the bytes that a pc_count_batch_static call with these

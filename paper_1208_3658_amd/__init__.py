@@ -92,6 +92,7 @@ _SIGNATURES = {
     "pc_debug_last_workspace": ([ctypes.POINTER(_u64)], ctypes.c_int),
     "pc_debug_set_order": ([_i32], ctypes.c_int),
     "pc_debug_last_ordered": ([ctypes.POINTER(_i32)], ctypes.c_int),
+    "pc_debug_products": ([_i32, _vp, _vp, _vp, _vp], ctypes.c_int),
     "pc_debug_chord_table": ([_vp, _i32, _vp, _vp, _i64], ctypes.c_int),
     "pc_debug_set_timing": ([_i32], ctypes.c_int),
     "pc_debug_set_flush_every": ([_u64], ctypes.c_int),
@@ -462,6 +463,18 @@ def pc_debug_last_workspace() -> int:
     v = _u64(0)
     _check(lib().pc_debug_last_workspace(ctypes.byref(v)))
     return v.value
+
+
+def pc_debug_products(a, b, c):
+    """c + the sums of 32 bfloat16 products each (uint16 arrays of n x 32, n
+    float32) as the block kernel's matrix instruction forms them."""
+    a, b = (np.ascontiguousarray(x, dtype=np.uint16) for x in (a, b))
+    c = np.ascontiguousarray(c, dtype=np.float32)
+    if a.shape != (c.size, 32) or b.shape != a.shape:
+        raise ValueError("a and b must be n x 32, c n")
+    out = np.empty(c.size, dtype=np.float32)
+    _check(lib().pc_debug_products(c.size, a.ctypes.data, b.ctypes.data, c.ctypes.data, out.ctypes.data))
+    return out
 
 
 def pc_debug_chord_table(theta_edges):

@@ -53,6 +53,7 @@ namespace t256 { PC_TILE_STEPS }
 // the block kernel (pc_blocks.hip)
 namespace blk {
 hipError_t launch_bounds(const ViewDesc *views, int n_views, int64_t tiles, hipStream_t st);
+hipError_t launch_products(int32_t n, const uint16_t *a, const uint16_t *b, const float *c, float *out);
 void lds_layout(bool fp64, bool few_pairs, double edges_met, int32_t max_edges, int32_t max_cells, int32_t cols, int32_t *cols_out, int32_t *cells_out,
                 uint32_t *lds_bytes);
 hipError_t occupancy(bool fp64, bool global_table, uint32_t lds_bytes, int *per_cu);
@@ -1539,6 +1540,32 @@ extern "C" int pc_debug_static_plan(const pc_job *jobs, int32_t n_jobs, int32_t 
     o.plan_bytes = need;
     o.ws_bytes = bytes;
     return run_batch_opts(v, mode, nullptr, nullptr, o);
+}
+
+extern "C" int pc_debug_products(int32_t n, const uint16_t *a, const uint16_t *b, const float *c, float *out) {
+    clear_error();
+    if (n < 0 || n > (1 << 20)) return fail(PC_ERR_INVALID, "n must be in [0, 2^20]");
+    if (n == 0) return PC_OK;
+    if (!a || !b || !c || !out) return fail(PC_ERR_INVALID, "NULL argument");
+    DeviceInfo *di = nullptr;
+    const int rc = device_info(&di);
+    if (rc) return rc;
+    const size_t k = static_cast<size_t>(n);
+    struct Free {
+        void *p = nullptr;
+        ~Free() {
+            if (p) (void)hipFree(p);
+        }
+    } m;
+    PC_HIP(hipMalloc(&m.p, 136 * k), "hipMalloc(products)");
+    float *const dc = static_cast<float *>(m.p), *const dout = dc + k;
+    uint16_t *const da = reinterpret_cast<uint16_t *>(dout + k), *const db = da + 32 * k;
+    PC_HIP(hipMemcpy(da, a, 64 * k, hipMemcpyHostToDevice), "H2D a");
+    PC_HIP(hipMemcpy(db, b, 64 * k, hipMemcpyHostToDevice), "H2D b");
+    PC_HIP(hipMemcpy(dc, c, 4 * k, hipMemcpyHostToDevice), "H2D c");
+    PC_HIP(blk::launch_products(n, da, db, dc, dout), "products");
+    PC_HIP(hipMemcpy(out, dout, 4 * k, hipMemcpyDeviceToHost), "D2H products");
+    return PC_OK;
 }
 
 extern "C" int pc_debug_chord_table(const double *theta_edges_deg, int32_t n_edges, int64_t *info, uint32_t *cells,
