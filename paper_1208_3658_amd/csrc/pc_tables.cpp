@@ -318,38 +318,40 @@ void build_lut32(const std::vector<float> &lo, const std::vector<float> &hi, uin
 // with q(x) = x 2^(S-26), at most a quarter of the narrower cell next to x.  A
 // chord known to within E_t of its exact value, E_t <= q(c) / 2 (so E_t <= q(mn):
 // c < 2 mn), is then placed by its cell's edge alone unless it is within E_t of
-// that edge: any other edge is farther than E_t from it.  The coarsest S that leaves no cell with two edges,
-// within kMaxChordCells cells; none: no table.  One cell more at each end takes
-// the chords outside.
+// that edge: any other edge is farther than E_t from it.  The coarsest S that leaves
+// no cell with two edges, within kMaxChordCells cells; none: no table.  One cell more
+// at each end takes the chords outside.
 void build_lutb(HostTable &t) {
     t.lutb.clear();
     const int n = static_cast<int>(t.e64.size());
     int first = 0;
     while (first < n && t.e64[first] < 0x1p-100) ++first;  // edges at (or next to) 0
     if (first == n || (first > 0 && t.e64[first - 1] > 0.0)) return;
-    for (int s = 22; s >= 12; --s) {
+    for (int s = 22; s >= kMinChordShift; --s) {
         const uint32_t c0 = (f2u(static_cast<float>(t.e64[first])) >> s) - 1, c1 = (f2u(static_cast<float>(t.e64[n - 1])) >> s) + 1;
         if (c1 - c0 + 1 > static_cast<uint32_t>(kMaxChordCells)) return;
-        std::vector<LutEntryB> cells;
+        const double q = std::ldexp(1.0, s - 26);
+        auto mn = [&](uint32_t c) { return static_cast<double>(u2f(c << s)) * (1.0 - q); };
+        auto mx = [&](uint32_t c) { return static_cast<double>(u2f((c + 1) << s)) * (1.0 + q); };
+        // the cells that an edge belongs to, all within one of its own (the last edges'
+        // first: where no S will do it is mostly they that crowd)
+        auto lowest = [&](double e, uint32_t c) { return e <= mx(c - 1) ? c - 1 : c; };
+        auto highest = [&](double e, uint32_t c) { return e >= mn(c + 1) ? c + 1 : c; };
+        auto own = [&](double e) { return f2u(static_cast<float>(e)) >> s; };
         bool ok = true;
-        int below = first, above = first;  // edges under the cell's reach, edges not past it
-        for (uint32_t c = c0; c <= c1 && ok; ++c) {
-            const double q = std::ldexp(1.0, s - 26);
-            const double mn = static_cast<double>(u2f(c << s)) * (1.0 - q), mx = static_cast<double>(u2f((c + 1) << s)) * (1.0 + q);
-            while (below < n && t.e64[below] < mn) ++below;
-            while (above < n && t.e64[above] <= mx) ++above;
-            ok = above - below <= 1;
-            LutEntryB e;
-            e.e = above > below ? static_cast<float>(t.e64[below]) : std::numeric_limits<float>::infinity();
-            e.row = static_cast<uint32_t>(below);
-            cells.push_back(e);
+        for (int k = n - 1; k > first && ok; --k)
+            ok = highest(t.e64[k - 1], own(t.e64[k - 1])) < lowest(t.e64[k], own(t.e64[k]));
+        if (!ok) continue;
+        t.b_shift = static_cast<uint32_t>(s);
+        t.b_key0 = c0;
+        t.lutb.resize(c1 - c0 + 1);
+        uint32_t c = c0;
+        for (int k = first; k <= n; ++k) {  // up to edge k's cells, and those
+            const uint32_t to = k < n ? lowest(t.e64[k], own(t.e64[k])) : c1 + 1, end = k < n ? highest(t.e64[k], own(t.e64[k])) + 1 : to;
+            for (; c < to; ++c) t.lutb[c - c0] = {std::numeric_limits<float>::infinity(), static_cast<uint32_t>(k)};
+            for (; c < end; ++c) t.lutb[c - c0] = {static_cast<float>(t.e64[k]), static_cast<uint32_t>(k)};
         }
-        if (ok) {
-            t.lutb = cells;
-            t.b_shift = static_cast<uint32_t>(s);
-            t.b_key0 = c0;
-            return;
-        }
+        return;
     }
 }
 

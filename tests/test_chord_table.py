@@ -12,6 +12,7 @@ SETS = {f"even_{k}": synth.linear_edges(0.0, 10.0, k) for k in (4, 30, 60, 100, 
 SETS.update({f"log_{k}": synth.log_edges(0.01, 20.0, k) for k in (12, 40, 150, 254, 300, 400, 500, 700, 1023)})
 SETS["wide_1023"] = synth.log_edges(1e-3, 170.0, 1023)
 SETS["even_from_1"] = synth.linear_edges(1.0, 10.0, 300)
+SETS.update({f"even_{k}_to_{hi}": synth.linear_edges(0.0, float(hi), k) for k, hi in ((100, 180), (179, 180), (400, 178), (1023, 170))})
 
 
 @pytest.mark.parametrize("name", sorted(SETS))
